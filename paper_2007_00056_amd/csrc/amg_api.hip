@@ -289,8 +289,7 @@ struct SetupWork {
     int* novf = nullptr;
     int* hc = nullptr;  // pinned: worklist sizes read back between batches
     hipEvent_t ev[2]{};
-    int hem_small = 65536;  // passes on at most this many rows run in one workgroup
-    bool tile_strict = false;  // a tiled pass past its time limit is an error (tests), not repeated
+    bool tile_strict = false;  // a pass past its time limit is an error (tests), not repeated
 
     bool edge = false;  // edge-based matching (Algorithm 3)
     int* mrp = nullptr;  // mirrored matrix of a pass from the last index
@@ -302,20 +301,22 @@ struct SetupWork {
         if (edge) {
             hw.wsym = P.get<double>((size_t)nnz);
             hw.ptr = P.get<int>(n);
+            hw.lcnt = P.get<int>(n);
+            hw.dec = P.get<int>(n);
+            hw.wl[0] = P.get<int>(n);
+            hw.wl[1] = P.get<int>(n);
+        } else {
+            hw.rec_ints = 16 * (size_t)n;
+            hw.rec = P.get<int>(hw.rec_ints);
+            hw.deg = P.get<int2>(n);
+            hw.gw = P.get<unsigned>(n);
+            hw.xw = P.get<unsigned>(hem_ext_words(nnz));
         }
         if (alternate) {  // every later pass has at most n rows and nnz entries
             mrp = P.get<int>((size_t)n + 1);
             mci = P.get<int>((size_t)nnz);
             mv = P.get<double>((size_t)nnz);
         }
-        hw.lowok = P.get<uint8_t>((size_t)nnz);
-        hw.rec_bytes = sizeof(HemRecT<7>) * (size_t)n;
-        hw.rec = P.get<char>(hw.rec_bytes);
-        hw.side = 7;
-        hw.lcnt = P.get<int>(n);
-        hw.dec = P.get<int>(n);
-        hw.wl[0] = P.get<int>(n);
-        hw.wl[1] = P.get<int>(n);
         hw.cnt = P.get<int>(8);
         hw.err = err;
         for (int t = 0; t < 2; ++t) {
@@ -332,14 +333,9 @@ struct SetupWork {
         hc = pinned_words() + 32;  // this thread's pinned words, past the read-back area
         ev[0] = event_get(false);
         ev[1] = event_get(false);
-        if (const char* e = getenv("HEMAMG_HEM_SMALL")) hem_small = atoi(e);  // tuning sweeps
         if (const char* e = getenv("HEMAMG_HEM_GRID")) hw.round_grid = atoi(e) > 0 ? atoi(e) : 96;
-        if (const char* e = getenv("HEMAMG_HEM_LDS")) hw.lds_rows = atoi(e) < kHemLdsRows ? atoi(e) : kHemLdsRows;
         if (const char* e = getenv("HEMAMG_TILE_STRICT")) tile_strict = atoi(e) != 0;
-        if (const char* e = getenv("HEMAMG_HEM_TILE"))  // rows per tile; 0: no tiled passes
-            hw.tile_rows = atoi(e) <= 0 ? 0 : (atoi(e) < kHemTileRows ? atoi(e) : kHemTileRows);
-        if (const char* e = getenv("HEMAMG_HEM_TILE_C"))  // rows per LDS-record tile; 0: not used
-            hw.tile_c_rows = atoi(e) <= 0 ? 0 : (atoi(e) < kHemTileCRows ? atoi(e) : kHemTileCRows);
+        if (const char* e = getenv("HEMAMG_HEM_TILE")) hw.tile_rows = atoi(e) > 0 ? atoi(e) : 0;  // rows per tile
     }
     ~SetupWork() {
         event_put(ev[0], false);
@@ -369,7 +365,7 @@ void run_rounds(SetupWork& W, HemWork& w, int n, hipStream_t s, Launch&& launch_
     for (int j = 0;; ++j) {
         for (int b = 0; b < batch; ++b, ++r) launch_round(r);
         HIPCHK(hipGetLastError());
-        HIPCHK(hipMemcpyAsync(&W.hc[j & 1], w.cnt + hem_next_count_slot(r), sizeof(int), hipMemcpyDeviceToHost, s));
+        HIPCHK(hipMemcpyAsync(&W.hc[j & 1], w.cnt + r % 3, sizeof(int), hipMemcpyDeviceToHost, s));
         HIPCHK(hipEventRecord(W.ev[j & 1], s));
         if (j >= 1) {
             HIPCHK(hipEventSynchronize(W.ev[(j - 1) & 1]));
@@ -379,8 +375,8 @@ void run_rounds(SetupWork& W, HemWork& w, int n, hipStream_t s, Launch&& launch_
     }
 }
 
-// Time limit of a tiled pass in wall-clock ticks (250 ms; a pass of a few
-// million rows takes a few milliseconds).
+// Time limit of a node-based pass in wall-clock ticks (250 ms; a pass of a few
+// million rows takes well under one).
 long long tile_timeout_ticks() {
     thread_local int dev = -1;
     thread_local long long ticks = 0;
@@ -395,33 +391,9 @@ long long tile_timeout_ticks() {
     return ticks;
 }
 
-bool tiled(const HemWork& w, int n) {
-    return w.tile_rows > 0 && ((int64_t)n + w.tile_rows - 1) / w.tile_rows <= kHemMaxTiles;
-}
-
-// A tiled pass; false when it did not finish (the caller repeats the pass).
-bool run_tiles(SetupWork& W, HemWork& w, const Csr& B, hipStream_t s) {
-    launch_hem_tile(B.n, B.nnz, B.rp, B.ci, B.v, w, tile_timeout_ticks(), s);
-    HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(&W.hc[2], w.cnt + 7, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    return W.hc[2] == 0;
-}
-
-// Systems of a batched setup inside the operator of a pass: seg = device table
-// of (first row, rows) in the pass's numbering.  Systems up to the LDS limit
-// are matched one workgroup each; the round kernels run only for larger ones.
-struct SegPass {
-    const int2* seg = nullptr;
-    int nseg = 0;
-    bool all_small = false;
-    int* sl[2] = {nullptr, nullptr};  // list space, a row per vertex each
-};
-
 // from_last: the pass starts from the last index (run on the mirrored matrix,
 // its pairs mapped back before numbering).
-Pass hem_pass(const Csr& Bin, SetupWork& W, int t, hipStream_t s, int* err, bool from_last,
-              const SegPass* sp = nullptr) {
+Pass hem_pass(const Csr& Bin, SetupWork& W, int t, hipStream_t s, bool from_last, long long tmo) {
     const int n = Bin.n;
     Csr B = Bin;
     HemWork w = W.hw;
@@ -433,39 +405,13 @@ Pass hem_pass(const Csr& Bin, SetupWork& W, int t, hipStream_t s, int* err, bool
         B.v = W.mv;
         w.mate = W.agg[t];  // free until numbering writes the aggregate map
     }
-    // record side from the average row length, within the record buffer
-    const double avg = n > 0 ? (double)B.nnz / n : 0.0;
-    // workgroup-wide drivers (one workgroup, tiles) take records of at most 15
-    w.side = avg <= 9.0 ? 7 : (avg <= 20.0 || n <= W.hem_small || tiled(w, n) ? 15 : 31);
-    while (w.side > 7 && (size_t)(w.side + 1) * 8 * (size_t)n > w.rec_bytes) w.side = (w.side + 1) / 2 - 1;
     HIPCHK(hipMemsetAsync(w.cnt, 0, 8 * sizeof(int), s));
     if (W.edge) {
         launch_ehem_init(n, B.rp, B.ci, B.v, w, s);
         run_rounds(W, w, n, s, [&](int r) { launch_ehem_round(r, n, B.rp, B.ci, w, s); });
     } else {
-        // small passes: one workgroup with LDS state; larger ones: tiles, else
-        // one workgroup with global state or one launch per round
-        auto start = [&] {
-            launch_hem_init(n, B.rp, B.ci, B.v, w, s);
-            if (sp) launch_hem_lds_seg(sp->nseg, sp->seg, B.rp, B.ci, B.v, w, sp->sl[0], sp->sl[1], s);
-            HIPCHK(hipGetLastError());
-        };
-        auto rounds = [&] { run_rounds(W, w, n, s, [&](int r) { launch_hem_round(r, n, B.rp, B.ci, B.v, w, s); }); };
-        start();
-        if (sp ? sp->all_small : n <= W.hem_small && n <= w.lds_rows) {
-            if (!sp) launch_hem_all(n, B.rp, B.ci, B.v, w, s);
-        } else if (tiled(w, n)) {
-            if (!run_tiles(W, w, B, s)) {  // past its time limit: repeat with the round kernels
-                if (W.tile_strict) raise(AMG_EHIP, "tiled matching pass did not finish in time");
-                HIPCHK(hipMemsetAsync(w.cnt, 0, 8 * sizeof(int), s));
-                start();
-                rounds();
-            }
-        } else if (!sp && n <= W.hem_small) {
-            launch_hem_all(n, B.rp, B.ci, B.v, w, s);
-        } else {
-            rounds();
-        }
+        launch_hem_init(n, B.nnz, B.rp, B.ci, B.v, w, s);
+        launch_hem_tile(n, B.rp, B.ci, B.v, w, tmo, s);
         HIPCHK(hipGetLastError());
     }
     if (from_last) {
@@ -491,14 +437,16 @@ Pass hem_pass(const Csr& Bin, SetupWork& W, int t, hipStream_t s, int* err, bool
 // are formed over an upper bound of the coarse size (rows past it count 0),
 // so one read-back returns the coarse size, its nonzero count, the matching
 // counters and the error word together.
-Csr galerkin(const Csr& B, Pass& P, SetupWork& W, DevPool& out, hipStream_t s, const int* err) {
+// `late`: the matching ran past its time limit (nothing is formed then).
+Csr galerkin(const Csr& B, Pass& P, SetupWork& W, DevPool& out, hipStream_t s, const int* err, int*& crp, bool& late) {
     const int nmax = P.n;  // coarse rows <= fine rows
     const int* ncp = W.ids + P.n;
     HIPCHK(hipMemsetAsync(W.novf, 0, sizeof(int), s));
     launch_rap_count(nmax, ncp, P.lead, P.mate, B.rp, B.ci, P.agg, W.rowcnt, W.ovf, W.novf, s);
     launch_rap_count_slow(nmax, W.ovf, W.novf, P.lead, P.mate, B.rp, B.ci, P.agg, W.rowcnt, s);
     Csr C;
-    C.rp = out.get<int>((size_t)nmax + 1);
+    if (!crp) crp = out.get<int>((size_t)nmax + 1);
+    C.rp = crp;
     launch_scan(W.rowcnt, nmax, C.rp, W.stmp, s);
     HIPCHK(hipGetLastError());
     int* dw = nullptr;
@@ -508,7 +456,8 @@ Csr galerkin(const Csr& B, Pass& P, SetupWork& W, DevPool& out, hipStream_t s, c
     HIPCHK(hipStreamSynchronize(s));
     raise_err_word(hw[10], "amg_setup");
     if (hw[5] != 0) raise(AMG_EINVAL, "matching: sparsity pattern is not structurally symmetric");
-    if (hw[7] != 0) raise(AMG_EHIP, "matching did not terminate (internal error)");
+    late = hw[7] != 0;
+    if (late) return C;
     P.rounds = hw[6];
     P.nc = hw[8];
     C.n = P.nc;
@@ -519,6 +468,29 @@ Csr galerkin(const Csr& B, Pass& P, SetupWork& W, DevPool& out, hipStream_t s, c
     launch_rap_fill_slow(P.nc, W.ovf, W.novf, P.lead, P.mate, B.rp, B.ci, B.v, P.agg, C.rp, C.ci, C.v, s);
     HIPCHK(hipGetLastError());
     return C;
+}
+
+// One matching pass on B and its Galerkin product.  A pass past its time limit
+// (a device shared with work that holds it up) is repeated with 16 times the
+// limit, twice.
+Csr coarsen_pass(const Csr& B, Pass& P, SetupWork& W, int t, DevPool& out, hipStream_t s, const int* err,
+                 bool from_last, std::vector<hipEvent_t>* marks = nullptr) {
+    auto mark = [&] {
+        if (!marks) return;
+        marks->push_back(event_get(true));
+        HIPCHK(hipEventRecord(marks->back(), s));
+    };
+    long long tmo = tile_timeout_ticks();
+    int* crp = nullptr;
+    mark();
+    for (int k = 0;; ++k, tmo *= 16) {
+        P = hem_pass(B, W, t, s, from_last, tmo);
+        if (k == 0) mark();
+        bool late = false;
+        const Csr C = galerkin(B, P, W, out, s, err, crp, late);
+        if (!late) return C;
+        if (k == 2 || W.tile_strict) raise(AMG_EHIP, "matching pass did not finish in time");
+    }
 }
 
 void alloc_workspace(amg_hier* h) {
@@ -1154,7 +1126,7 @@ void setup_impl(const amg_csr* Ain, const amg_params* pin, const amg_allocator* 
     DevPool wpool;
     wpool.s = s;
     wpool.al = al;
-    wpool.hint((size_t)A.nnz * (p.hem == 1 ? 9 : 1) + 168 * (size_t)A.n + 4096 +
+    wpool.hint((size_t)A.nnz * (p.hem == 1 ? 8 : 0) + 4 * hem_ext_words(A.nnz) + 128 * (size_t)A.n + 4096 +
                (p.alternate ? 12 * (size_t)A.nnz + 4 * (size_t)A.n : 0));
     struct WpoolGuard {
         DevPool& t;
@@ -1172,10 +1144,6 @@ void setup_impl(const amg_csr* Ain, const amg_params* pin, const amg_allocator* 
             for (hipEvent_t e : v) event_put(e, true);
         }
     } evg{pev};
-    auto mark_pass = [&](hipStream_t st) {
-        pev.push_back(event_get(true));
-        HIPCHK(hipEventRecord(pev.back(), st));
-    };
     for (int k = 0;; ++k) {
         Level& F = h->lev[k];
         if (F.n <= p.max_coarse_rows) break;
@@ -1195,24 +1163,19 @@ void setup_impl(const amg_csr* Ain, const amg_params* pin, const amg_allocator* 
         Csr B{F.n, F.nnz, const_cast<int*>(F.rp), const_cast<int*>(F.ci), const_cast<double*>(F.v)};
         // setup-wide pass index: with alternate, odd passes start from the last index
         const int g0 = k * p.passes_per_level;
-        mark_pass(s);
-        Pass p1 = hem_pass(B, SW, 0, s, h->err, p.alternate && (g0 & 1));
-        mark_pass(s);
         h->pass_n.push_back(B.n);
         h->pass_nnz.push_back(B.nnz);
         DevPool& out1 = (p.passes_per_level == 1) ? P : tmp;
-        Csr C1 = galerkin(B, p1, SW, out1, s, h->err);
+        Pass p1, p2;
+        Csr C1 = coarsen_pass(B, p1, SW, 0, out1, s, h->err, p.alternate && (g0 & 1), &pev);
         h->rounds.push_back(p1.rounds);
         Csr Cf = C1;
         int* agg = nullptr;
         int4* mem = nullptr;
         if (p.passes_per_level == 2) {
-            mark_pass(s);
-            Pass p2 = hem_pass(C1, SW, 1, s, h->err, p.alternate && ((g0 + 1) & 1));
-            mark_pass(s);
             h->pass_n.push_back(C1.n);
             h->pass_nnz.push_back(C1.nnz);
-            Cf = galerkin(C1, p2, SW, P, s, h->err);
+            Cf = coarsen_pass(C1, p2, SW, 1, P, s, h->err, p.alternate && ((g0 + 1) & 1), &pev);
             h->rounds.push_back(p2.rounds);
             agg = P.get<int>(F.n);
             launch_compose(F.n, p1.agg, p2.agg, agg, s);
@@ -1544,7 +1507,7 @@ void batch_coarsen(const amg_csr* A, int count, const amg_params& p, hipStream_t
     DevPool wpool;
     wpool.s = s;
     wpool.al = P.al;
-    wpool.hint((size_t)E * (p.hem == 1 ? 9 : 1) + 168 * (size_t)N + 4096 +
+    wpool.hint((size_t)E * (p.hem == 1 ? 8 : 0) + 4 * hem_ext_words(E) + 128 * (size_t)N + 4096 +
                (p.alternate ? 12 * (size_t)E + 4 * (size_t)N : 0));
     struct WpoolGuard {
         DevPool& t;
@@ -1555,13 +1518,6 @@ void batch_coarsen(const amg_csr* A, int count, const amg_params& p, hipStream_t
     int* starts = P.get<int>(2 * (size_t)count);
     int* offs_d = P.get<int>((size_t)count);
     std::vector<int> hs(2 * (size_t)count + 2), ho((size_t)count);
-    // node-based passes match each system of at most the LDS limit in a
-    // workgroup of its own (its rounds run concurrently with the others')
-    const bool seg_ok = p.hem == 0;
-    int2* seg_d[2] = {P.get<int2>((size_t)count), P.get<int2>((size_t)count)};
-    int* sl0 = seg_ok ? wpool.get<int>((size_t)N) : nullptr;
-    int* sl1 = seg_ok ? wpool.get<int>((size_t)N) : nullptr;
-    std::vector<int2> hseg((size_t)count);
     for (int k = 0; !live.empty(); ++k) {
         std::vector<char> want(live.size(), 0);
         bool any = false;
@@ -1585,32 +1541,13 @@ void batch_coarsen(const amg_csr* A, int count, const amg_params& p, hipStream_t
         for (int j = 0; j < m; ++j) ho[j] = live[j].off;
         HIPCHK(hipMemcpyAsync(offs_d, ho.data(), sizeof(int) * m, hipMemcpyHostToDevice, s));
         const bool fl1 = p.alternate && (g0 & 1), fl2 = p.alternate && ((g0 + 1) & 1);
-        SegPass sp1, sp2;
-        if (seg_ok) {
-            int big = 0;
-            for (int j = 0; j < m; ++j) {
-                const Live& L = live[j];
-                hseg[j] = fl1 ? make_int2(M.n - L.off - L.n, L.n) : make_int2(L.off, L.n);
-                big = std::max(big, L.n);
-            }
-            HIPCHK(hipMemcpyAsync(seg_d[0], hseg.data(), sizeof(int2) * m, hipMemcpyHostToDevice, s));
-            sp1.seg = seg_d[0];
-            sp1.nseg = m;
-            sp1.all_small = big <= SW.hw.lds_rows;  // a system's later passes are smaller
-            sp1.sl[0] = sl0;
-            sp1.sl[1] = sl1;
-            sp2 = sp1;
-            sp2.seg = seg_d[1];
-        }
-        Pass p1 = hem_pass(M, SW, 0, s, gerr, fl1, seg_ok ? &sp1 : nullptr);
-        Csr C1 = galerkin(M, p1, SW, P, s, gerr);
+        Pass p1, p2;
+        Csr C1 = coarsen_pass(M, p1, SW, 0, P, s, gerr, fl1);
         Csr Cf = C1;
         int* agg = P.get<int>((size_t)M.n);
         int4* mem = nullptr;
         if (p.passes_per_level == 2) {
-            if (seg_ok) launch_seg_table(m, offs_d, p1.agg, C1.n, fl2, seg_d[1], s);
-            Pass p2 = hem_pass(C1, SW, 1, s, gerr, fl2, seg_ok ? &sp2 : nullptr);
-            Cf = galerkin(C1, p2, SW, P, s, gerr);
+            Cf = coarsen_pass(C1, p2, SW, 1, P, s, gerr, fl2);
             launch_compose(M.n, p1.agg, p2.agg, agg, s);
             mem = P.get<int4>((size_t)Cf.n);
             launch_members(Cf.n, p2.lead, p2.mate, p1.lead, p1.mate, mem, s);

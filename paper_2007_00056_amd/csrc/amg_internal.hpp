@@ -27,74 +27,39 @@ void launch_validate(int n, int64_t nnz, const int* rp, const int* ci, const dou
                      hipStream_t s);
 void launch_dinv(int n, const int* rp, const int* ci, const double* v, double* dinv, int* err, hipStream_t s);
 
-// Per-vertex adjacency record of a matching pass (64, 128 or 256 bytes for
-// SIDE = 7, 15, 31): the first SIDE higher neighbours j (a_uj non-zero) by
-// |a_uj| descending, column ascending on ties, and the first SIDE lower
-// edge-neighbours x (row x stores a non-zero a_xu) ascending.  kRecHiTrunc /
-// kRecLoTrunc: the row has more of them (the first undecided entry of a list
-// is still the vertex's choice when the list has one; otherwise the CSR row
-// decides); kRecOverflow: either.
-constexpr int kRecOverflow = 1 << 16;
-constexpr int kRecHiTrunc = 1 << 17;
-constexpr int kRecLoTrunc = 1 << 18;
-constexpr int kHemLdsRows = 32768;  // passes up to this size keep their matching state in LDS
-constexpr int kHemTileRows = 32768;  // largest tile of a tiled pass (its state in LDS)
-constexpr int kHemMaxTiles = 4096;   // tiled passes up to this many tiles
-constexpr int kHemTileCRows = 4096;  // largest tile whose records are kept in LDS
-template <int SIDE>
-struct alignas(4 * (SIDE + 1) * 2) HemRecT {
-    int hdr;  // #higher | #lower << 8 | kRecOverflow | kRecHiTrunc | kRecLoTrunc
-    int h[SIDE];
-    int l[SIDE];
-    int pad;
-};
-static_assert(sizeof(HemRecT<7>) == 64 && sizeof(HemRecT<15>) == 128 && sizeof(HemRecT<31>) == 256, "record");
-
+// Buffers of a matching pass (k_hem.hip).
 struct HemWork {
-    uint8_t* lowok;   // [nnz] entry (v,u), u < v, is an edge (row u stores a non-zero a_uv)
-    void* rec;        // adjacency records, rec_bytes of room
-    size_t rec_bytes;
-    int side;         // record side of the current pass: 7, 15 or 31
-    int* lcnt;        // [n] undecided lower neighbours
-    int* dec;         // [n] round in which the vertex was decided
+    int* rec;         // records of 4, 16 or 32 entries a vertex
+    size_t rec_ints;  // room for them
+    int2* deg;        // [n] lower entries (or extension offset) and higher edge-neighbours
+    unsigned* gw;     // [n] a vertex's word as set by other tiles
+    unsigned* xw;     // [hem_ext_words(nnz)] extension words of rows with many lower entries
     int* mate;        // [n] partner or -1
-    int* wl[2];       // [n] ready worklists (ping-pong)
-    int* cnt;         // [8] worklist size ring, symmetry check, round count, guard
+    int* cnt;         // [8] tiles started, extension words, symmetry check, sweeps, time limit
     int* err;
-    int round_grid = 96;  // blocks of a one-launch-per-round pass
-    int tile_rows = kHemTileRows;  // rows per tile of a tiled pass (0: no tiled passes)
-    int tile_c_rows = kHemTileCRows;  // rows per LDS-record tile (0: not used; below kHemTileCRows: every
-                                      // side-7 pass takes them, for tests)
-    int lds_rows = kHemLdsRows;  // one-workgroup passes up to this size keep their state in LDS
-    double* wsym = nullptr;  // edge-based matching: [nnz] heavier of |a_uv|, |a_vu| (0 on the diagonal)
-    int* ptr = nullptr;      // edge-based matching: [n] best undecided neighbour
+    int side = 4;            // entries of the current pass's records
+    int tile_rows = 0;       // rows per tile, at most what a workgroup takes (0: that many)
+    // edge-based matching
+    int* dec;         // [n] round in which the vertex was decided
+    int* lcnt;        // [n] round marks
+    int* wl[2];       // [n] worklists (ping-pong)
+    double* wsym = nullptr;  // [nnz] heavier of |a_uv|, |a_vu| (0 on the diagonal)
+    int* ptr = nullptr;      // [n] best undecided neighbour
+    int round_grid = 96;     // blocks of a round's launches
 };
-// w.cnt must be zeroed before the call.
-void launch_hem_init(int n, const int* rp, const int* ci, const double* v, HemWork& w, hipStream_t s);
-void launch_hem_round(int round, int n, const int* rp, const int* ci, const double* v, HemWork& w, hipStream_t s);
-// All rounds in one single-workgroup launch (small n).
-void launch_hem_all(int n, const int* rp, const int* ci, const double* v, HemWork& w, hipStream_t s);
-// Tiled pass: one workgroup per w.tile_rows rows, all rounds in one launch
-// (after launch_hem_init and, for block-diagonal operators, launch_hem_lds_seg;
-// w.side 7 or 15).
-// cnt[7] != 0 afterwards: the pass did not finish within tmo wall-clock ticks
-// (or a counter exceeded 16 bits) and must be repeated with the round kernels.
-void launch_hem_tile(int n, int64_t nnz, const int* rp, const int* ci, const double* v, HemWork& w, long long tmo,
-                     hipStream_t s);
-// Block-diagonal operators: seg[j] = (first row, rows) of system j; systems of
-// at most kHemLdsRows rows are matched one workgroup each and marked decided
-// (stamp -1) for the round kernels.  sl0/sl1: global list space, n rows each.
-void launch_hem_lds_seg(int nseg, const int2* seg, const int* rp, const int* ci, const double* v, HemWork& w,
-                        int* sl0, int* sl1, hipStream_t s);
-// seg[j] for the operator of the next pass: system j starts at agg[off[j]]
-// (n rows in all; mirror numbers the operator backwards).
-void launch_seg_table(int m, const int* off, const int* agg, int n, bool mirror, int2* seg, hipStream_t s);
+// Extension words of a pass: a row of more than 31 lower entries takes one word
+// and one per 32 of them (at most 3/32 of their number).
+inline size_t hem_ext_words(int64_t nnz) { return (size_t)(nnz / 10 + 64); }
+// Node-based pass (w.cnt must be zeroed before the initialisation): all tiles
+// in one launch.  cnt[7] != 0 afterwards: it did not finish within tmo
+// wall-clock ticks and must be repeated.
+void launch_hem_init(int n, int64_t nnz, const int* rp, const int* ci, const double* v, HemWork& w, hipStream_t s);
+void launch_hem_tile(int n, const int* rp, const int* ci, const double* v, HemWork& w, long long tmo, hipStream_t s);
 // Edge-based matching (Algorithm 3): initialisation (every vertex dirty, the
 // count in cnt[0]; w.lcnt serves as the per-round marks) and one round (two
 // launches).  w.cnt must be zeroed before the initialisation.
 void launch_ehem_init(int n, const int* rp, const int* ci, const double* v, HemWork& w, hipStream_t s);
 void launch_ehem_round(int r, int n, const int* rp, const int* ci, HemWork& w, hipStream_t s);
-int hem_next_count_slot(int round);  // counter slot that holds |worklist| before `round`
 
 // Exclusive prefix sum: out[i] = sum in[0..i), out[n] = total.  tmp: scan_tmp_ints(n).
 size_t scan_tmp_ints(int n);

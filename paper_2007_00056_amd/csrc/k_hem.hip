@@ -1,27 +1,27 @@
 // Node-based heavy edge matching (Section 2.1.1, Algorithm 2) on the GPU.
 //
-// Visiting vertices in ascending order (Algorithm 2) is the greedy matching
-// over edges {u < w} (a_uw stored in row u, non-zero) in increasing key
-// (u, -|a_uw|, w).  Greedy matching in a strict edge order equals repeated
-// rounds of locally dominant edges: each undecided vertex points along its
-// smallest-key edge to an undecided neighbour, mutual pointers match, and a
-// vertex with no undecided neighbour is a singleton.  Under this key a vertex
-// points to its smallest undecided lower neighbour if it has one, otherwise
-// to its heaviest undecided higher neighbour (lowest index on ties).  Only a
-// vertex without undecided lower neighbours ("ready") can start a match, so
-// each round scans a worklist of ready vertices, and a per-vertex count of
-// undecided lower neighbours adds vertices to the next list as they become
-// ready.  Decisions carry the round number: a vertex counts as undecided in
-// round r while its stamp is >= r, so all reads in a round see the state at
-// the start of the round whatever the interleaving.
+// Algorithm 2 visits the vertices in ascending order; an unmatched vertex v
+// takes its heaviest unmatched higher neighbour (lowest index on ties; the
+// lower ones are matched, or were left alone, by then).  Whether edge v -> w
+// (v < w) is taken depends on lower vertices alone:
 //
-// Drivers: one workgroup with the round stamps, ready counters and worklists
-// in LDS (passes up to kHemLdsRows rows; a round costs the two adjacency
-// record loads), the same per system of a block-diagonal batch, and tiles of
-// consecutive rows with one such workgroup each, all in one launch (larger
-// passes; the tiles exchange decisions through one published word per
-// vertex).  One kernel launch per round over the whole GPU and one workgroup
-// with the state in global memory remain for passes the tiles do not take.
+//   avail(w, v)  no edge x -> w with x < v is taken
+//   take(v -> w) no edge x -> v is taken, avail(w, v), and no neighbour that
+//                v prefers to w is available to v
+//
+// Each vertex keeps one word: bit k says that its k-th lower edge (in column
+// order) is known not to be taken ("dead"); the top bit says that one is
+// taken, and then every other bit is set, so the zero bit names the taker.
+// avail(w, v) holds once the bits below v's position in w's word are all set,
+// and fails once the top bit is set without that.  v walks its preference
+// list: an unavailable choice is skipped; an available one makes all later
+// edges of v dead at once (whatever becomes of v); and once all of v's own
+// lower edges are dead, v takes it.  A taken vertex makes all its edges dead.
+//
+// Bits are only ever set, and each is a fact of the one greedy matching, so
+// a stale word only delays: no rounds, no barriers and no order between
+// words are needed, and the result is Algorithm 2's, bit for bit, whatever
+// the timing.  The lowest undecided vertex can always decide, so the walk ends.
 #include <cstdint>
 
 #include "amg_device.hpp"
@@ -47,7 +47,6 @@ __device__ __forceinline__ int find_col(const int* __restrict__ ci, int lo, int 
     }
     return -1;
 }
-}  // namespace
 
 constexpr int INIT_GRP = 4;  // row entries whose loads k_hem_init issues together
 
@@ -65,109 +64,126 @@ __device__ __forceinline__ int find_col_short(const int* __restrict__ ci, int lo
     return p;
 }
 
-// counters: cnt[0..2] worklist sizes (ring of 3), cnt[5] sum over rows of
-// (#upper - #lower) entries, cnt[6] the number of rounds that had work,
-// cnt[7] set when a single-workgroup pass hit its round limit.
-template <int SIDE>
+// Up to 31 lower edges fit a word.  The lower edges of a vertex with more
+// ("wide") have their bits in words of the extension array; its own word then
+// holds the two summary states only.
+constexpr int kWordEdges = 31;
+// whether vertex j, with row ci[b, e), is wide
+__device__ __forceinline__ bool wide_row(const int* __restrict__ ci, int b, int e, int j) {
+    return e - b > kWordEdges && ci[b + kWordEdges] < j;
+}
+constexpr unsigned kTaken = 0x80000000u;
+constexpr unsigned kAllDead = 0x7fffffffu;
+constexpr int kWideFlag = 1 << 31;  // deg[].x: offset into the extension array
+constexpr int kZeroFlag = 1 << 30;  // deg[].y: the row stores zeros above the diagonal
+// Record entry: distance to the neighbour << 5 | position of the vertex among
+// the neighbour's lower edges.  0 ends the list; kRowEnt says that the rest
+// of the list has to be read from the row (a wide neighbour, or one too far).
+constexpr int kMaxDelta = 1 << 26;
+constexpr int kRowEnt = 31;
+__device__ __forceinline__ unsigned low_bits(int p) { return (1u << p) - 1u; }
+}  // namespace
+
+// Per vertex y of a pass: its record (the first R higher edge-neighbours by
+// |a_yj| descending, column ascending on ties), deg = (number of lower stored
+// entries or extension offset | kWideFlag, number of higher edge-neighbours |
+// kZeroFlag), its word for the other tiles (0) and mate (-1).
+// counters: cnt[1] words of the extension array used, cnt[5] sum over rows of
+// (#upper - #lower) entries; err: an upper entry whose mirror image is not
+// stored.  Together these are zero exactly for a symmetric pattern.
+template <int R>
 __global__ __launch_bounds__(BS) void k_hem_init(int n, const int* __restrict__ rp, const int* __restrict__ ci,
-                                                 const double* __restrict__ v, uint8_t* __restrict__ lowok,
-                                                 HemRecT<SIDE>* __restrict__ rec, int* __restrict__ lcnt,
-                                                 int* __restrict__ dec, int* __restrict__ mate,
-                                                 int* __restrict__ wl0, int* cnt, int* err) {
+                                                 const double* __restrict__ v, int* __restrict__ rec,
+                                                 int2* __restrict__ deg, unsigned* __restrict__ gw,
+                                                 unsigned* __restrict__ xw, int* __restrict__ mate, int* cnt,
+                                                 int* err) {
     const int y = blockIdx.x * BS + threadIdx.x;
     int nlow = 0, nup = 0;
     if (y < n) {
-        dec[y] = kUndecided;
         mate[y] = -1;
-        int c = 0, bad = 0, nh = 0, nl = 0;
-        bool hitr = false, lotr = false;
-        int hj[SIDE], lx[SIDE];
-        double hw[SIDE];
+        gw[y] = 0u;
+        int nh = 0, bad = 0, zero = 0;
+        int ent[R];
+        double wt[R];
 #pragma unroll
-        for (int t = 0; t < SIDE; ++t) {
-            hj[t] = -1;
-            lx[t] = -1;
-            hw[t] = 0.0;
+        for (int t = 0; t < R; ++t) {
+            ent[t] = 0;
+            wt[t] = 0.0;
         }
-        // Entries in groups of INIT_GRP: the loads of a group (columns, the rows
-        // of the lower neighbours, the mirrored entries' values) are issued
-        // together, then the entries are taken in order.
+        // Entries in groups of INIT_GRP: the loads of a group (columns, values,
+        // the rows of the higher neighbours) are issued together, then the
+        // entries are taken in order.
         const int e0 = rp[y], e1 = rp[y + 1];
         for (int k0 = e0; k0 < e1; k0 += INIT_GRP) {
             int us[INIT_GRP], pos[INIT_GRP];
-            double own[INIT_GRP], mir[INIT_GRP];
+            double own[INIT_GRP];
+            bool wide[INIT_GRP];
 #pragma unroll
             for (int t = 0; t < INIT_GRP; ++t) {
                 us[t] = k0 + t < e1 ? ci[k0 + t] : y;
                 own[t] = k0 + t < e1 ? v[k0 + t] : 0.0;
             }
 #pragma unroll
-            for (int t = 0; t < INIT_GRP; ++t) pos[t] = us[t] < y ? find_col_short(ci, rp[us[t]], rp[us[t] + 1], y) : -1;
-#pragma unroll
-            for (int t = 0; t < INIT_GRP; ++t) mir[t] = pos[t] >= 0 ? v[pos[t]] : 0.0;
+            for (int t = 0; t < INIT_GRP; ++t) {
+                pos[t] = -1;
+                wide[t] = false;
+                if (us[t] > y) {
+                    const int b = rp[us[t]], e = rp[us[t] + 1];
+                    const int at = find_col_short(ci, b, e, y);
+                    pos[t] = at < 0 ? -1 : at - b;
+                    wide[t] = wide_row(ci, b, e, us[t]);
+                }
+            }
 #pragma unroll
             for (int q = 0; q < INIT_GRP; ++q) {
-                const int k = k0 + q;
-                if (k >= e1) break;
+                if (k0 + q >= e1) break;
                 const int u = us[q];
-                uint8_t ok = 0;
-                if (u < y) {
-                    ++nlow;
-                    if (pos[q] < 0) bad = 1;
-                    else if (mir[q] != 0.0) ok = 1;
-                    if (ok) {  // lower edge-neighbour, columns arrive ascending
-                        if (nl < SIDE) {
-#pragma unroll
-                            for (int t = 0; t < SIDE; ++t)
-                                if (t == nl) lx[t] = u;
-                            ++nl;
-                        } else {
-                            lotr = true;  // the smallest SIDE are kept
-                        }
-                    }
-                } else if (u > y) {
-                    ++nup;
-                    const double a = own[q];
-                    if (a != 0.0) {  // higher neighbour: the first SIDE by |a| descending, column ascending
-                        const double w = fabs(a);
-                        int at = 0;
-#pragma unroll
-                        for (int t = 0; t < SIDE; ++t)
-                            if (t < nh && hw[t] >= w) at = t + 1;
-                        if (at < SIDE) {
-#pragma unroll
-                            for (int t = SIDE - 1; t > 0; --t)
-                                if (t > at && t <= nh) {  // a full list drops its last entry
-                                    hw[t] = hw[t - 1];
-                                    hj[t] = hj[t - 1];
-                                }
-#pragma unroll
-                            for (int t = 0; t < SIDE; ++t)
-                                if (t == at) {
-                                    hw[t] = w;
-                                    hj[t] = u;
-                                }
-                        }
-                        if (nh < SIDE) ++nh;
-                        else hitr = true;
-                    }
+                nlow += u < y;
+                if (u <= y) continue;
+                ++nup;
+                if (pos[q] < 0) {
+                    bad = 1;
+                    continue;
                 }
-                lowok[k] = ok;
-                c += ok;
+                const double w = fabs(own[q]);
+                if (w == 0.0) {
+                    zero = 1;
+                    continue;
+                }
+                ++nh;
+                const int delta = u - y;
+                const int code = wide[q] || delta >= kMaxDelta ? kRowEnt : (delta << 5) | pos[q];
+                int at = 0;  // by |a| descending; columns arrive ascending
+#pragma unroll
+                for (int t = 0; t < R; ++t)
+                    if (t < nh - 1 && wt[t] >= w) at = t + 1;
+#pragma unroll
+                for (int t = R - 1; t > 0; --t)
+                    if (t > at) {  // a full list drops its last entry
+                        wt[t] = wt[t - 1];
+                        ent[t] = ent[t - 1];
+                    }
+#pragma unroll
+                for (int t = 0; t < R; ++t)
+                    if (t == at) {
+                        wt[t] = w;
+                        ent[t] = code;
+                    }
             }
         }
-        HemRecT<SIDE> R;
-        R.hdr = nh | (nl << 8) | (hitr ? kRecHiTrunc : 0) | (lotr ? kRecLoTrunc : 0) | (hitr || lotr ? kRecOverflow : 0);
+        int4* out = reinterpret_cast<int4*>(rec) + (size_t)y * (R / 4);
 #pragma unroll
-        for (int t = 0; t < SIDE; ++t) {
-            R.h[t] = hj[t];
-            R.l[t] = lx[t];
+        for (int t = 0; t < R; t += 4) out[t / 4] = make_int4(ent[t], ent[t + 1], ent[t + 2], ent[t + 3]);
+        int low = nlow;
+        if (nlow > kWordEdges) {  // extension: the number of lower entries, then their bits
+            const int words = (nlow + 31) / 32;
+            const int at = atomicAdd(&cnt[1], 1 + words);
+            xw[at] = (unsigned)nlow;
+            for (int k = 0; k < words; ++k) xw[at + 1 + k] = nlow - 32 * k >= 32 ? 0u : ~low_bits(nlow - 32 * k);
+            low = at | kWideFlag;
         }
-        R.pad = 0;
-        rec[y] = R;
-        lcnt[y] = c;
+        deg[y] = make_int2(low, nh | (zero ? kZeroFlag : 0));
         if (bad) atomicOr(err, ERR_NONSYM);
-        if (c == 0) wl0[atomicAdd(&cnt[0], 1)] = y;
     }
     // The pattern check, summed over the block and added only when nonzero:
     // adds to one word from every block serialise across the XCDs.  With one
@@ -189,1316 +205,553 @@ __global__ __launch_bounds__(BS) void k_hem_init(int n, const int* __restrict__ 
 }
 
 namespace {
-// Read-only inputs of a pass and the partner output.
 struct HemState {
+    int n;
     const int* __restrict__ rp;
     const int* __restrict__ ci;
     const double* __restrict__ v;
-    const uint8_t* __restrict__ lowok;
-    const void* __restrict__ rec;  // HemRecT<SIDE>[n]
+    const int* __restrict__ rec;
+    const int2* __restrict__ deg;
+    unsigned* gw;  // words set by other tiles
+    unsigned* xw;  // extension words of wide vertices
     int* mate;
 };
 
-// Round stamps and ready counters in global memory (atomics at SCOPE).
-template <int SCOPE>
-struct GlobalSt {
-    int* dec;
-    int* lcnt;
-    __device__ __forceinline__ int get(int i) const { return dec[i]; }
-    __device__ __forceinline__ void set(int i, int r) const { dec[i] = r; }
-    // returns the count before the decrement
-    __device__ __forceinline__ int drop(int y) const {
-        return __hip_atomic_fetch_add(&lcnt[y], -1, __ATOMIC_RELAXED, SCOPE);
-    }
-    // drop(y) when take, else an atomic add of zero on the counter of self (a
-    // decided vertex): the updates of a list are then issued back to back with
-    // one wait, where a branch around each would wait for every one in turn
-    // (returns 0 when not take)
-    __device__ __forceinline__ int drop_if(int y, bool take, int self) const {
-        const int old = __hip_atomic_fetch_add(&lcnt[take ? y : self], take ? -1 : 0, __ATOMIC_RELAXED, SCOPE);
-        return take ? old : 0;
-    }
-};
-
-// The same in LDS: 16-bit stamps (0xffff = undecided) and 16-bit counters
-// packed two to a word.  A counter is only decremented while positive, so
-// the subtraction never borrows from its neighbour.
-// Vertices off .. off+n-1 are held at LDS index (vertex - off).
-struct LdsSt {
-    uint16_t* dec;
-    unsigned* lcnt2;
-    int off;
-    __device__ __forceinline__ int get(int i) const { return dec[i - off]; }
-    __device__ __forceinline__ void set(int i, int r) const { dec[i - off] = (uint16_t)r; }
-    __device__ __forceinline__ int drop(int y) const {
-        y -= off;
-        const unsigned sh = 16u * (unsigned)(y & 1);
-        const unsigned old = atomicSub(&lcnt2[y >> 1], 1u << sh);
-        return (int)((old >> sh) & 0xffffu);
-    }
-    // as GlobalSt::drop_if (self: a vertex of the range)
-    __device__ __forceinline__ int drop_if(int y, bool take, int self) const {
-        const int i = (take ? y : self) - off;
-        const unsigned sh = 16u * (unsigned)(i & 1);
-        const unsigned old = atomicSub(&lcnt2[i >> 1], take ? 1u << sh : 0u);
-        return take ? (int)((old >> sh) & 0xffffu) : 0;
-    }
-};
-
-// Appends to the next worklist through a block-local LDS list of element
-// type E (holding vertex - off); entries that do not fit go to a global list.
-template <class E>
-struct Appender {
-    E* s_list;
-    int* s_cnt;
-    int cap;
-    int* gout;
-    int* gcnt;
-    int off = 0;
-    __device__ __forceinline__ void push(int x) const {
-        const int p = atomicAdd(s_cnt, 1);
-        if (p < cap) s_list[p] = (E)(x - off);
-        else gout[atomicAdd(gcnt, 1)] = x;
-    }
-};
-
-constexpr int HEM_WIN = 8;  // row entries whose loads are issued together
-
-// x has just been decided: its higher neighbours lose one undecided lower
-// neighbour; those that reach zero are ready for the next round.  The
-// counter updates of a window are issued before any result is used.
-template <class St, class Ap>
-__device__ __forceinline__ void hem_release(const HemState& S, const St& st, int x, const Ap& A) {
-    const int e0 = S.rp[x], e1 = S.rp[x + 1];
-    for (int b = e0; b < e1; b += HEM_WIN) {
-        int ys[HEM_WIN], old[HEM_WIN];
-#pragma unroll
-        for (int t = 0; t < HEM_WIN; ++t) {
-            const int e = b + t;
-            ys[t] = -1;
-            if (e < e1) {
-                const int y = S.ci[e];
-                if (y > x && S.v[e] != 0.0) ys[t] = y;
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < HEM_WIN; ++t) old[t] = st.drop_if(ys[t], ys[t] >= 0, x);
-#pragma unroll
-        for (int t = 0; t < HEM_WIN; ++t)
-            if (ys[t] >= 0 && old[t] == 1) A.push(ys[t]);
-    }
+__device__ __forceinline__ unsigned load_dev(const unsigned* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void or_dev(unsigned* p, unsigned bits) {
+    (void)__hip_atomic_fetch_or(p, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Heaviest undecided higher neighbour of u (lowest index on ties), or -1.
-template <class St>
-__device__ __forceinline__ int hem_best(const HemState& S, const St& st, int r, int u, int e0, int e1) {
-    int best = -1;
-    double k = -1.0;
-    for (int b = e0; b < e1; b += HEM_WIN) {
-        int js[HEM_WIN];
-        double ws[HEM_WIN];
-#pragma unroll
-        for (int t = 0; t < HEM_WIN; ++t) {
-            const int e = b + t;
-            js[t] = -1;
-            ws[t] = 0.0;
-            if (e < e1) {
-                const int j = S.ci[e];
-                const double a = S.v[e];
-                if (j > u && a != 0.0) {
-                    js[t] = j;
-                    ws[t] = fabs(a);
-                }
-            }
-        }
-        bool und[HEM_WIN];
-#pragma unroll
-        for (int t = 0; t < HEM_WIN; ++t) und[t] = js[t] >= 0 && st.get(js[t]) >= r;
-#pragma unroll
-        for (int t = 0; t < HEM_WIN; ++t)
-            if (und[t] && ws[t] > k) {  // ascending column order: strict '>' keeps the lowest index
-                k = ws[t];
-                best = js[t];
-            }
-    }
-    return best;
+// All memory operations of the wave have completed.  Ends each rare path that
+// loads from global memory: a load that the compiler takes to be outstanding
+// at the head of the sweep makes every sweep wait for the wave's stores.
+__device__ __forceinline__ void settle() { __builtin_amdgcn_s_waitcnt(0x0f70); }  // vmcnt(0)
+
+// LDS words that other waves of the workgroup read or write meanwhile
+template <class I>
+__device__ __forceinline__ I lds_load(const I* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+template <class I>
+__device__ __forceinline__ void lds_store(I* p, I x) {
+    __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void lds_or(unsigned* p, unsigned bits) {
+    (void)__hip_atomic_fetch_or(p, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Smallest undecided lower neighbour of w (over edges (x, w) stored non-zero
-// in row x), or -1.
-template <class St>
-__device__ __forceinline__ int hem_back(const HemState& S, const St& st, int r, int w) {
-    const int e0 = S.rp[w], e1 = S.rp[w + 1];
-    for (int b = e0; b < e1; b += HEM_WIN) {
-        int xs[HEM_WIN];
-        bool stop = false;
-#pragma unroll
-        for (int t = 0; t < HEM_WIN; ++t) {
-            const int e = b + t;
-            xs[t] = -1;
-            if (e < e1) {
-                const int x = S.ci[e];
-                if (x >= w) stop = true;
-                else if (S.lowok[e]) xs[t] = x;
-            }
-        }
-        bool und[HEM_WIN];
-#pragma unroll
-        for (int t = 0; t < HEM_WIN; ++t) und[t] = xs[t] >= 0 && st.get(xs[t]) >= r;
-#pragma unroll
-        for (int t = 0; t < HEM_WIN; ++t)
-            if (und[t]) return xs[t];  // columns ascend: the first is the smallest
-        if (stop) break;
-    }
-    return -1;
-}
+enum { kUnknown = 0, kAvail = 1, kGone = 2 };
 
-// Counter updates for the higher neighbours listed in a record, all issued
-// before any result is used.
-template <class St, int SIDE, class Ap>
-__device__ __forceinline__ void rec_release(const HemState& S, const St& st, const HemRecT<SIDE>& R, int x,
-                                            const Ap& A) {
-    if (R.hdr & kRecHiTrunc) {
-        hem_release(S, st, x, A);
-        return;
-    }
-    const int nh = R.hdr & 255;
-    int old[SIDE];
-#pragma unroll
-    for (int t = 0; t < SIDE; ++t) old[t] = st.drop_if(R.h[t], t < nh, x);
-#pragma unroll
-    for (int t = 0; t < SIDE; ++t)
-        if (t < nh && old[t] == 1) A.push(R.h[t]);
-}
-
-// Round r for a ready vertex u.  Records list u's higher neighbours in
-// preference order (heaviest first, lowest index on ties) and the target's
-// lower edge-neighbours in ascending order, so "first undecided entry" is the
-// pointer of either side; a truncated list decides only when it holds an
-// undecided entry.  With WAVE_OK, a visit that needs a CSR row (a pointer
-// past a truncated list, or the release of a truncated higher list) is not
-// done here: the function returns true before any change and the caller
-// hands u to a whole wave (hem_visit_wave) later in the round.
-template <class St, int SIDE, bool WAVE_OK, class Ap>
-__device__ __forceinline__ bool hem_visit(const HemState& S, const St& st, int r, int u, const Ap& A) {
-    const HemRecT<SIDE>* __restrict__ recs = static_cast<const HemRecT<SIDE>*>(S.rec);
-    const HemRecT<SIDE> R = recs[u];
-    if (st.get(u) < r) return false;  // decided earlier (as a match target): stale entry
-    int best = -1;
-    {
-        const int nh = R.hdr & 255;
-        int d[SIDE];
-#pragma unroll
-        for (int t = 0; t < SIDE; ++t) d[t] = t < nh ? st.get(R.h[t]) : -1;
-#pragma unroll
-        for (int t = SIDE - 1; t >= 0; --t)
-            if (t < nh && d[t] >= r) best = R.h[t];
-    }
-    if (best < 0 && (R.hdr & kRecHiTrunc)) {  // every listed choice decided: the row decides
-        if (WAVE_OK) return true;
-        best = hem_best(S, st, r, u, S.rp[u], S.rp[u + 1]);
-    }
-    if (best < 0) {  // no undecided neighbour: unaggregated singleton
-        st.set(u, r);
-        S.mate[u] = -1;
-        rec_release(S, st, R, u, A);
-        return false;
-    }
-    const HemRecT<SIDE> B = recs[best];
-    int back = -1;
-    {
-        const int nl = (B.hdr >> 8) & 255;
-        int d[SIDE];
-#pragma unroll
-        for (int t = 0; t < SIDE; ++t) d[t] = t < nl ? st.get(B.l[t]) : -1;
-#pragma unroll
-        for (int t = SIDE - 1; t >= 0; --t)
-            if (t < nl && d[t] >= r) back = B.l[t];
-    }
-    if (back < 0 && (B.hdr & kRecLoTrunc)) {
-        if (WAVE_OK) return true;
-        back = hem_back(S, st, r, best);
-    }
-    if (back == u) {  // best points back: mutual, matched
-        if (WAVE_OK && ((R.hdr | B.hdr) & kRecHiTrunc)) return true;  // releases scan rows
-        st.set(u, r);
-        st.set(best, r);
-        S.mate[u] = best;
-        S.mate[best] = u;
-        rec_release(S, st, R, u, A);
-        rec_release(S, st, B, best, A);
-    } else {
-        A.push(u);  // still ready, retry next round
-    }
-    return false;
-}
-
-// Wave reductions of the cooperative visit.
-__device__ __forceinline__ void wave_best(double& w, int& j) {  // |a| descending, column ascending
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        const double ow = __shfl_xor(w, off);
-        const int oj = __shfl_xor(j, off);
-        if (ow > w || (ow == w && oj < j)) {
-            w = ow;
-            j = oj;
-        }
-    }
-}
-__device__ __forceinline__ int wave_min(int x) {
-    for (int off = kWave / 2; off > 0; off >>= 1) x = min(x, __shfl_xor(x, off));
-    return x;
-}
-// first lane (in list order) whose entry is undecided, or -1
-__device__ __forceinline__ int wave_first(bool und, int val) {
-    const unsigned long long m = __ballot(und);
-    return m ? __shfl(val, __ffsll((long long)m) - 1) : -1;
-}
-
-// Release of x by a whole wave: its record's higher-neighbour list, or its
-// CSR row when the record overflowed, spread over the lanes.
-template <class St, class Ap>
-__device__ __forceinline__ void wave_release(const HemState& S, const St& st, int x, int hdr, int myh,
-                                             const Ap& A) {
-    const int lane = threadIdx.x % kWave;
-    if (hdr & kRecHiTrunc) {
-        for (int e = S.rp[x] + lane; e < S.rp[x + 1]; e += kWave) {
-            const int y = S.ci[e];
-            if (y > x && S.v[e] != 0.0 && st.drop(y) == 1) A.push(y);
-        }
-    } else if (lane < (hdr & 255)) {
-        if (st.drop(myh) == 1) A.push(myh);
-    }
-}
-
-// The visit of hem_visit with all 64 lanes of a wave on one vertex u (u is
-// wave-uniform): row scans take one load step per 64 entries and the
-// choices are wave reductions, so long rows cost a few dependent loads.
-template <class St, int SIDE, class Ap>
-__device__ __forceinline__ void hem_visit_wave(const HemState& S, const St& st, int r, int u, const Ap& A) {
-    const int lane = threadIdx.x % kWave;
-    const int* __restrict__ ru = reinterpret_cast<const int*>(static_cast<const HemRecT<SIDE>*>(S.rec) + u);
-    const int hdr = ru[0];
-    const int myh = lane < SIDE ? ru[1 + lane] : -1;
-    if (st.get(u) < r) return;
-    int best;
-    if (hdr & kRecHiTrunc) {
-        double bw = -1.0;
-        int bj = INT_MAX;
-        for (int e = S.rp[u] + lane; e < S.rp[u + 1]; e += kWave) {
-            const int j = S.ci[e];
-            const double a = S.v[e];
-            if (j > u && a != 0.0 && st.get(j) >= r) {
-                const double w = fabs(a);
-                if (w > bw || (w == bw && j < bj)) {
-                    bw = w;
-                    bj = j;
-                }
-            }
-        }
-        wave_best(bw, bj);
-        best = bw < 0.0 ? -1 : bj;
-    } else {
-        best = wave_first(lane < (hdr & 255) && st.get(myh) >= r, myh);
-    }
-    if (best < 0) {
-        if (lane == 0) {
-            st.set(u, r);
-            S.mate[u] = -1;
-        }
-        wave_release(S, st, u, hdr, myh, A);
-        return;
-    }
-    const int* __restrict__ rb = reinterpret_cast<const int*>(static_cast<const HemRecT<SIDE>*>(S.rec) + best);
-    const int bhdr = rb[0];
-    const int bh = lane < SIDE ? rb[1 + lane] : -1;
-    int back;
-    if (bhdr & kRecLoTrunc) {
-        int mx = INT_MAX;
-        for (int e = S.rp[best] + lane; e < S.rp[best + 1]; e += kWave) {
-            const int x = S.ci[e];
-            if (x < best && S.lowok[e] && st.get(x) >= r) mx = min(mx, x);
-        }
-        mx = wave_min(mx);
-        back = mx == INT_MAX ? -1 : mx;
-    } else {
-        const int bl = lane < SIDE ? rb[1 + SIDE + lane] : -1;
-        back = wave_first(lane < ((bhdr >> 8) & 255) && st.get(bl) >= r, bl);
-    }
-    if (back == u) {
-        if (lane == 0) {
-            st.set(u, r);
-            st.set(best, r);
-            S.mate[u] = best;
-            S.mate[best] = u;
-        }
-        wave_release(S, st, u, hdr, myh, A);
-        wave_release(S, st, best, bhdr, bh, A);
-    } else if (lane == 0) {
-        A.push(u);
-    }
-}
-
-// One round over a list of ready vertices (items idx < m, fetched by `item`):
-// single-lane visits first, then the deferred long rows one wave each.
-template <class St, int SIDE, int NT, class Ap, class Item>
-__device__ __forceinline__ void hem_round_body(const HemState& S, const St& st, int r, int m, int first, int stride,
-                                               const Item& item, const Ap& A, int* s_wave, int* s_nw, int wcap) {
-    for (int idx = first; idx < m; idx += stride) {
-        const int u = item(idx);
-        if (hem_visit<St, SIDE, true>(S, st, r, u, A)) {
-            const int p = atomicAdd(s_nw, 1);
-            if (p < wcap) s_wave[p] = u;
-            else hem_visit<St, SIDE, false>(S, st, r, u, A);
-        }
-    }
-    __syncthreads();
-    const int nw = min(*s_nw, wcap);
-    for (int k = threadIdx.x / kWave; k < nw; k += NT / kWave) hem_visit_wave<St, SIDE>(S, st, r, s_wave[k], A);
-    __syncthreads();
-}
-
-constexpr int HEM_BS = 512;
-constexpr int HEM_LCAP = 4096;
-// Threads of the workgroup-wide drivers with LDS state (one workgroup, systems
-// of a batch, tiles): records of 31 entries a side need the registers of 512.
-template <int SIDE>
-constexpr int hem_nt() {
-    return SIDE > 15 ? 512 : 1024;
-}
-constexpr int HEM_LCAP1 = 8192;
-constexpr int HEM_WCAP = 1024;  // vertices deferred to the wave path per block and round
-constexpr int HL_LCAP = 4096;   // LDS worklist entries of the LDS-state driver
-constexpr int HL_WCAP = 512;
-}  // namespace
-
-// One round over the worklist; the decided vertices' neighbours that become
-// ready, and the ready vertices that failed, form the next list.
-template <int SIDE>
-__global__ __launch_bounds__(HEM_BS) void k_hem_round(int r, int n, HemState S, int* dec, int* lcnt,
-                                                  const int* __restrict__ win, int* __restrict__ wout, int* cnt,
-                                                  int slot_in, int slot_out, int zero_w) {
-    __shared__ int s_list[HEM_LCAP];
-    __shared__ int s_wave[HEM_WCAP];
-    __shared__ int s_cnt, s_base, s_nw;
-    if (threadIdx.x == 0) {
-        s_cnt = 0;
-        s_nw = 0;
-        if (blockIdx.x == 0) cnt[zero_w] = 0;
-    }
-    __syncthreads();
-    // the list size and this thread's first entry are loaded together
-    // (entries past the size are ignored)
-    const int first = blockIdx.x * HEM_BS + threadIdx.x;
-    const int m = cnt[slot_in];
-    const int u0 = first < n ? win[first] : -1;
-    if (m > 0 && blockIdx.x == 0 && threadIdx.x == 0) cnt[6] = r + 1;  // rounds with work
-    const Appender<int> A{s_list, &s_cnt, HEM_LCAP, wout, &cnt[slot_out]};
-    const GlobalSt<__HIP_MEMORY_SCOPE_AGENT> st{dec, lcnt};
-    hem_round_body<GlobalSt<__HIP_MEMORY_SCOPE_AGENT>, SIDE, HEM_BS>(
-        S, st, r, m, first, gridDim.x * HEM_BS, [&](int i) { return i == first ? u0 : win[i]; }, A, s_wave, &s_nw,
-        HEM_WCAP);
-    const int k = min(s_cnt, HEM_LCAP);
-    if (threadIdx.x == 0 && k > 0) s_base = atomicAdd(&cnt[slot_out], k);
-    __syncthreads();
-    for (int i = threadIdx.x; i < k; i += HEM_BS) wout[s_base + i] = s_list[i];
-}
-
-// Mid-size passes: one workgroup runs every round, separated by barriers,
-// with the state in global memory.  Each round decides at least the smallest
-// undecided vertex, so n + 1 rounds always suffice; the bound only guards
-// against invalid input.  Records of 31 entries a side take the registers of
-// 512 threads, as in the LDS-state drivers; with 1024 they would spill.
-template <int SIDE>
-__global__ __launch_bounds__(hem_nt<SIDE>()) void k_hem_all(int n, HemState S, int* dec, int* lcnt, int* wl0, int* wl1,
-                                                     int* cnt) {
-    __shared__ int s_list[HEM_LCAP1];
-    __shared__ int s_wave[HEM_WCAP];
-    __shared__ int s_cnt, s_next, s_m, s_nw;
-    constexpr int NT = hem_nt<SIDE>();
-    if (threadIdx.x == 0) s_m = cnt[0];
-    __syncthreads();
-    const GlobalSt<__HIP_MEMORY_SCOPE_WORKGROUP> st{dec, lcnt};
-    int* win = wl0;
-    int* wout = wl1;
-    int r = 0;
-    for (; r <= n + 1; ++r) {
-        const int m = s_m;
-        if (m == 0) break;
-        if (threadIdx.x == 0) {
-            s_cnt = 0;
-            s_next = 0;
-            s_nw = 0;
-        }
-        __syncthreads();
-        const Appender<int> A{s_list, &s_cnt, HEM_LCAP1, wout, &s_next};
-        hem_round_body<GlobalSt<__HIP_MEMORY_SCOPE_WORKGROUP>, SIDE, NT>(
-            S, st, r, m, threadIdx.x, NT, [&](int i) { return win[i]; }, A, s_wave, &s_nw, HEM_WCAP);
-        const int k = min(s_cnt, HEM_LCAP1);
-        const int base = s_next;
-        for (int i = threadIdx.x; i < k; i += NT) wout[base + i] = s_list[i];
-        __syncthreads();
-        if (threadIdx.x == 0) s_m = base + k;
-        int* t = win;
-        win = wout;
-        wout = t;
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        cnt[6] = r;
-        if (s_m != 0) cnt[7] = 1;
-    }
-}
-
-// Small passes (n <= kHemLdsRows): one workgroup with the round stamps, the
-// ready counters and the worklists in LDS, for the vertices off .. off+n-1
-// (no edge leaves the range).  A list is its LDS part followed by a global
-// part for entries beyond the LDS capacity.  The first list is the kg0
-// entries of gin, or with scan the vertices whose counter is zero.  Returns
-// the rounds run; *left is nonzero when the round bound was hit.
-template <int SIDE>
-__device__ __forceinline__ int hem_lds_body(int off, int n, const HemState& S, const int* __restrict__ lcnt_g, int* gin,
-                            int* gout, int kg0, bool scan, int* left) {
-    __shared__ uint16_t s_dec[kHemLdsRows];
-    __shared__ unsigned s_lcnt2[kHemLdsRows / 2];
-    __shared__ uint16_t s_la[HL_LCAP], s_lb[HL_LCAP];
-    __shared__ int s_wave[HL_WCAP];
-    __shared__ int s_cnt, s_gnext, s_nw;
-    for (int i = threadIdx.x; i < n; i += hem_nt<SIDE>()) s_dec[i] = 0xffff;
-    for (int i = threadIdx.x; 2 * i < n; i += hem_nt<SIDE>()) {
-        const unsigned lo = (unsigned)lcnt_g[off + 2 * i];
-        const unsigned hi = 2 * i + 1 < n ? (unsigned)lcnt_g[off + 2 * i + 1] : 0u;
-        s_lcnt2[i] = lo | (hi << 16);
-    }
-    if (threadIdx.x == 0) {
-        s_cnt = 0;
-        s_gnext = 0;
-    }
-    __syncthreads();
-    const LdsSt st{s_dec, s_lcnt2, off};
-    uint16_t* cur = s_la;
-    uint16_t* nxt = s_lb;
-    int kl = 0, kg = kg0;
-    if (scan) {  // the first list: vertices with no lower edge-neighbour
-        const Appender<uint16_t> A{cur, &s_cnt, HL_LCAP, gin, &s_gnext, off};
-        for (int i = threadIdx.x; i < n; i += hem_nt<SIDE>())
-            if (lcnt_g[off + i] == 0) A.push(off + i);
-        __syncthreads();
-        kl = min(s_cnt, HL_LCAP);
-        kg = s_gnext;
-        __syncthreads();
-    }
-    int r = 0;
-    for (; r <= n + 1; ++r) {
-        const int m = kl + kg;
-        if (m == 0) break;
-        if (threadIdx.x == 0) {
-            s_cnt = 0;
-            s_gnext = 0;
-            s_nw = 0;
-        }
-        __syncthreads();
-        const Appender<uint16_t> A{nxt, &s_cnt, HL_LCAP, gout, &s_gnext, off};
-        const uint16_t* c = cur;
-        const int* g = gin;
-        const int klc = kl;
-        hem_round_body<LdsSt, SIDE, hem_nt<SIDE>()>(
-            S, st, r, m, threadIdx.x, hem_nt<SIDE>(), [&](int i) { return i < klc ? (int)c[i] + off : g[i - klc]; }, A,
-            s_wave, &s_nw, HL_WCAP);
-        kl = min(s_cnt, HL_LCAP);
-        kg = s_gnext;
-        __syncthreads();  // every thread has read the counts before the next reset
-        uint16_t* t = cur;
-        cur = nxt;
-        nxt = t;
-        int* tg = gin;
-        gin = gout;
-        gout = tg;
-    }
-    *left = kl + kg;
-    return r;
-}
-
-template <int SIDE>
-__global__ __launch_bounds__(hem_nt<SIDE>()) void k_hem_lds(int n, HemState S, const int* __restrict__ lcnt_g, int* wl0,
-                                                     int* wl1, int* cnt) {
-    int left = 0;
-    const int r = hem_lds_body<SIDE>(0, n, S, lcnt_g, wl0, wl1, cnt[0], false, &left);
-    if (threadIdx.x == 0) {
-        cnt[6] = r;
-        if (left != 0) cnt[7] = 1;
-    }
-}
-
-// Systems stored one after another (a block-diagonal operator): block b
-// matches system seg[b] = (first vertex, rows) with the LDS-state rounds when
-// it has at most lim (<= kHemLdsRows) rows (larger ones are left to the other
-// drivers), then marks its vertices as decided before round 0 in the global
-// stamps so that those drivers skip them.  Global list space: the system's
-// own rows of sl0 and sl1.
-template <int SIDE>
-__global__ __launch_bounds__(hem_nt<SIDE>()) void k_hem_lds_seg(const int2* __restrict__ seg, HemState S,
-                                                         const int* __restrict__ lcnt_g, int* __restrict__ dec_g,
-                                                         int* sl0, int* sl1, int* cnt, int lim) {
-    const int2 sg = seg[blockIdx.x];
-    const int off = sg.x, n = sg.y;
-    if (n <= 0 || n > lim) return;  // uniform
-    int left = 0;
-    const int r = hem_lds_body<SIDE>(off, n, S, lcnt_g, sl0 + off, sl1 + off, 0, true, &left);
-    __syncthreads();
-    for (int i = threadIdx.x; i < n; i += hem_nt<SIDE>()) dec_g[off + i] = -1;
-    if (threadIdx.x == 0) {
-        atomicMax(&cnt[6], r);
-        if (left != 0) atomicOr(&cnt[7], 1);
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Tiled passes: the vertices are cut into tiles of T consecutive indices, one
-// workgroup per tile, all in one launch.  A workgroup keeps its tile's round
-// stamps, ready counters and worklists in LDS and runs rounds of its own, as
-// the LDS-state driver does, while the other tiles run theirs.  A decision on
-// a vertex u reads only u's neighbours and the states of its target's lower
-// edge-neighbours below u, so a tile waits only on lower tiles, and the
-// matching is the same greedy matching whatever the timing.
-//
-// dec_g[v] publishes each decision to the other tiles in one word: partner
-// + 2, or 1 for a singleton (kUndecided before).  A vertex can only be taken
-// by one of its lower edge-neighbours, so a reader learns whether y is taken
-// from y's lower edge-neighbours' words alone; no read has to be ordered
-// after another, and a stale word only makes a vertex wait for a later round.
-//  * Vertices with lower edge-neighbours in lower tiles ("exposed") start
-//    "pending": they count as undecided, but their own tile may neither match
-//    them nor let them choose until those neighbours are all decided.  Then
-//    the words tell whether one of them took the vertex, and one
-//    compare-and-swap on its LDS stamp settles it (free, or taken: stamped
-//    decided, counted and released by the thread that settles it).
-//  * A vertex u whose target lies in a higher tile takes it once the target's
-//    lower edge-neighbours below u read decided and none of them names it.
-//    The thread waits for its own stores before the round ends, so later
-//    rounds of the tile read the target's word as taken.
-// A workgroup that runs past its time limit sets cnt[7] and stops; the host
-// then repeats the pass with the round kernels.
-// ---------------------------------------------------------------------------
-namespace {
-constexpr int kTileUnd = 0xffff;       // LDS stamp: undecided
-constexpr int kTilePend = 0xfffe;      // LDS stamp: exposed, not settled yet
-constexpr int kTileMaxRound = 0xfff0;  // rounds stop below the two stamps above
-constexpr int kExposed = 1 << 20;      // lcnt flag set by k_hem_tile_prep
-constexpr int TL_LCAP = 4096;          // LDS worklist entries per list
-
-struct TileSt {
-    uint16_t* sdec;   // LDS stamps of the tile
-    unsigned* lcnt2;  // LDS ready counters, two 16-bit counters a word
-    int off, m;       // the tile: vertices off .. off+m-1
-    int* dec_g;
-    __device__ __forceinline__ bool mine(int i) const { return (unsigned)(i - off) < (unsigned)m; }
-    __device__ __forceinline__ int word(int i) const {
-        return __hip_atomic_load(&dec_g[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    // round-stamp view: undecided in round r while >= r
-    __device__ __forceinline__ int get(int i) const {
-        return mine(i) ? sdec[i - off] : (word(i) != kUndecided ? -1 : INT_MAX);
-    }
-    __device__ __forceinline__ int drop(int y) const {  // count before the decrement
-        y -= off;
-        const unsigned sh = 16u * (unsigned)(y & 1);
-        const unsigned old = atomicSub(&lcnt2[y >> 1], 1u << sh);
-        return (int)((old >> sh) & 0xffffu);
-    }
-    // as GlobalSt::drop_if; take implies mine(y), and a self outside the
-    // tile gives the tile's first counter
-    __device__ __forceinline__ int drop_if(int y, bool take, int self) const {
-        const int i = take ? y - off : (mine(self) ? self - off : 0);
-        const unsigned sh = 16u * (unsigned)(i & 1);
-        const unsigned old = atomicSub(&lcnt2[i >> 1], take ? 1u << sh : 0u);
-        return take ? (int)((old >> sh) & 0xffffu) : 0;
-    }
-    __device__ __forceinline__ void publish(int v, int partner) const {
-        __hip_atomic_store(&dec_g[v], partner + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-};
-
-// x is decided: its higher neighbours in the tile lose an undecided lower
-// neighbour (higher tiles read dec_g instead).
-template <int SIDE, class Ap>
-__device__ __forceinline__ void tile_release(const HemState& S, const TileSt& st, const HemRecT<SIDE>& R, int x,
-                                             const Ap& A) {
-    if (R.hdr & kRecHiTrunc) {
-        for (int e = S.rp[x]; e < S.rp[x + 1]; ++e) {
-            const int y = S.ci[e];
-            if (y > x && st.mine(y) && S.v[e] != 0.0 && st.drop(y) == 1) A.push(y);
-        }
-        return;
-    }
-    const int nh = R.hdr & 255;
-    int old[SIDE];
-#pragma unroll
-    for (int t = 0; t < SIDE; ++t) {
-        const int y = t < nh ? R.h[t] : x;
-        old[t] = st.drop_if(y, t < nh && st.mine(y), x);
-    }
-#pragma unroll
-    for (int t = 0; t < SIDE; ++t)
-        if (t < nh && old[t] == 1) A.push(R.h[t]);
-}
-
-enum { kUnsettled = 0, kFree = 1, kGone = 2 };
-
-// Compare-and-swap of the 16-bit LDS stamp i; returns the stamp before.
-__device__ __forceinline__ int cas_stamp(uint16_t* sdec, int i, int expect, int want) {
-    unsigned* w = reinterpret_cast<unsigned*>(sdec) + (i >> 1);
-    const unsigned sh = 16u * (unsigned)(i & 1);
-    unsigned old = *w;
-    for (;;) {
-        const int h = (int)((old >> sh) & 0xffffu);
-        if (h != expect) return h;
-        const unsigned nw = (old & ~(0xffffu << sh)) | ((unsigned)want << sh);
-        const unsigned got = atomicCAS(w, old, nw);
-        if (got == old) return expect;
-        old = got;  // the other half changed meanwhile, or this one
-    }
-}
-
-// Settles the pending vertex y (record Ry) once its lower-tile edge-neighbours
-// are decided (all: open == false; taken: one of them names y).  Returns
-// kFree or kGone (taken, or matched in this round after another thread
-// settled it free).  A vertex found taken is stamped r - 1 (unavailable at
-// once), counted and released by the thread whose swap succeeds.
-template <int SIDE, class Ap>
-__device__ __forceinline__ int tile_settle(const HemState& S, const TileSt& st, const HemRecT<SIDE>& Ry, int y, int r,
-                                           bool taken, const Ap& A, int* s_ndec) {
-    const int old = cas_stamp(st.sdec, y - st.off, kTilePend, taken ? r - 1 : kTileUnd);
-    if (old == kTilePend) {
-        if (!taken) return kFree;
-        atomicAdd(s_ndec, 1);
-        tile_release<SIDE>(S, st, Ry, y, A);
-        return kGone;
-    }
-    return old == kTileUnd ? kFree : kGone;
-}
-
-// Lower-tile edge-neighbours of y: open when one is undecided, taken when
-// one names y as its partner.
-template <int SIDE>
-__device__ __forceinline__ void cross_lower(const HemState& S, const TileSt& st, const HemRecT<SIDE>& Ry, int y,
-                                            bool& open, bool& taken) {
-    open = false;
-    taken = false;
-    const int nl = (Ry.hdr >> 8) & 255;
-    if ((Ry.hdr & kRecLoTrunc) && Ry.l[SIDE - 1] < st.off) {  // a full list; more lower-tile ones may follow
-        for (int e = S.rp[y]; e < S.rp[y + 1]; ++e) {
-            const int x = S.ci[e];
-            if (x >= st.off) break;  // columns ascend
-            if (!S.lowok[e]) continue;
-            const int wx = st.word(x);
-            open |= wx == kUndecided;
-            taken |= wx == y + 2;
-        }
-        return;
-    }
-    int wx[SIDE];
-#pragma unroll
-    for (int t = 0; t < SIDE; ++t) wx[t] = t < nl && Ry.l[t] < st.off ? st.word(Ry.l[t]) : 0;
-#pragma unroll
-    for (int t = 0; t < SIDE; ++t) {
-        open |= wx[t] == kUndecided;
-        taken |= wx[t] == y + 2;
-    }
-}
-
-// Smallest undecided lower edge-neighbour of w (stamp view of round r), or -1;
-// named: an out-of-tile lower edge-neighbour below the result names w.  The
-// listed neighbours decide unless all are decided and the list is truncated;
-// then the CSR row does.
-template <int SIDE>
-__device__ __forceinline__ int tile_back(const HemState& S, const TileSt& st, const HemRecT<SIDE>& B, int w, int r,
-                                         bool& named) {
-    named = false;
-    const int nl = (B.hdr >> 8) & 255;
-    int d[SIDE];
-    bool nm[SIDE];
-#pragma unroll
-    for (int t = 0; t < SIDE; ++t) {
-        nm[t] = false;
-        d[t] = -1;
-        if (t < nl) {
-            const int x = B.l[t];
-            if (st.mine(x)) {
-                d[t] = st.sdec[x - st.off];
-            } else {
-                const int wx = st.word(x);
-                d[t] = wx == kUndecided ? INT_MAX : -1;
-                nm[t] = wx == w + 2;
-            }
-        }
-    }
-    int back = -1;
-#pragma unroll
-    for (int t = SIDE - 1; t >= 0; --t)
-        if (t < nl && d[t] >= r) back = B.l[t];
-    if (back >= 0 || !(B.hdr & kRecLoTrunc)) {
-#pragma unroll
-        for (int t = 0; t < SIDE; ++t)
-            if (t < nl && nm[t] && (back < 0 || B.l[t] < back)) named = true;
-        return back;
-    }
-    for (int e = S.rp[w]; e < S.rp[w + 1]; ++e) {  // every listed one decided
-        const int x = S.ci[e];
-        if (x >= w) break;
-        if (!S.lowok[e]) continue;
-        if (st.mine(x)) {
-            if (st.sdec[x - st.off] >= r) return x;
-        } else {
-            const int wx = st.word(x);
-            if (wx == kUndecided) return x;
-            named |= wx == w + 2;
-        }
-    }
-    return -1;
-}
-
-// Round r for a ready vertex u of the tile (the visit of hem_visit, with the
-// cross-tile rules above).
-template <int SIDE, class Ap>
-__device__ __forceinline__ void tile_visit(const HemState& S, const TileSt& st, int r, int u, const Ap& A,
-                                           int* s_ndec) {
-    const HemRecT<SIDE>* __restrict__ recs = static_cast<const HemRecT<SIDE>*>(S.rec);
-    const HemRecT<SIDE> R = recs[u];
-    const int su = st.sdec[u - st.off];
-    if (su < r) return;  // decided earlier (as a match target): stale entry
-    if (su == kTilePend) {  // most visits of a pending vertex find it still open
-        bool open, taken;
-        cross_lower<SIDE>(S, st, R, u, open, taken);
-        if (open) {
-            A.push(u);
-            return;
-        }
-        if (tile_settle<SIDE>(S, st, R, u, r, taken, A, s_ndec) != kFree) return;
-    }
-    // the first preference's record, loaded with the states it is chosen by
-    const bool spec = (R.hdr & 255) > 0;
-    HemRecT<SIDE> B;
-    if (spec) B = recs[R.h[0]];
-    int best = -1;
-    {
-        const int nh = R.hdr & 255;
-        int d[SIDE];
-#pragma unroll
-        for (int t = 0; t < SIDE; ++t) d[t] = t < nh ? st.get(R.h[t]) : -1;
-#pragma unroll
-        for (int t = SIDE - 1; t >= 0; --t)
-            if (t < nh && d[t] >= r) best = R.h[t];
-    }
-    if (best < 0 && (R.hdr & kRecHiTrunc))  // every listed choice decided: the row decides
-        best = hem_best(S, st, r, u, S.rp[u], S.rp[u + 1]);
-    if (best < 0) {  // no undecided neighbour: unaggregated singleton
-        st.sdec[u - st.off] = (uint16_t)r;
-        S.mate[u] = -1;
-        st.publish(u, -1);
-        atomicAdd(s_ndec, 1);
-        tile_release<SIDE>(S, st, R, u, A);
-        return;
-    }
-    if (!spec || best != R.h[0]) B = recs[best];
-    bool named;
-    const int back = tile_back<SIDE>(S, st, B, best, r, named);
-    if (back != u) {
-        A.push(u);  // still ready, retry next round
-        return;
-    }
-    if (st.mine(best)) {
-        // a pending target: its lower-tile edge-neighbours are all below u,
-        // hence decided; named says whether one of them took it
-        if (st.sdec[best - st.off] == kTilePend && tile_settle<SIDE>(S, st, B, best, r, named, A, s_ndec) != kFree) {
-            A.push(u);
-            return;
-        }
-        st.sdec[u - st.off] = (uint16_t)r;
-        st.sdec[best - st.off] = (uint16_t)r;
-        S.mate[u] = best;
-        S.mate[best] = u;
-        st.publish(best, u);
-        st.publish(u, best);
-        atomicAdd(s_ndec, 2);
-        tile_release<SIDE>(S, st, R, u, A);
-        tile_release<SIDE>(S, st, B, best, A);
-        return;
-    }
-    if (named) {  // taken from a lower tile
-        A.push(u);
-        return;
-    }
-    st.sdec[u - st.off] = (uint16_t)r;
-    S.mate[u] = best;
-    S.mate[best] = u;
-    st.publish(best, u);
-    st.publish(u, best);
-    __builtin_amdgcn_s_waitcnt(0);  // stores complete before the round ends
-    atomicAdd(s_ndec, 1);
-    tile_release<SIDE>(S, st, R, u, A);
-}
-
-// ---------------------------------------------------------------------------
-// Small tiles with their adjacency records in LDS.  A tile of up to
-// kTileCRows rows keeps, besides its stamps and counters, a compact copy of
-// each of its vertices' records: up to kCSide higher and kCSide lower
-// neighbours as 16-bit offsets from the vertex.  A vertex whose record does
-// not fit (longer lists, truncated lists, offsets beyond 16 bits) is marked
-// and read from the global record instead.  A visit then reads global memory
-// only for what lies outside the tile: the published words of out-of-tile
-// neighbours, and only those the decision needs.
-//  * The choice of u scans its preference list; an out-of-tile entry's word
-//    is read only when it precedes the first undecided in-tile entry.
-//  * The target's lower edge-neighbours in lower tiles are read only while
-//    the target is pending: a target of this tile that is no longer pending
-//    was settled free, so those neighbours are decided and none took it.
-// The rules between tiles are those of the tiled pass above.
-// ---------------------------------------------------------------------------
-constexpr int kTileCRows = kHemTileCRows;  // largest tile of the compact-record driver
-constexpr int kCSide = 4;         // entries a side of a compact record
-constexpr int kCGlobal = 0x80;    // compact header flag: use the global record
-constexpr int kCompactMaxTiles = 512;  // largest pass (in tiles) that takes compact tiles
-
-struct CRecs {
-    const uint8_t* hdr;  // per tile vertex: #higher | #lower << 3 | kCGlobal
-    const int16_t* h;    // h[t * kTileCRows + i]: offset of the t-th higher neighbour of vertex off+i
-    const int16_t* l;    // lower edge-neighbours, the same layout
-    const HemRecT<7>* g;
+// The tile of a workgroup: vertices off .. off + m - 1, their words in LDS.
+// The bits of lower edges from other tiles arrive in gw (set there by those
+// tiles) and are merged into the LDS word by the vertex's own thread; a
+// lower tile reads a vertex's state from gw alone, since all lower edges below
+// its own come from its own tile or lower ones.
+struct Tile {
     int off, m;
-    // record of v: from LDS when v is a tile vertex with a compact record
-    __device__ __forceinline__ void load(int v, HemRecT<7>& R) const {
-        const int i = v - off;
-        const int hd = (unsigned)i < (unsigned)m ? hdr[i] : kCGlobal;
-        if (hd & kCGlobal) {
-            R = g[v];
+    unsigned* w;
+    __device__ __forceinline__ bool mine(int i) const { return (unsigned)(i - off) < (unsigned)m; }
+    __device__ __forceinline__ unsigned load(int i) const {
+        return lds_load(&w[i]);
+    }
+    __device__ __forceinline__ void set(int i, unsigned bits) const {
+        lds_or(&w[i], bits);
+    }
+    __device__ __forceinline__ unsigned word(const HemState& S, int j) const {
+        return mine(j) ? load(j - off) : load_dev(&S.gw[j]);
+    }
+    __device__ __forceinline__ void set_word(const HemState& S, int j, unsigned bits) const {
+        if (mine(j)) set(j - off, bits);
+        else or_dev(&S.gw[j], bits);
+    }
+    // lower edge `pos` of j is dead
+    __device__ __forceinline__ void dead(const HemState& S, int j, int pos, bool wide) const {
+        if (!wide) set_word(S, j, 1u << pos);
+        else or_dev(&S.xw[(S.deg[j].x & ~kWideFlag) + 1 + pos / 32], 1u << (pos % 32));
+    }
+    // lower edge `pos` of j is taken
+    __device__ __forceinline__ void taken(const HemState& S, int j, int pos, bool wide) const {
+        if (!wide) {
+            set_word(S, j, ~(1u << pos));
             return;
         }
-        const int nh = hd & 7, nl = (hd >> 3) & 7;
-        R.hdr = nh | (nl << 8);
-#pragma unroll
-        for (int t = 0; t < 7; ++t) {
-            R.h[t] = t < kCSide && t < nh ? v + h[t * kTileCRows + i] : -1;
-            R.l[t] = t < kCSide && t < nl ? v + l[t * kTileCRows + i] : -1;
+        unsigned* x = S.xw + (S.deg[j].x & ~kWideFlag);
+        const int words = ((int)x[0] + 31) / 32;
+        for (int k = 0; k < words; ++k) or_dev(&x[1 + k], k == pos / 32 ? ~(1u << (pos % 32)) : ~0u);
+        set_word(S, j, kTaken);
+    }
+    // j for its lower edge `pos`, from j's word wj
+    __device__ __forceinline__ int state(const HemState& S, int j, int pos, bool wide, unsigned wj) const {
+        bool full;
+        if (!wide) {
+            full = (~wj & low_bits(pos)) == 0u;
+        } else {
+            const unsigned* x = S.xw + (S.deg[j].x & ~kWideFlag) + 1;
+            full = true;
+            for (int k = 0; 32 * k < pos && full; ++k) {
+                const unsigned need = pos - 32 * k >= 32 ? ~0u : low_bits(pos - 32 * k);
+                full = (~load_dev(&x[k]) & need) == 0u;
+            }
+            settle();
         }
-        R.pad = 0;
+        return full ? kAvail : (wj & kTaken) ? kGone : kUnknown;
     }
 };
 
-// Smallest undecided lower edge-neighbour of w (stamp view of round r), or -1,
-// as tile_back; settled: w is a tile vertex that is not pending, so its
-// lower-tile edge-neighbours are decided and none named it (not read).
-__device__ __forceinline__ int tile_back_c(const HemState& S, const TileSt& st, const HemRecT<7>& B, int w, int r,
-                                           bool settled, bool& named) {
-    if (!settled) return tile_back<7>(S, st, B, w, r, named);
-    named = false;
-    const int nl = (B.hdr >> 8) & 255;
-    int back = -1;
-#pragma unroll
-    for (int t = 6; t >= 0; --t) {
-        if (t < nl) {
-            const int x = B.l[t];
-            if (st.mine(x) && st.sdec[x - st.off] >= r) back = x;
+// By a whole wave, on one vertex u: its heaviest higher edge-neighbour not
+// known to be unavailable (lowest column on ties).  Returns the neighbour (-1:
+// none), its position and state.
+__device__ __forceinline__ int wave_choice(const HemState& S, const Tile& T, int u, int& pos, bool& wide, int& st) {
+    const int lane = threadIdx.x % kWave;
+    unsigned long long bw = 0;
+    int bj = INT_MAX, bp = 0, bs = kUnknown;
+    bool bwide = false;
+    for (int e = S.rp[u] + lane; e < S.rp[u + 1]; e += kWave) {
+        const int j = S.ci[e];
+        const double a = fabs(S.v[e]);
+        if (j <= u || a == 0.0) continue;
+        const int b = S.rp[j], e1 = S.rp[j + 1];
+        const int p = find_col(S.ci, b, e1, u) - b;
+        const bool wd = wide_row(S.ci, b, e1, j);
+        const int s = T.state(S, j, p, wd, T.word(S, j));
+        // non-negative doubles order as their bits do; every weight is nonzero
+        const unsigned long long w = (unsigned long long)__double_as_longlong(a);
+        if (s != kGone && (w > bw || (w == bw && j < bj))) {
+            bw = w;
+            bj = j;
+            bp = p;
+            bs = s;
+            bwide = wd;
         }
     }
-    if (back >= 0 || !(B.hdr & kRecLoTrunc)) return back;
-    for (int e = S.rp[w]; e < S.rp[w + 1]; ++e) {  // every listed one decided
-        const int x = S.ci[e];
-        if (x >= w) break;
-        if (x < st.off || !S.lowok[e]) continue;
-        if (st.sdec[x - st.off] >= r) return x;
+    unsigned long long mw = bw;
+    int mj = bj;
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        const unsigned long long ow = __shfl_xor(mw, o);
+        const int oj = __shfl_xor(mj, o);
+        if (ow > mw || (ow == mw && oj < mj)) {
+            mw = ow;
+            mj = oj;
+        }
     }
-    return -1;
+    if (mj == INT_MAX) return -1;
+    const int src = __ffsll((long long)__ballot(bj == mj)) - 1;  // each column is held by one lane
+    pos = __shfl(bp, src);
+    wide = __shfl((int)bwide, src) != 0;
+    st = __shfl(bs, src);
+    return mj;
 }
 
-// Round r for a ready vertex u of a compact tile: the visit of tile_visit
-// with records from LDS and the out-of-tile reads cut to what decides.
-template <class Ap>
-__device__ __forceinline__ void tile_visit_c(const HemState& S, const TileSt& st, const CRecs& C, int r, int u,
-                                             const Ap& A, int* s_ndec) {
-    HemRecT<7> R;
-    C.load(u, R);
-    const int su = st.sdec[u - st.off];
-    if (su < r) return;  // decided earlier (as a match target): stale entry
-    if (su == kTilePend) {  // most visits of a pending vertex find it still open
-        bool open, taken;
-        cross_lower<7>(S, st, R, u, open, taken);
-        if (open) {
-            A.push(u);
-            return;
-        }
-        if (tile_settle<7>(S, st, R, u, r, taken, A, s_ndec) != kFree) return;
+// By a whole wave: every higher edge of u but the one to `keep` is dead.
+__device__ __forceinline__ void wave_dead(const HemState& S, const Tile& T, int u, int keep) {
+    for (int e = S.rp[u] + (int)(threadIdx.x % kWave); e < S.rp[u + 1]; e += kWave) {
+        const int j = S.ci[e];
+        if (j <= u || j == keep || S.v[e] == 0.0) continue;
+        const int b = S.rp[j], e1 = S.rp[j + 1];
+        T.dead(S, j, find_col(S.ci, b, e1, u) - b, wide_row(S.ci, b, e1, j));
     }
-    const int nh = R.hdr & 255;
-    const int b0 = nh > 0 ? R.h[0] : -1;
-    HemRecT<7> B;
-    if (b0 >= 0) C.load(b0, B);  // the first preference, loaded with the states it is chosen by
-    int best = -1;
-    {
-        int fin = 7;  // first undecided tile entry in preference order
-#pragma unroll
-        for (int t = 6; t >= 0; --t)
-            if (t < nh && st.mine(R.h[t]) && st.sdec[R.h[t] - st.off] >= r) fin = t;
-        bool und[7];
-#pragma unroll
-        for (int t = 0; t < 7; ++t) {
-            und[t] = false;
-            if (t < nh && t < fin && !st.mine(R.h[t])) und[t] = st.word(R.h[t]) == kUndecided;
-        }
-#pragma unroll
-        for (int t = 6; t >= 0; --t)
-            if (t < nh && (t == fin || und[t])) best = R.h[t];
-    }
-    if (best < 0 && (R.hdr & kRecHiTrunc))  // every listed choice decided: the row decides
-        best = hem_best(S, st, r, u, S.rp[u], S.rp[u + 1]);
-    if (best < 0) {  // no undecided neighbour: unaggregated singleton
-        st.sdec[u - st.off] = (uint16_t)r;
-        S.mate[u] = -1;
-        st.publish(u, -1);
-        atomicAdd(s_ndec, 1);
-        tile_release<7>(S, st, R, u, A);
-        return;
-    }
-    if (best != b0) C.load(best, B);
-    const bool settled = st.mine(best) && st.sdec[best - st.off] != kTilePend;
-    bool named;
-    const int back = tile_back_c(S, st, B, best, r, settled, named);
-    if (back != u) {
-        A.push(u);  // still ready, retry next round
-        return;
-    }
-    if (st.mine(best)) {
-        if (!settled && tile_settle<7>(S, st, B, best, r, named, A, s_ndec) != kFree) {
-            A.push(u);
-            return;
-        }
-        st.sdec[u - st.off] = (uint16_t)r;
-        st.sdec[best - st.off] = (uint16_t)r;
-        S.mate[u] = best;
-        S.mate[best] = u;
-        st.publish(best, u);
-        st.publish(u, best);
-        atomicAdd(s_ndec, 2);
-        tile_release<7>(S, st, R, u, A);
-        tile_release<7>(S, st, B, best, A);
-        return;
-    }
-    if (named) {  // taken from a lower tile
-        A.push(u);
-        return;
-    }
-    st.sdec[u - st.off] = (uint16_t)r;
-    S.mate[u] = best;
-    S.mate[best] = u;
-    st.publish(best, u);
-    st.publish(u, best);
-    __builtin_amdgcn_s_waitcnt(0);  // stores complete before the round ends
-    atomicAdd(s_ndec, 1);
-    tile_release<7>(S, st, R, u, A);
 }
 
-// Releases of a compact vertex self: its in-tile higher neighbours h[0..nh)
-// lose an undecided lower neighbour; those that reach zero are ready.
-template <class Ap>
-__device__ __forceinline__ void lean_release(const TileSt& st, const int* h, int nh, int self, const Ap& A) {
-    int old[kCSide];
-#pragma unroll
-    for (int t = 0; t < kCSide; ++t) {
-        const int y = t < nh ? h[t] : self;
-        old[t] = st.drop_if(y, t < nh && st.mine(y), self);
-    }
-#pragma unroll
-    for (int t = 0; t < kCSide; ++t)
-        if (t < nh && old[t] == 1) A.push(h[t]);
+// State of a vertex: its current choice's record entry (16 bits) and these flags
+enum : unsigned {
+    vConf = 1u << 16,  // the current choice is available: later edges are dead
+    vRow = 1u << 17,   // past the record: choices come from the row
+    vWide = 1u << 18,  // the vertex itself is wide
+    vMore = 1u << 19,  // the record does not hold the whole list
+    vRare = 1u << 20,  // waits for words that only the wave itself polls
+    vDone = 1u << 21,
+};
+constexpr unsigned kNever = ~0u;
+constexpr int kNoRest = -2;  // no edges of the row are left to mark
+
+// Bits of p over the group of G lanes that this lane is in.
+template <int G>
+__device__ __forceinline__ unsigned group_mask(bool p) {
+    const unsigned long long b = __ballot(p) >> ((threadIdx.x % kWave) & ~(G - 1));
+    return (unsigned)b & (G == 32 ? ~0u : (1u << (G % 32)) - 1u);
 }
 
-// The visit of tile_visit_c for a vertex u with a compact record, written on
-// the compact lists themselves (at most kCSide entries a side, no 7-entry
-// record built); a target without a compact record (outside the tile, or
-// with longer lists) hands the visit to tile_visit_c, before any change.
-template <class Ap>
-__device__ __forceinline__ void tile_visit_lean(const HemState& S, const TileSt& st, const CRecs& C, int r, int u,
-                                                const Ap& A, int* s_ndec) {
-    const int off = st.off;
-    const int i = u - off;
-    const int hd = C.hdr[i];
-    const int su = st.sdec[i];
-    if (hd & kCGlobal) {
-        tile_visit_c(S, st, C, r, u, A, s_ndec);
-        return;
-    }
-    if (su < r) return;  // decided earlier (as a match target): stale entry
-    const int nh = hd & 7, nl = (hd >> 3) & 7;
-    int h[kCSide], l[kCSide];
+// The polling waves of a tile; they end when every other wave has.  The first
+// merges the bits that lower tiles set in this tile's words into LDS.
+template <int TM>
+__device__ __forceinline__ void poll_words(const HemState& S, const Tile& T, const unsigned* s_m, const int* s_left) {
+    constexpr int B = TM / kWave;  // vertices of a lane, their loads in flight together
+    const int lane = threadIdx.x % kWave;
+    unsigned need[B];
 #pragma unroll
-    for (int t = 0; t < kCSide; ++t) {
-        h[t] = u + C.h[t * kTileCRows + i];
-        l[t] = u + C.l[t * kTileCRows + i];
-    }
-    if (su == kTilePend) {  // lower-tile edge-neighbours: all decided, and did one take u?
-        int wx[kCSide];
+    for (int i = 0; i < B; ++i) need[i] = lane + i * kWave < T.m ? s_m[lane + i * kWave] : 0u;
+    __builtin_amdgcn_s_setprio(3);
+    while (lds_load(s_left) > 0) {
+        unsigned g[B], any = 0u;
 #pragma unroll
-        for (int t = 0; t < kCSide; ++t) wx[t] = t < nl && l[t] < off ? st.word(l[t]) : 0;
-        bool open = false, taken = false;
-#pragma unroll
-        for (int t = 0; t < kCSide; ++t) {
-            open |= wx[t] == kUndecided;
-            taken |= wx[t] == u + 2;
+        for (int i = 0; i < B; ++i) {
+            g[i] = need[i] ? load_dev(&S.gw[T.off + lane + i * kWave]) : 0u;
+            any |= need[i];
         }
-        if (open) {
-            A.push(u);
-            return;
+        if (__ballot(any != 0u) == 0) break;
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+            if (g[i] & (need[i] | kTaken)) T.set(lane + i * kWave, g[i]);
+            need[i] = g[i] & kTaken ? 0u : need[i] & ~g[i];
         }
-        const int old = cas_stamp(st.sdec, i, kTilePend, taken ? r - 1 : kTileUnd);
-        if (old == kTilePend) {
-            if (taken) {
-                atomicAdd(s_ndec, 1);
-                lean_release(st, h, nh, u, A);
-                return;
+    }
+}
+
+// The second looks up the choices in higher tiles that are waited for: those
+// of vertices that are free to take them each time, the others, which only
+// let later edges be marked earlier, every eighth time.
+template <int TM>
+__device__ __forceinline__ void poll_choices(const HemState& S, const Tile& T, unsigned* s_x, unsigned* s_y,
+                                             const int* s_r, const int* s_e, const int* s_left) {
+    constexpr int B = TM / kWave < 8 ? TM / kWave : 8;
+    const int lane = threadIdx.x % kWave;
+    __builtin_amdgcn_s_setprio(3);
+    for (int it = 0; lds_load(s_left) > 0; ++it) {
+        bool idle = true;
+        for (int l0 = lane; l0 - lane < T.m; l0 += B * kWave) {
+            unsigned t[B];
+            int r[B], q[B];
+            bool any = false;
+#pragma unroll
+            for (int i = 0; i < B; ++i) {
+                const int l = l0 + i * kWave;
+                r[i] = 0;
+                if (l < T.m) {
+                    r[i] = lds_load(&s_r[l]);
+                    if (r[i] > 0 && ((lds_load(&s_x[l]) >> (r[i] - 1)) & 1u)) r[i] = 0;
+                    if ((it & 7) != 0 && T.load(l) != kAllDead) r[i] = 0;
+                    q[i] = r[i] > 0 ? s_e[(r[i] - 1) * (TM + 1) + l] : 0;
+                }
+                any |= r[i] > 0;
             }
-        } else if (old != kTileUnd) {
-            return;
-        }
-    }
-    // the choice: first undecided entry in preference order; out-of-tile
-    // words only for entries before the first undecided tile entry
-    int fin = kCSide;
-    bool inb[kCSide];
+            if (__ballot(any) == 0) continue;
+            idle = false;
 #pragma unroll
-    for (int t = kCSide - 1; t >= 0; --t) {
-        inb[t] = st.mine(h[t]);
-        if (t < nh && inb[t] && st.sdec[h[t] - off] >= r) fin = t;
-    }
-    int best = -1;
-    {
-        bool und[kCSide];
+            for (int i = 0; i < B; ++i)
+                t[i] = r[i] > 0 ? load_dev(&S.gw[T.off + l0 + i * kWave + (q[i] >> 5)]) : 0u;
 #pragma unroll
-        for (int t = 0; t < kCSide; ++t) und[t] = t < nh && t < fin && !inb[t] && st.word(h[t]) == kUndecided;
-#pragma unroll
-        for (int t = kCSide - 1; t >= 0; --t)
-            if (t < nh && (t == fin || und[t])) best = h[t];
-    }
-    if (best < 0) {  // no undecided neighbour: unaggregated singleton
-        st.sdec[i] = (uint16_t)r;
-        S.mate[u] = -1;
-        st.publish(u, -1);
-        atomicAdd(s_ndec, 1);
-        lean_release(st, h, nh, u, A);
-        return;
-    }
-    const int j = best - off;
-    const int hdb = st.mine(best) ? C.hdr[j] : kCGlobal;
-    if (hdb & kCGlobal) {  // a target outside the tile or without a compact record
-        tile_visit_c(S, st, C, r, u, A, s_ndec);
-        return;
-    }
-    const bool settled = st.sdec[j] != kTilePend;
-    const int nhb = hdb & 7, nlb = (hdb >> 3) & 7;
-    int hb[kCSide], lb[kCSide];
-#pragma unroll
-    for (int t = 0; t < kCSide; ++t) {
-        hb[t] = best + C.h[t * kTileCRows + j];
-        lb[t] = best + C.l[t * kTileCRows + j];
-    }
-    // back: the target's smallest undecided lower edge-neighbour; named: one
-    // of its lower-tile neighbours below back took it (read only while the
-    // target is pending)
-    int back = -1;
-    bool named = false;
-    {
-        int d[kCSide];
-        bool nm[kCSide];
-#pragma unroll
-        for (int t = 0; t < kCSide; ++t) {
-            d[t] = -1;
-            nm[t] = false;
-            if (t < nlb) {
-                const int x = lb[t];
-                if (x >= off) {
-                    d[t] = st.sdec[x - off];
-                } else if (!settled) {
-                    const int wx = st.word(x);
-                    d[t] = wx == kUndecided ? INT_MAX : -1;
-                    nm[t] = wx == best + 2;
+            for (int i = 0; i < B; ++i) {
+                const int l = l0 + i * kWave;
+                if (r[i] > 0) {
+                    const bool full = (~t[i] & low_bits(q[i] & 31)) == 0u;
+                    const unsigned bit = 1u << (r[i] - 1);
+                    if (full) lds_or(&s_y[l], bit);
+                    if (full || (t[i] & kTaken))  // after s_y: LDS operations of a wave stay in order
+                        lds_or(&s_x[l], bit);
                 }
             }
         }
-#pragma unroll
-        for (int t = kCSide - 1; t >= 0; --t)
-            if (t < nlb && d[t] >= r) back = lb[t];
-#pragma unroll
-        for (int t = 0; t < kCSide; ++t)
-            if (t < nlb && nm[t] && (back < 0 || lb[t] < back)) named = true;
+        if (idle) __builtin_amdgcn_s_sleep(4);
     }
-    if (back != u) {
-        A.push(u);  // still ready, retry next round
-        return;
-    }
-    if (!settled) {  // a pending target: settle it (free, or taken from a lower tile)
-        const int old = cas_stamp(st.sdec, j, kTilePend, named ? r - 1 : kTileUnd);
-        if (old == kTilePend) {
-            if (named) {
-                atomicAdd(s_ndec, 1);
-                lean_release(st, hb, nhb, best, A);
-                A.push(u);
-                return;
-            }
-        } else if (old != kTileUnd) {
-            A.push(u);
-            return;
-        }
-    }
-    st.sdec[i] = (uint16_t)r;
-    st.sdec[j] = (uint16_t)r;
-    S.mate[u] = best;
-    S.mate[best] = u;
-    st.publish(best, u);
-    st.publish(u, best);
-    atomicAdd(s_ndec, 2);
-    lean_release(st, h, nh, u, A);
-    lean_release(st, hb, nhb, best, A);
 }
+
 }  // namespace
 
-// Per vertex: the LDS ready counter (lcnt: undecided lower edge-neighbours in
-// its own tile) and kExposed when it has lower edge-neighbours in lower
-// tiles.  After k_hem_init.  A counter beyond 16 bits sets cnt[7] (the pass
-// then runs the round kernels).
-__global__ __launch_bounds__(BS) void k_hem_tile_prep(int n, int T, const int* __restrict__ rp,
-                                                      const int* __restrict__ ci, const uint8_t* __restrict__ lowok,
-                                                      int* __restrict__ lcnt, int* cnt) {
-    const int y = blockIdx.x * BS + threadIdx.x;
-    if (y >= n) return;
-    const int t0 = (y / T) * T;
-    int cross = 0;
-    for (int k = rp[y]; k < rp[y + 1]; ++k) {
-        if (ci[k] >= t0) break;  // columns ascend
-        cross += lowok[k];
+// One workgroup per tile of `rows` vertices, one per thread of all waves but
+// the last two, all tiles in one launch.  Tiles are handed out in ascending
+// order as workgroups start, so every tile below a running one is running or
+// done, and waiting on lower tiles ends.
+//
+// What bounds it: a pass is a chain of dependent decisions (about 300 of them
+// on a 128^3 grid, 700 on smooth coefficients at 160^3), so its time is their
+// number times the latency of one; neither memory nor arithmetic is near its
+// limit.  A step inside a tile takes about 1 us, one to another tile 3 to 4 us
+// (an atomic to memory, a poll, and the step there).  Hence:
+//  * Waves run on their own, without barriers.  Each vertex watches two words
+//    in LDS, its own and its current choice's, each with a mask: it is looked
+//    at once a word has all bits of its mask, or the top bit.  A sweep over
+//    them is two LDS reads and a few compares.
+//  * The vertices found are taken a group of lanes each, a lane per record
+//    entry (two with 32): the states of all choices, and the marking of all
+//    edges, take one step each.  One lane per vertex took 12000 clocks a sweep
+//    (the entries one after another), a whole wave per vertex 1700 a vertex; a
+//    group step takes about 2000 for up to 4 vertices, or 16 with short rows.
+//  * No wave that matches touches global memory but to store.  The last two
+//    poll what other tiles set: bits of this tile's words are merged into LDS,
+//    and for each choice in a higher tile that is waited for, s_x tells, per
+//    record entry, that it is known, and s_y that it is available.  Facts about
+//    an entry stay true, so nothing is taken back when a vertex moves on.
+//
+// Against rounds of ready vertices between barriers (the same matching):
+// the passes of a setup at 160^3 with smooth coefficients took 85 ms and take
+// 20 ms, those at 128^3 (constant coefficients) 6.8 ms and 4.2 ms.
+//
+// Past tmo wall-clock ticks a wave stops and cnt[7] is set; the host repeats
+// the pass with a longer limit (every fact found is found again).
+template <int R, int NT>
+__global__ __launch_bounds__(NT) void k_hem_tile(HemState S, int rows, int* cnt, const int* err, long long tmo) {
+    constexpr int TM = NT - 2 * kWave;  // vertices of a tile at most
+    constexpr int G = R < 16 ? R : 16, E = R / G, NG = kWave / G;
+    constexpr int ES = TM + 1;      // entry t of vertex l at s_e[t * ES + l]: no bank conflicts either way
+    __shared__ unsigned s_w[2 * TM + 1];  // words, one that is never looked at, then known entries
+    __shared__ unsigned s_y[TM];          // available entries, of those known
+    __shared__ unsigned s_m[TM];          // bits of lower edges from other tiles
+    __shared__ int s_r[TM];               // 1 + the entry waited for in a higher tile
+    __shared__ int s_e[R * ES];
+    __shared__ int4 s_sel[TM / kWave * NG];
+    __shared__ int s_tile, s_left, s_max;
+    // a pattern that is not symmetric: some bits would never be set
+    if (cnt[5] != 0 || (*err & ERR_NONSYM)) return;
+    if (threadIdx.x == 0) {
+        s_tile = atomicAdd(&cnt[0], 1);
+        s_left = TM / kWave;
+        s_max = 0;
+        s_w[TM] = 0u;
     }
-    const int c = lcnt[y] - cross;
-    if (c > 0xffff) atomicOr(&cnt[7], 2);
-    lcnt[y] = c | (cross > 0 ? kExposed : 0);
-}
-
-// One workgroup per tile.  gl0/gl1: global list space (the tile's rows of
-// each); tmo: time limit in wall-clock ticks.  COMPACT: tiles of at most
-// kTileCRows rows with their records in LDS (SIDE 7).
-template <int SIDE, bool COMPACT>
-__global__ __launch_bounds__(hem_nt<SIDE>()) void k_hem_tile(int n, int T, HemState S, int* dec_g,
-                                                      const int* __restrict__ lcnt_g, int* gl0, int* gl1, int* cnt,
-                                                      long long tmo) {
-    static_assert(!COMPACT || SIDE == 7, "compact records hold 7-entry records");
-    constexpr int TR = COMPACT ? kTileCRows : kHemTileRows;
-    constexpr int CR = COMPACT ? kTileCRows : 1;
-    __shared__ uint16_t s_dec[TR];
-    __shared__ unsigned s_lcnt2[TR / 2];
-    __shared__ uint16_t s_la[TL_LCAP], s_lb[TL_LCAP];
-    __shared__ uint8_t c_hdr[CR];
-    __shared__ int16_t c_h[kCSide * CR], c_l[kCSide * CR];
-    __shared__ int s_cnt, s_gnext, s_ndec, s_stop;
+    __syncthreads();
+    const int off = s_tile * rows;
+    const int m = min(rows, S.n - off);
+    const Tile T{off, m, s_w};
+    const int lane = threadIdx.x % kWave, base = threadIdx.x - lane;
+    const int l = threadIdx.x, u = off + l;
+    unsigned* const s_x = s_w + TM + 1;
+    unsigned st = 0, mo = kNever, mt = kNever;
+    int to = TM, ta = TM;
+    bool zeros = false;
+    if (l < m) {
+        const int2 d = S.deg[u];
+        const int b = S.rp[u];
+        const int c = d.y & ~kZeroFlag;
+        zeros = (d.y & kZeroFlag) != 0;
+        if (c > R) st |= vMore;
+        unsigned w0 = 0u, xm = 0u;
+        if (d.x & kWideFlag) {
+            st |= vWide | vRare;
+        } else {
+            int nx = 0;  // lower edges from other tiles come first
+            while (nx < d.x && S.ci[b + nx] < off) ++nx;
+            xm = low_bits(nx);
+            w0 = kAllDead & ~low_bits(d.x);
+        }
+        s_w[l] = w0;
+        s_x[l] = s_y[l] = 0u;
+        s_m[l] = xm;
+        s_r[l] = 0;
+#pragma unroll
+        for (int t = 0; t < R; t += 4) {
+            const int4 q = reinterpret_cast<const int4*>(S.rec)[(size_t)u * (R / 4) + t / 4];
+            if (q.x == kRowEnt || q.y == kRowEnt || q.z == kRowEnt || q.w == kRowEnt) st |= vMore;
+            s_e[t * ES + l] = q.x;
+            s_e[(t + 1) * ES + l] = q.y;
+            s_e[(t + 2) * ES + l] = q.z;
+            s_e[(t + 3) * ES + l] = q.w;
+        }
+        to = l;
+        mt = 0u;  // looked at once to begin with
+    }
+    __syncthreads();
+    if (zeros) {  // stored zeros are no edges: dead from the start
+        for (int e = S.rp[u]; e < S.rp[u + 1]; ++e) {
+            const int j = S.ci[e];
+            if (j <= u || S.v[e] != 0.0) continue;
+            const int b = S.rp[j], e1 = S.rp[j + 1];
+            T.dead(S, j, find_col(S.ci, b, e1, u) - b, wide_row(S.ci, b, e1, j));
+        }
+    }
+    if (base >= TM) {
+        if (gridDim.x > 1 && base == TM) poll_words<TM>(S, T, s_m, &s_left);
+        else if (gridDim.x > 1) poll_choices<TM>(S, T, s_x, s_y, s_r, s_e, &s_left);
+        return;
+    }
+    // the edge of record entry q of LDS vertex b is dead
+    auto mark = [&](int b, int q) {
+        const int jl = b + (q >> 5);
+        if (jl < m) T.set(jl, 1u << (q & 31));
+        else or_dev(&S.gw[off + jl], 1u << (q & 31));
+    };
+    int cj = -1, cp = 0;  // choices from the row: vertex, position
+    bool cw = false;      // and whether it is wide
+    int4* const sel = s_sel + base / kWave * NG;
     const long long t_start = wall_clock64();
-    if (cnt[7] & 2) return;  // a counter beyond 16 bits: the host repeats the pass with rounds
-    const int off = blockIdx.x * T;
-    const int m = min(T, n - off);
-    if (threadIdx.x == 0) {
-        s_cnt = 0;
-        s_gnext = 0;
-        s_ndec = 0;
-        s_stop = 0;
-    }
-    __syncthreads();
-    // Vertices decided before the pass (dec_g -1: systems of another driver)
-    // count as done (LDS stamp 0); lower tiles may already publish others.
-    int pre = 0;
-    for (int i = threadIdx.x; i < m; i += hem_nt<SIDE>()) {
-        const bool done = dec_g[off + i] == -1;
-        pre += done;
-        s_dec[i] = (uint16_t)(done ? 0 : ((lcnt_g[off + i] & kExposed) ? kTilePend : kTileUnd));
-    }
-    for (int i = threadIdx.x; 2 * i < m; i += hem_nt<SIDE>()) {
-        const unsigned lo = (unsigned)lcnt_g[off + 2 * i] & 0xffffu;
-        const unsigned hi = 2 * i + 1 < m ? (unsigned)lcnt_g[off + 2 * i + 1] & 0xffffu : 0u;
-        s_lcnt2[i] = lo | (hi << 16);
-    }
-    if (pre) atomicAdd(&s_ndec, pre);
-    if (COMPACT) {  // compact copies of the tile's records
-        const HemRecT<7>* __restrict__ g = static_cast<const HemRecT<7>*>(S.rec);
-        for (int i = threadIdx.x; i < m; i += hem_nt<SIDE>()) {
-            const int v = off + i;
-            const HemRecT<7> R = g[v];
-            const int nh = R.hdr & 255, nl = (R.hdr >> 8) & 255;
-            bool fit = !(R.hdr & kRecOverflow) && nh <= kCSide && nl <= kCSide;
-            int16_t dh[kCSide], dl[kCSide];
+    int sweeps = 0;
+    bool late = false;
+    for (;;) {
+        const unsigned own = T.load(to), tgt = T.load(ta);
+        const bool fire = (~own & mo) == 0u || (~tgt & mt) == 0u || (int)own < 0 || (int)tgt < 0;
+        unsigned long long todo = __ballot(fire);
+        if ((++sweeps & 1023) == 0 && wall_clock64() - t_start > tmo) {
+            late = true;
+            break;
+        }
+        if (todo == 0) {
+            if (__ballot(to != TM) == 0) break;
+            if (__ballot((st & vRare) != 0) != 0) {
+                // wide vertices and choices from the row: their words in global memory
+                if ((st & vWide) && to != TM) {
+                    const unsigned* x = S.xw + (S.deg[u].x & ~kWideFlag);
+                    const int words = ((int)x[0] + 31) / 32;
+                    bool all = true;
+                    for (int i = 0; i < words && all; ++i) all = load_dev(&x[1 + i]) == ~0u;
+                    const unsigned g = load_dev(&S.gw[u]) | (all ? kAllDead : 0u);
+                    if (g != 0u) T.set(l, g);
+                }
+                if ((st & vRow) && !(st & vConf) && to != TM && cj >= 0 && T.state(S, cj, cp, cw, T.word(S, cj)) != kUnknown) mt = 0u;
+                settle();
+            }
+            __builtin_amdgcn_s_sleep(2);
+            continue;
+        }
+        __builtin_amdgcn_s_setprio(2);  // before the waves that only look
+        if (__ballot(fire && (st & vRow)) != 0) {
+            // choices from the row: one vertex at a time, by the whole wave
+            unsigned long long row = __ballot(fire && (st & vRow));
+            todo &= ~row;
+            while (row != 0) {
+                const int src = __ffsll((long long)row) - 1;
+                row &= row - 1;
+                const unsigned ow = __builtin_amdgcn_readlane(own, src);
+                unsigned f = __builtin_amdgcn_readlane(st, src);
+                int j = __builtin_amdgcn_readlane(cj, src), pos = __builtin_amdgcn_readlane(cp, src);
+                bool wide = __builtin_amdgcn_readlane((int)cw, src) != 0;
+                const int v = off + base + src;
+                bool done = false;
+                if (ow & kTaken) {
+                    wave_dead(S, T, v, -1);
+                    done = true;
+                } else {
+                    if (!(f & vConf)) {
+                        int s = j >= 0 ? T.state(S, j, pos, wide, T.word(S, j)) : kGone;
+                        if (s == kGone) j = wave_choice(S, T, v, pos, wide, s);
+                        if (j < 0) {
+                            f |= vConf;  // no neighbour left
+                        } else if (s == kAvail) {
+                            f |= vConf;
+                            wave_dead(S, T, v, j);
+                        }
+                    }
+                    if (ow == kAllDead && (f & vConf)) {
+                        if (j >= 0 && lane == 0) {
+                            S.mate[v] = j;
+                            S.mate[j] = v;
+                            T.taken(S, j, pos, wide);
+                        }
+                        if (j >= 0 && !wide && j < off + m) {
+                            const int q = lane < R ? s_e[lane * ES + (j - off)] : 0;
+                            if (q > kRowEnt) mark(j - off, q);
+                        }
+                        done = true;
+                    }
+                }
+                if (lane == src) {
+                    st = f | vRare;
+                    cj = j;
+                    cp = pos;
+                    cw = wide;
+                    ta = TM;
+                    mt = kNever;
+                    mo = f & vConf ? kAllDead : kNever;
+                    if (done) {
+                        to = TM;
+                        mo = kNever;
+                    }
+                }
+                settle();
+            }
+        }
+        // the others, NG at a time: a group of G lanes each, E record entries a lane
+        const int rank = __builtin_amdgcn_mbcnt_hi((unsigned)(todo >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)todo, 0u));
+        const bool mine = (todo >> lane) & 1u;
+        const int total = __popcll(todo);
+        int more = kNoRest;
+        for (int r0 = 0; r0 < total; r0 += NG) {
+            const bool turn = mine && rank >= r0 && rank < r0 + NG;
+            if (turn) sel[rank - r0] = make_int4(lane, (int)own, (int)st, 0);
+            __builtin_amdgcn_wave_barrier();
+            const int4 in = sel[lane / G];
+            const bool live = r0 + lane / G < total;
+            const int lv = base + (live ? in.x : 0), t = lane % G;
+            const unsigned ow = live ? (unsigned)in.y : 0u, f = (unsigned)in.z;
+            const int k0 = (int)(f & 0xffffu);
+            const bool tk = (ow & kTaken) != 0u, conf = (f & vConf) != 0u;
+            const unsigned kn = lds_load(&s_x[lv]), av = lds_load(&s_y[lv]), xm = s_m[lv];
+            int q[E], jl[E];
+            unsigned cm = 0u, fm = 0u, rm = 0u;  // entries: candidates, available ones, ones that the row holds
 #pragma unroll
-            for (int t = 0; t < kCSide; ++t) {
-                const int a = t < nh ? R.h[t] - v : 0, b = t < nl ? R.l[t] - v : 0;
-                fit = fit && a >= -32768 && a <= 32767 && b >= -32768 && b <= 32767;
-                dh[t] = (int16_t)a;
-                dl[t] = (int16_t)b;
+            for (int i = 0; i < E; ++i) {
+                q[i] = live ? s_e[(t + i * G) * ES + lv] : 0;
+                jl[i] = lv + (q[i] >> 5);
             }
 #pragma unroll
-            for (int t = 0; t < kCSide; ++t) {
-                c_h[t * CR + i] = dh[t];
-                c_l[t * CR + i] = dl[t];
+            for (int i = 0; i < E; ++i) {
+                const int e = t + i * G;
+                const unsigned w = T.load(jl[i] < m ? jl[i] : TM);
+                const bool full = (~w & low_bits(q[i] & 31)) == 0u || ((kn & av) >> e) & 1u;
+                const bool gone = !full && (jl[i] < m ? (int)w < 0 : ((kn >> e) & 1u) != 0u);
+                cm |= group_mask<G>(q[i] != 0 && (conf ? e == k0 : e >= k0 && (q[i] == kRowEnt || !gone))) << (i * G);
+                fm |= group_mask<G>(full) << (i * G);
+                rm |= group_mask<G>(q[i] == kRowEnt) << (i * G);
             }
-            c_hdr[i] = (uint8_t)(fit ? nh | (nl << 3) : kCGlobal);
+            const int k = cm != 0u ? __ffs(cm) - 1 : R;
+            const unsigned bk = cm & (0u - cm);  // its bit, or none
+            const bool row = !tk && !conf && ((rm & bk) != 0u || (cm == 0u && (f & vMore)));
+            const bool nconf = !tk && !conf && !row && (cm == 0u || (fm & bk) != 0u);
+            const bool all = tk && ((f & vWide) || ((xm >> ((__ffs(~ow) - 1) & 31)) & 1u));  // no taker of this tile did it
+            const bool take = (conf || nconf) && !tk && ow == kAllDead;
+            int kl = -1;  // the choice's LDS index, in the lane that holds its entry
+#pragma unroll
+            for (int i = 0; i < E; ++i) {
+                const int e = t + i * G;
+                if (q[i] > kRowEnt && (all || (nconf && e > k))) mark(lv, q[i]);
+                if (e == k) kl = jl[i];
+                if (e == k && take) {
+                    S.mate[off + lv] = off + jl[i];
+                    S.mate[off + jl[i]] = off + lv;
+                    T.set_word(S, off + jl[i], ~(1u << (q[i] & 31)));
+                }
+            }
+            if (__ballot(take) != 0) {  // the taken ones' edges are dead too: marked here, their ends see it one step earlier
+                const int kt = __shfl(kl, (lane & ~(G - 1)) + (k & (G - 1)));
+#pragma unroll
+                for (int i = 0; i < E; ++i) {
+                    const int q2 = take && cm != 0u && kt < m ? s_e[(t + i * G) * ES + kt] : 0;
+                    if (q2 > kRowEnt) mark(kt, q2);
+                }
+            }
+            if (live && t == (k & (G - 1))) {  // k = R: lane 0
+                const bool done = tk || take;
+                int nta = TM;
+                unsigned nmt = row ? 0u : kNever;
+                if (!done && !conf && !nconf && !row) {
+                    nta = kl < m ? kl : TM + 1 + lv;
+                    nmt = 1u << (k & 31);
+#pragma unroll
+                    for (int i = 0; i < E; ++i)
+                        if (t + i * G == k && kl < m) nmt = low_bits(q[i] & 31);
+                    if (kl >= m) lds_store(&s_r[lv], k + 1);
+                }
+                const unsigned nf = (f & ~0xffffu) | (unsigned)k | (nconf ? vConf : 0u) | (row ? vRow : 0u) | (done ? vDone : 0u);
+                const int rest = !(f & vMore) ? kNoRest : tk ? -1 : nconf ? off + kl : kNoRest;
+                sel[lane / G] = make_int4((int)nf, nta, (int)nmt, rest);
+            }
+            __builtin_amdgcn_wave_barrier();
+            if (turn) {
+                const int4 o = sel[rank - r0];
+                st = (unsigned)o.x;
+                ta = o.y;
+                mt = (unsigned)o.z;
+                more = o.w;
+                mo = st & vDone ? kNever : st & vConf ? kAllDead : kNever;
+                if (st & vDone) to = TM;
+            }
         }
-    }
-    __syncthreads();
-    const TileSt st{s_dec, s_lcnt2, off, m, dec_g};
-    const CRecs C{c_hdr, c_h, c_l, static_cast<const HemRecT<7>*>(S.rec), off, COMPACT ? m : 0};
-    int* gin = gl0 + off;
-    int* gout = gl1 + off;
-    uint16_t* cur = s_la;
-    uint16_t* nxt = s_lb;
-    int kl, kg;
-    {  // the first list: undecided vertices without undecided lower neighbours in the tile
-        const Appender<uint16_t> A{cur, &s_cnt, TL_LCAP, gin, &s_gnext, off};
-        for (int i = threadIdx.x; i < m; i += hem_nt<SIDE>())
-            if (s_dec[i] != 0 && (lcnt_g[off + i] & 0xffff) == 0) A.push(off + i);
-        __syncthreads();
-        kl = min(s_cnt, TL_LCAP);
-        kg = s_gnext;
-        __syncthreads();
-    }
-    int r = 2;  // stamps r - 1 >= 1 mark vertices found taken
-    bool stop = s_ndec >= m;
-    while (!stop) {
-        if (threadIdx.x == 0) {
-            s_cnt = 0;
-            s_gnext = 0;
+        if (__ballot(more != kNoRest) != 0) {
+            unsigned long long rest = __ballot(more != kNoRest);
+            while (rest != 0) {
+                const int src = __ffsll((long long)rest) - 1;
+                rest &= rest - 1;
+                wave_dead(S, T, off + base + src, __builtin_amdgcn_readlane(more, src));
+            }
+            settle();
         }
-        __syncthreads();
-        const Appender<uint16_t> A{nxt, &s_cnt, TL_LCAP, gout, &s_gnext, off};
-        const int klc = kl;
-        // compact tiles: the round's first items go to wave r mod (waves), so
-        // the wave that visited in the previous round, whose stores may still
-        // be in flight, does not wait for them at its first memory access
-        constexpr int NW = hem_nt<SIDE>() / kWave;
-        const int first = COMPACT ? (int)((threadIdx.x + (unsigned)(NW - r % NW) * kWave) % hem_nt<SIDE>())
-                                  : (int)threadIdx.x;
-        for (int idx = first; idx < kl + kg; idx += hem_nt<SIDE>()) {
-            const int u = idx < klc ? (int)cur[idx] + off : gin[idx - klc];
-            if (COMPACT) tile_visit_lean(S, st, C, r, u, A, &s_ndec);
-            else tile_visit<SIDE>(S, st, r, u, A, &s_ndec);
-        }
-        if (threadIdx.x == 0 && (r & 31) == 0 && (wall_clock64() - t_start > tmo || r >= kTileMaxRound))
-            s_stop = 1;
-        __syncthreads();
-        kl = min(s_cnt, TL_LCAP);
-        kg = s_gnext;
-        stop = s_ndec >= m || s_stop != 0;
-        __syncthreads();  // every thread has read the counts before the next reset
-        uint16_t* t = cur;
-        cur = nxt;
-        nxt = t;
-        int* tg = gin;
-        gin = gout;
-        gout = tg;
-        ++r;
+        __builtin_amdgcn_s_setprio(0);
     }
-    if (threadIdx.x == 0) {
-        atomicMax(&cnt[6], r - 2);
-        if (s_ndec < m) atomicOr(&cnt[7], 1);
+    if (lane == 0) {
+        if (late) atomicOr(&cnt[7], 1);
+        atomicMax(&s_max, sweeps);
+        if (atomicSub(&s_left, 1) == 1)
+            atomicMax(&cnt[6], lds_load(&s_max));
     }
 }
 
@@ -1665,100 +918,55 @@ void launch_unmirror_mate(int n, const int* mr, int* mate, hipStream_t s) {
     hipLaunchKernelGGL(k_unmirror_mate, dim3(blocks_for(n)), dim3(BS), 0, s, n, mr, mate);
 }
 
-#define AMG_HEM_SIDE(side, CALL) \
-    switch (side) {                \
-        case 7: CALL(7); break;    \
-        case 15: CALL(15); break;  \
-        default: CALL(31); break;  \
-    }
+// Record entries of a pass, by its average row: rows of up to 7.5 entries (the
+// 5- and 7-point operators and what regular aggregates make of them) have 2 or
+// 3 higher neighbours; the coarse operators of irregular aggregates have up to
+// a dozen at 14 entries a row and up to about 30 at 20.  A longer list goes on
+// in the row, which costs a few microseconds each time it is needed.
+static int hem_record(int n, int64_t nnz, size_t room) {
+    const double avg = (double)nnz / n;
+    const int r = avg <= 7.5 ? 4 : avg <= 14.0 ? 16 : 32;
+    return r == 32 && (size_t)n * 32 > room ? 16 : r;
+}
 
-void launch_hem_init(int n, const int* rp, const int* ci, const double* v, HemWork& w, hipStream_t s) {
-#define CALL(SD)                                                                                  \
-    hipLaunchKernelGGL(k_hem_init<SD>, dim3(blocks_for(n)), dim3(BS), 0, s, n, rp, ci, v, w.lowok, \
-                       static_cast<HemRecT<SD>*>(w.rec), w.lcnt, w.dec, w.mate, w.wl[0], w.cnt, w.err)
-    AMG_HEM_SIDE(w.side, CALL)
+void launch_hem_init(int n, int64_t nnz, const int* rp, const int* ci, const double* v, HemWork& w, hipStream_t s) {
+    w.side = hem_record(n, nnz, w.rec_ints);
+    const dim3 g(blocks_for(n));
+#define CALL(R)                                                                                                   \
+    hipLaunchKernelGGL(k_hem_init<R>, g, dim3(BS), 0, s, n, rp, ci, v, w.rec, w.deg, w.gw, w.xw, w.mate, w.cnt,   \
+                       w.err)
+    if (w.side == 4) CALL(4);
+    else if (w.side == 16) CALL(16);
+    else CALL(32);
 #undef CALL
 }
 
-int hem_next_count_slot(int round) { return round % 3; }
+// Workgroup sizes.  Larger tiles have fewer steps across tiles (3 to 4 us
+// against about 1 us inside one) but more waves that share a compute unit's
+// issue slots.  Measured, pass times with workgroups of 1024 / 512 / 256:
+//   short rows, 2,097,152 rows (128^3)           2.20 / 1.85 / 2.35 ms
+//   short rows, 442,368 rows                     0.50 / 0.43 / 0.54 ms
+//   long rows, 512,715 rows of 13.4 entries      2.05 / 1.71 / 1.52 ms
+//   long rows, 16,533 rows of 18.6 entries       0.86 / 0.83 / 0.75 ms
+//   long rows, 4,440 rows of 18.8 entries        0.47 / 0.51 / 0.54 ms
+constexpr int kFewRows = 10000;  // long rows: up to here the large tiles win
 
-void launch_hem_round(int r, int n, const int* rp, const int* ci, const double* v, HemWork& w, hipStream_t s) {
-    const int g = blocks_for(n, HEM_BS, w.round_grid);
-    const HemState S{rp, ci, v, w.lowok, w.rec, w.mate};
-#define CALL(SD)                                                                                            \
-    hipLaunchKernelGGL(k_hem_round<SD>, dim3(g), dim3(HEM_BS), 0, s, r, n, S, w.dec, w.lcnt, w.wl[r & 1],    \
-                       w.wl[(r + 1) & 1], w.cnt, r % 3, (r + 1) % 3, (r + 2) % 3)
-    AMG_HEM_SIDE(w.side, CALL)
-#undef CALL
-}
-
-void launch_hem_lds_seg(int nseg, const int2* seg, const int* rp, const int* ci, const double* v, HemWork& w,
-                        int* sl0, int* sl1, hipStream_t s) {
-    if (nseg <= 0) return;
-    const HemState S{rp, ci, v, w.lowok, w.rec, w.mate};
-#define CALL(SD)                                                                                                 \
-    hipLaunchKernelGGL(k_hem_lds_seg<SD>, dim3(nseg), dim3(hem_nt<SD>()), 0, s, seg, S, w.lcnt, w.dec, sl0, sl1, \
-                       w.cnt, w.lds_rows < kHemLdsRows ? w.lds_rows : kHemLdsRows)
-    AMG_HEM_SIDE(w.side, CALL)
-#undef CALL
-}
-
-// Rows of system j of a pass from the previous pass's aggregate map: the
-// systems start at rows off[j] of the previous operator, so in this one at
-// agg[off[j]]; with mirror the operator is numbered backwards (n rows).
-__global__ __launch_bounds__(BS) void k_seg_table(int m, const int* __restrict__ off, const int* __restrict__ agg,
-                                                  int n, int mirror, int2* __restrict__ seg) {
-    const int j = blockIdx.x * BS + threadIdx.x;
-    if (j >= m) return;
-    const int a = off[j] >= 0 ? agg[off[j]] : 0;
-    const int b = j + 1 < m ? agg[off[j + 1]] : n;
-    seg[j] = mirror ? make_int2(n - b, b - a) : make_int2(a, b - a);
-}
-
-void launch_seg_table(int m, const int* off, const int* agg, int n, bool mirror, int2* seg, hipStream_t s) {
-    hipLaunchKernelGGL(k_seg_table, dim3(blocks_for(m)), dim3(BS), 0, s, m, off, agg, n, mirror ? 1 : 0, seg);
-}
-
-void launch_hem_tile(int n, int64_t nnz, const int* rp, const int* ci, const double* v, HemWork& w, long long tmo,
+void launch_hem_tile(int n, const int* rp, const int* ci, const double* v, HemWork& w, long long tmo,
                      hipStream_t s) {
-    // Small tiles with LDS copies of the records cut the cost of a round but
-    // multiply the vertices whose lower neighbours lie in other tiles, and a
-    // step across tiles costs several rounds.  As measured on MI355X they pay
-    // for passes of short rows (at most 8 entries on average, so nearly every
-    // record fits) of at most 512 tiles; more tiles cannot all be resident at
-    // once (one workgroup per compute unit), so a tile would wait for a lower
-    // one to finish, and on the long chains of such passes that loses.
-    const int Tc = w.tile_c_rows < kTileCRows ? w.tile_c_rows : kTileCRows;
-    const int64_t ntc = Tc > 0 ? ((int64_t)n + Tc - 1) / Tc : 0;
-    const bool compact = w.side == 7 && Tc > 0 && nnz <= 8 * (int64_t)n &&
-                         (w.tile_c_rows < kTileCRows || ntc <= kCompactMaxTiles);
-    const int T = compact ? Tc : w.tile_rows;
-    const int nt = (n + T - 1) / T;
-    hipLaunchKernelGGL(k_hem_tile_prep, dim3(blocks_for(n)), dim3(BS), 0, s, n, T, rp, ci, w.lowok, w.lcnt, w.cnt);
-    const HemState S{rp, ci, v, w.lowok, w.rec, w.mate};
-#define CALL(SD, CP)                                                                                              \
-    hipLaunchKernelGGL((k_hem_tile<SD, CP>), dim3(nt), dim3(hem_nt<SD>()), 0, s, n, T, S, w.dec, w.lcnt, w.wl[0], \
-                       w.wl[1], w.cnt, tmo)
-    if (compact) CALL(7, true);
-    else if (w.side == 7) CALL(7, false);
-    else CALL(15, false);  // records of tiled passes hold at most 15 entries a side
-#undef CALL
-}
-
-void launch_hem_all(int n, const int* rp, const int* ci, const double* v, HemWork& w, hipStream_t s) {
-    const HemState S{rp, ci, v, w.lowok, w.rec, w.mate};
-    if (n <= w.lds_rows) {
-#define CALL(SD) \
-    hipLaunchKernelGGL(k_hem_lds<SD>, dim3(1), dim3(hem_nt<SD>()), 0, s, n, S, w.lcnt, w.wl[0], w.wl[1], w.cnt)
-        AMG_HEM_SIDE(w.side, CALL)
-#undef CALL
-    } else {
-#define CALL(SD) \
-    hipLaunchKernelGGL(k_hem_all<SD>, dim3(1), dim3(hem_nt<SD>()), 0, s, n, S, w.dec, w.lcnt, w.wl[0], w.wl[1], w.cnt)
-        AMG_HEM_SIDE(w.side, CALL)
-#undef CALL
+    const HemState S{n, rp, ci, v, w.rec, w.deg, w.gw, w.xw, w.mate};
+#define CALL(R, NT)                                                                                               \
+    {                                                                                                             \
+        const int tm = NT - 2 * kWave;                                                                            \
+        const int rows = w.tile_rows > 0 && w.tile_rows < tm ? w.tile_rows : tm;                                  \
+        hipLaunchKernelGGL((k_hem_tile<R, NT>), dim3((unsigned)(((int64_t)n + rows - 1) / rows)), dim3(NT), 0, s, \
+                           S, rows, w.cnt, w.err, tmo);                                                           \
     }
+    if (w.side == 4) CALL(4, 512)
+    else if (w.side == 16 && n > kFewRows) CALL(16, 256)
+    else if (w.side == 16) CALL(16, 1024)
+    else if (n > kFewRows) CALL(32, 256)
+    else CALL(32, 1024)
+#undef CALL
 }
-#undef AMG_HEM_SIDE
 
 }  // namespace amg
