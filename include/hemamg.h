@@ -61,8 +61,8 @@ typedef struct {
     int32_t max_levels;       /* levels including the coarsest, 1..64 (32)        */
     int32_t max_dense_rows;   /* largest coarsest level accepted when coarsening  *
                                * stalls or hits max_levels, 1..4096 (4096); the   *
-                               * coarsest level is factored densely (LU) and      *
-                               * applied as an explicit inverse                   */
+                               * coarsest level is inverted densely (partial      *
+                               * pivoting) and applied as an explicit inverse     */
     double omega;             /* damped-Jacobi weight (2/3)                       */
     int32_t pre, post;        /* smoothing sweeps before/after the coarse
                                * correction, 0..8 (1, 1)                          */
@@ -145,7 +145,7 @@ amg_status amg_release_cached(void);
 amg_status amg_params_default(amg_params* p);
 
 /* Setup phase (Section 3; Algorithm 2 per pass; coarse operator P^T A P of
- * Section 2.1.1; LU of the coarsest matrix, Section 2).  Validates A (sorted
+ * Section 2.1.1; inverse of the coarsest matrix, Section 2).  Validates A (sorted
  * in-range columns, non-zero finite diagonal, finite values, structural
  * symmetry), builds every level on the GPU and returns a handle in *out
  * (*out = NULL on error).  Blocks the host until the stream has finished.

@@ -1212,7 +1212,7 @@ void setup_impl(const amg_csr* Ain, const amg_params* pin, const amg_allocator* 
         HIPCHK(hipGetLastError());  // its error bit is read back with the next level's sizes
         h->lev.push_back(C);
     }
-    // coarsest level: dense LU and inverse
+    // coarsest level: dense inverse
     Level& Lc = h->lev.back();
     const int m = Lc.n;
     h->n_coarse = m;
@@ -1221,17 +1221,15 @@ void setup_impl(const amg_csr* Ain, const amg_params* pin, const amg_allocator* 
         DevPool tmp;
         tmp.s = s;
         tmp.al = al;
-        tmp.hint(8 * (size_t)m * m + 8 * (size_t)m + 4096);
+        const size_t wd = dense_work_doubles(m);
+        tmp.hint(8 * wd + 4096);
         struct TmpGuard {
             DevPool& t;
             ~TmpGuard() { t.release(); }
         } tg{tmp};
-        double* a = tmp.get<double>((size_t)m * m);
-        int* piv = tmp.get<int>(2 * (size_t)m);  // permutation and pivot rows
+        double* work = wd ? tmp.get<double>(wd) : nullptr;
         h->ainv_t = P.get<double>((size_t)m * m);
-        HIPCHK(hipMemsetAsync(a, 0, sizeof(double) * (size_t)m * m, s));
-        launch_dense_assemble(m, Lc.rp, Lc.ci, Lc.v, a, s);
-        launch_dense_lu_inverse(m, a, piv, h->ainv_t, h->err, s);
+        launch_dense_inverse(DenseJob{m, 0, Lc.rp, Lc.ci, Lc.v, h->ainv_t, h->err}, work, s);
         HIPCHK(hipGetLastError());
         check_err_word(h->err, s, "coarsest level");
     }
@@ -1618,7 +1616,8 @@ void batch_coarsen(const amg_csr* A, int count, const amg_params& p, hipStream_t
         live.swap(next);
     }
     check_err_word(gerr, s, "amg_batch_setup");
-    // coarsest blocks: dense LU and inverse per system
+    // coarsest blocks: the inverse of each system, small ones in one launch a size class
+    std::vector<DenseJob> jobs[2];
     for (const Coarsest& c : fin) {
         SegSrc& S = out[c.seg];
         const int m = c.L.n;
@@ -1627,14 +1626,18 @@ void batch_coarsen(const amg_csr* A, int count, const amg_params& p, hipStream_t
             continue;
         }
         if (m > kDenseMaxRows) raise(AMG_EHIP, "coarsest level of %d rows exceeds the dense limit (internal error)", m);
-        double* a = P.get<double>((size_t)m * m);
-        int* piv = P.get<int>(2 * (size_t)m);
         double* ainv = P.get<double>((size_t)m * m);
-        HIPCHK(hipMemsetAsync(a, 0, sizeof(double) * (size_t)m * m, s));
-        launch_dense_assemble(m, c.C.rp + c.L.off, c.C.ci, c.C.v, a, s, -c.L.off);
-        launch_dense_lu_inverse(m, a, piv, ainv, err + c.seg, s);
+        const DenseJob J{m, -c.L.off, c.C.rp + c.L.off, c.C.ci, c.C.v, ainv, err + c.seg};
+        if (m <= kDenseSmall) jobs[m > 64].push_back(J);
+        else launch_dense_inverse(J, P.get<double>(dense_work_doubles(m)), s);
         S.ainv_t = ainv;
         S.lev.back().mem = nullptr;
+    }
+    for (int k = 0; k < 2; ++k) {
+        if (jobs[k].empty()) continue;
+        DenseJob* jd = P.get<DenseJob>(jobs[k].size());
+        HIPCHK(hipMemcpyAsync(jd, jobs[k].data(), sizeof(DenseJob) * jobs[k].size(), hipMemcpyHostToDevice, s));
+        launch_dense_small(DenseJob{}, jd, (int)jobs[k].size(), k == 0 ? 64 : kDenseSmall, s);
     }
     HIPCHK(hipGetLastError());
     std::vector<int> e(count);

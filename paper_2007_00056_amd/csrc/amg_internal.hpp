@@ -17,7 +17,7 @@ enum : int {
 };
 
 constexpr int kUndecided = 0x3fffffff;  // round stamp of an undecided vertex
-constexpr int kDenseMaxRows = 4096;     // largest coarsest level (dense LU, explicit inverse)
+constexpr int kDenseMaxRows = 4096;     // largest coarsest level (explicit inverse)
 
 // Lanes per CSR row used by the level kernels (a power of two, 1..16).
 int pick_lanes_per_row(double avg_row_len);
@@ -93,15 +93,30 @@ void launch_compose(int n, const int* agg1, const int* agg2, int* out, hipStream
 void launch_members(int nc, const int* lead2, const int* mate2, const int* lead1, const int* mate1, int4* mem,
                     hipStream_t s);
 
-// a must be zeroed before the call.  col_add shifts the stored columns (a
-// diagonal block of a larger matrix); entries outside the block are skipped.
-void launch_dense_assemble(int n, const int* rp, const int* ci, const double* v, double* a, hipStream_t s,
-                           int col_add = 0);
 // Systems stored one after another in a level: out[2j] = agg[off[j]],
 // out[2j+1] = crp[out[2j]] (coarse row and entry where system j starts).
 void launch_seg_starts(int m, const int* off, const int* agg, const int* crp, int* out, hipStream_t s);
-// piv: int32[2n] scratch.  n <= kDenseMaxRows.
-void launch_dense_lu_inverse(int n, double* a, int* piv, double* ainv_t, int* err, hipStream_t s);
+
+// ---- coarsest inverse (k_dense.hip) -----------------------------------------
+// One system: n <= kDenseMaxRows CSR rows; col_add shifts the stored columns (a
+// diagonal block of a larger matrix; entries outside the block are skipped).
+// ainv_t receives the inverse column-major; err |= ERR_SINGULAR on a zero pivot.
+struct DenseJob {
+    int n;
+    int col_add;
+    const int* rp;
+    const int* ci;
+    const double* v;
+    double* ainv_t;
+    int* err;
+};
+constexpr int kDenseSmall = 128;  // systems up to this size take one workgroup and no workspace
+// Systems of at most nmax <= kDenseSmall rows, one workgroup each: the `count`
+// jobs at `many` (device), or `one` when that is null.
+void launch_dense_small(const DenseJob& one, const DenseJob* many, int count, int nmax, hipStream_t s);
+// Any size; work: dense_work_doubles(n) doubles.
+size_t dense_work_doubles(int n);
+void launch_dense_inverse(const DenseJob& J, double* work, hipStream_t s);
 
 // ---- solve kernels (k_solve.hip) --------------------------------------------
 struct LevelView {

@@ -1,7 +1,7 @@
 // Setup-phase kernels: CSR validation and D^{-1}, coarse numbering of a
-// matching (Algorithm 2) by prefix sum, the 0/1 Galerkin product P^T A P,
-// aggregate member lists, and the dense LU + inverse of the coarsest level.
-// The matching itself is in k_hem.hip.
+// matching (Algorithm 2) by prefix sum, the 0/1 Galerkin product P^T A P and
+// aggregate member lists.  The matching itself is in k_hem.hip, the coarsest
+// level's inverse in k_dense.hip.
 #include "amg_device.hpp"
 #include "amg_internal.hpp"
 
@@ -548,30 +548,6 @@ void launch_members(int nc, const int* lead2, const int* mate2, const int* lead1
     hipLaunchKernelGGL(k_members, dim3(blocks_for(nc)), dim3(BS), 0, s, nc, lead2, mate2, lead1, mate1, mem);
 }
 
-// ---------------------------------------------------------------------------
-// Coarsest level (Section 2, coarse level solver): dense partial-pivot LU,
-// largest |pivot| with the lowest row on ties, then the explicit inverse so
-// that each V-cycle applies the exact coarse solve as one dense product
-// (n <= 1024).
-// ---------------------------------------------------------------------------
-// Row i of the block: entries rp[i]..rp[i+1]-1 of ci/v, columns shifted by
-// col_add (a diagonal block of a larger matrix starts at column -col_add).
-__global__ __launch_bounds__(BS) void k_dense_assemble(int n, const int* __restrict__ rp, const int* __restrict__ ci,
-                                                       const double* __restrict__ v, double* __restrict__ a,
-                                                       int col_add) {
-    const int i = blockIdx.x * BS + threadIdx.x;
-    if (i >= n) return;
-    for (int k = rp[i]; k < rp[i + 1]; ++k) {
-        const int c = ci[k] + col_add;
-        if (c >= 0 && c < n) a[(size_t)i * n + c] = v[k];
-    }
-}
-
-void launch_dense_assemble(int n, const int* rp, const int* ci, const double* v, double* a, hipStream_t s,
-                           int col_add) {
-    hipLaunchKernelGGL(k_dense_assemble, dim3(blocks_for(n)), dim3(BS), 0, s, n, rp, ci, v, a, col_add);
-}
-
 // Start of each system inside a concatenated level and its coarse level:
 // out[2j] = agg[off[j]] (first coarse row), out[2j+1] = crp[out[2j]].
 __global__ __launch_bounds__(BS) void k_seg_starts(int m, const int* __restrict__ off, const int* __restrict__ agg,
@@ -585,248 +561,6 @@ __global__ __launch_bounds__(BS) void k_seg_starts(int m, const int* __restrict_
 
 void launch_seg_starts(int m, const int* off, const int* agg, const int* crp, int* out, hipStream_t s) {
     hipLaunchKernelGGL(k_seg_starts, dim3(blocks_for(m)), dim3(BS), 0, s, m, off, agg, crp, out);
-}
-
-namespace {
-constexpr int LU_BS = 1024;
-constexpr int INV_BS = 256;
-
-// Block-wide argmax of (|value|, lowest index on ties) over LU_BS threads.
-__device__ __forceinline__ void lu_argmax(double& v, int& i, double* sv, int* si) {
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        const double ov = __shfl_xor(v, off);
-        const int oi = __shfl_xor(i, off);
-        if (ov > v || (ov == v && oi < i)) {
-            v = ov;
-            i = oi;
-        }
-    }
-    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-    if (lane == 0) {
-        sv[wid] = v;
-        si[wid] = i;
-    }
-    __syncthreads();
-    v = sv[0];
-    i = si[0];
-    for (int w = 1; w < LU_BS / kWave; ++w)
-        if (sv[w] > v || (sv[w] == v && si[w] < i)) {
-            v = sv[w];
-            i = si[w];
-        }
-}
-}  // namespace
-
-// Blocked right-looking LU with partial pivoting in place (row-major a, unit
-// lower L below the diagonal; P A = L U with perm[i] = original row of
-// position i).  Panels of NB columns: k_lu_panel factors the panel's rows
-// k0.. in LDS (pivot = largest |value|, lowest row on ties), then k_lu_rest
-// applies the panel's interchanges to every other column and, right of the
-// panel, forms U12 = L11^{-1} A12 and A22 -= L21 U12.  Each entry receives its
-// updates in the order of the unblocked algorithm, whatever NB.  The panel of
-// the remaining m = n - k0 rows must fit LDS: NB = 16 up to 1024 rows, 8 up
-// to 2048, 4 up to 4096 (n <= 4096).
-constexpr int LU_COLS = 64;        // columns per block of k_lu_rest
-constexpr int LU_LDS_DOUBLES = 18432;  // 144 KiB of panel
-
-template <int NB>
-constexpr int lu_ldp() { return NB >= 8 ? NB + 1 : NB; }  // padded LDS row of the panel
-
-template <int NB>
-__global__ __launch_bounds__(LU_BS) void k_lu_panel(int n, int k0, double* __restrict__ a, int* __restrict__ perm,
-                                                    int* __restrict__ piv, int* err) {
-    constexpr int LDP = lu_ldp<NB>();
-    __shared__ double P[LU_LDS_DOUBLES];
-    __shared__ double sv[LU_BS / kWave];
-    __shared__ int si[LU_BS / kWave];
-    if (*err & ERR_SINGULAR) return;  // an earlier panel failed (uniform)
-    const int tid = threadIdx.x;
-    const int kb = min(NB, n - k0), m = n - k0;
-    if (k0 == 0)
-        for (int i = tid; i < n; i += LU_BS) perm[i] = i;
-    if (tid < kb) piv[k0 + tid] = k0 + tid;  // valid even if this panel fails
-    for (int t = tid; t < m * NB; t += LU_BS) {
-        const int r = t / NB, c = t % NB;
-        P[r * LDP + c] = c < kb ? a[(size_t)(k0 + r) * n + k0 + c] : 0.0;
-    }
-    __syncthreads();
-    for (int c = 0; c < kb; ++c) {
-        double best = -1.0;
-        int bi = m;
-        for (int r = c + tid; r < m; r += LU_BS) {
-            const double v = fabs(P[r * LDP + c]);
-            if (v > best) {  // rows ascend per thread: strict '>' keeps the lowest
-                best = v;
-                bi = r;
-            }
-        }
-        lu_argmax(best, bi, sv, si);
-        if (!(best > 0.0) || !isfinite(best)) {  // uniform across the block
-            if (tid == 0) atomicOr(err, ERR_SINGULAR);
-            return;
-        }
-        if (bi != c && tid < NB) {
-            const double t = P[c * LDP + tid];
-            P[c * LDP + tid] = P[bi * LDP + tid];
-            P[bi * LDP + tid] = t;
-        }
-        if (tid == 0) piv[k0 + c] = k0 + bi;
-        __syncthreads();
-        const double d = P[c * LDP + c];
-        for (int r = c + 1 + tid; r < m; r += LU_BS) {
-            const double l = P[r * LDP + c] / d;
-            P[r * LDP + c] = l;
-            for (int j = c + 1; j < kb; ++j) P[r * LDP + j] -= l * P[c * LDP + j];
-        }
-        __syncthreads();
-    }
-    for (int t = tid; t < m * NB; t += LU_BS) {
-        const int r = t / NB, c = t % NB;
-        if (c < kb) a[(size_t)(k0 + r) * n + k0 + c] = P[r * LDP + c];
-    }
-    if (tid == 0)
-        for (int c = 0; c < kb; ++c) {
-            const int p = piv[k0 + c];
-            if (p != k0 + c) {
-                const int t = perm[k0 + c];
-                perm[k0 + c] = perm[p];
-                perm[p] = t;
-            }
-        }
-}
-
-// A block owns LU_COLS columns; 4 groups of 64 threads share its rows.
-template <int NB>
-__global__ __launch_bounds__(256) void k_lu_rest(int n, int k0, double* __restrict__ a, const int* __restrict__ piv,
-                                                 const int* err) {
-    __shared__ double L11[NB][NB];
-    __shared__ double U[NB][LU_COLS];
-    if (*err & ERR_SINGULAR) return;  // uniform
-    const int kb = min(NB, n - k0);
-    const int cl = threadIdx.x % LU_COLS, rg = threadIdx.x / LU_COLS;
-    const int j = blockIdx.x * LU_COLS + cl;
-    const bool mine = j < n && (j < k0 || j >= k0 + kb);
-    const bool right = mine && j >= k0 + kb;
-    for (int t = threadIdx.x; t < kb * kb; t += 256) L11[t / kb][t % kb] = a[(size_t)(k0 + t / kb) * n + k0 + t % kb];
-    if (rg == 0 && mine)
-        for (int c = 0; c < kb; ++c) {
-            const int p = piv[k0 + c];
-            if (p > k0 + c && p < n) {
-                const double t = a[(size_t)(k0 + c) * n + j];
-                a[(size_t)(k0 + c) * n + j] = a[(size_t)p * n + j];
-                a[(size_t)p * n + j] = t;
-            }
-        }
-    __syncthreads();
-    if (rg == 0 && right)
-        for (int i = 0; i < kb; ++i) {
-            double u = a[(size_t)(k0 + i) * n + j];
-            for (int q = 0; q < i; ++q) u -= L11[i][q] * U[q][cl];
-            U[i][cl] = u;
-            a[(size_t)(k0 + i) * n + j] = u;
-        }
-    __syncthreads();
-    if (right)
-        for (int r = k0 + kb + rg; r < n; r += 4) {
-            const double* l = a + (size_t)r * n + k0;
-            double s = a[(size_t)r * n + j];
-            for (int q = 0; q < kb; ++q) s -= l[q] * U[q][cl];
-            a[(size_t)r * n + j] = s;
-        }
-}
-
-// Columns of A^{-1} = U^{-1} L^{-1} P, INV_COLS per block, held in LDS as
-// x[i * INV_COLS + c].  Both substitutions go by blocks of 16 rows: the
-// block's rows first subtract the contributions of the rows already solved
-// (one dot per row and column, all threads), then lane c of the first wave
-// finishes column c through the 16x16 diagonal block kept in LDS.  Writes
-// the inverse column-major: ainv_t[c * n + i] = (A^{-1})_{ic}.
-template <int INV_COLS, int XCAP>
-__global__ __launch_bounds__(INV_BS) void k_dense_inverse(int n, const double* __restrict__ lu,
-                                                          const int* __restrict__ perm, double* __restrict__ ainv_t) {
-    constexpr int RB = 16;
-    __shared__ double x[XCAP];  // n * INV_COLS <= XCAP
-    __shared__ double D[RB][RB + 1];
-    const int c0 = blockIdx.x * INV_COLS;
-    const int tid = threadIdx.x;
-    for (int t = tid; t < n * INV_COLS; t += INV_BS) {
-        const int i = t / INV_COLS, cc = t % INV_COLS;
-        x[t] = perm[i] == c0 + cc ? 1.0 : 0.0;
-    }
-    __syncthreads();
-    const int oi = tid / INV_COLS, oc = tid % INV_COLS;  // (row in block, column) of this thread's output
-    for (int b0 = 0; b0 < n; b0 += RB) {  // unit lower
-        const int bs = min(RB, n - b0);
-        if (oi < bs) {
-            const double* l = lu + (size_t)(b0 + oi) * n;
-            double s = 0.0;
-            for (int k = 0; k < b0; ++k) s += l[k] * x[k * INV_COLS + oc];
-            x[(b0 + oi) * INV_COLS + oc] -= s;
-        }
-        for (int t = tid; t < bs * bs; t += INV_BS) D[t / bs][t % bs] = lu[(size_t)(b0 + t / bs) * n + b0 + t % bs];
-        __syncthreads();
-        if (tid < INV_COLS)
-            for (int i = 1; i < bs; ++i) {
-                double s = 0.0;
-                for (int k = 0; k < i; ++k) s += D[i][k] * x[(b0 + k) * INV_COLS + tid];
-                x[(b0 + i) * INV_COLS + tid] -= s;
-            }
-        __syncthreads();
-    }
-    for (int b0 = ((n - 1) / RB) * RB; b0 >= 0; b0 -= RB) {  // upper
-        const int bs = min(RB, n - b0);
-        if (oi < bs) {
-            const double* u = lu + (size_t)(b0 + oi) * n;
-            double s = 0.0;
-            for (int k = b0 + bs; k < n; ++k) s += u[k] * x[k * INV_COLS + oc];
-            x[(b0 + oi) * INV_COLS + oc] -= s;
-        }
-        for (int t = tid; t < bs * bs; t += INV_BS) D[t / bs][t % bs] = lu[(size_t)(b0 + t / bs) * n + b0 + t % bs];
-        __syncthreads();
-        if (tid < INV_COLS)
-            for (int i = bs - 1; i >= 0; --i) {
-                double s = 0.0;
-                for (int k = i + 1; k < bs; ++k) s += D[i][k] * x[(b0 + k) * INV_COLS + tid];
-                x[(b0 + i) * INV_COLS + tid] = (x[(b0 + i) * INV_COLS + tid] - s) / D[i][i];
-            }
-        __syncthreads();
-    }
-    for (int t = tid; t < n * INV_COLS; t += INV_BS) {
-        const int cc = t / n, i = t % n;
-        if (c0 + cc < n) ainv_t[(size_t)(c0 + cc) * n + i] = x[i * INV_COLS + cc];
-    }
-}
-
-// piv: int32[2n] scratch (permutation, then the panels' pivot rows).  n <= 4096.
-void launch_dense_lu_inverse(int n, double* a, int* piv, double* ainv_t, int* err, hipStream_t s) {
-    int* perm = piv;
-    int* steps = piv + n;
-    const dim3 rest_grid((n + LU_COLS - 1) / LU_COLS);
-#define LU_STEP(NB)                                                                                           \
-    hipLaunchKernelGGL(k_lu_panel<NB>, dim3(1), dim3(LU_BS), 0, s, n, k0, a, perm, steps, err);             \
-    hipLaunchKernelGGL(k_lu_rest<NB>, rest_grid, dim3(256), 0, s, n, k0, a, steps, (const int*)err);        \
-    k0 += NB
-    static_assert(4096 * lu_ldp<4>() <= LU_LDS_DOUBLES && 2048 * lu_ldp<8>() <= LU_LDS_DOUBLES &&
-                      1024 * lu_ldp<16>() <= LU_LDS_DOUBLES, "panel LDS");
-    for (int k0 = 0; k0 < n;) {
-        const int m = n - k0;
-        if (m > 2048) {
-            LU_STEP(4);
-        } else if (m > 1024) {
-            LU_STEP(8);
-        } else {
-            LU_STEP(16);
-        }
-    }
-#undef LU_STEP
-    if (n <= 512)
-        hipLaunchKernelGGL((k_dense_inverse<16, 8192>), dim3((n + 15) / 16), dim3(INV_BS), 0, s, n, a, perm, ainv_t);
-    else if (n <= 1024)
-        hipLaunchKernelGGL((k_dense_inverse<8, 8192>), dim3((n + 7) / 8), dim3(INV_BS), 0, s, n, a, perm, ainv_t);
-    else if (n <= 2048)
-        hipLaunchKernelGGL((k_dense_inverse<8, 16384>), dim3((n + 7) / 8), dim3(INV_BS), 0, s, n, a, perm, ainv_t);
-    else
-        hipLaunchKernelGGL((k_dense_inverse<4, 16384>), dim3((n + 3) / 4), dim3(INV_BS), 0, s, n, a, perm, ainv_t);
 }
 
 }  // namespace amg
