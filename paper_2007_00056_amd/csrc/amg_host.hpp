@@ -222,6 +222,7 @@ struct Level {
     // row; rb = rows per block of the CSR-stream kernels.
     int sched = -1;
     int rb = 256;
+    SliceCode* code = nullptr;  // level 0: column codes of its rows, when they fit
 
     LevelView view() const {
         LevelView w;
@@ -234,6 +235,7 @@ struct Level {
         w.agg = agg;
         w.mem = mem;
         w.lpr = lpr;
+        w.code = code;
         return w;
     }
 };
@@ -362,6 +364,11 @@ struct amg_hier {
     double* part = nullptr;
     int* err = nullptr;
     int stream_min = 262144;  // levels with at least this many rows use CSR-stream kernels
+    // Level 0 from this many rows on is given column codes.  Writing them takes
+    // 5-10 us at 4096-175,000 rows (47 us at 2.1M); a PCG solve to 1e-8 is
+    // 1.30 ms with and 1.33 ms without them at 4096 rows, 3.88 and 4.00 ms at
+    // 110,592.
+    int code_min = 4096;
     // the PCG iteration's reductions are added by their consumer kernels
     // (HEMAMG_FUSE_DOTS=0: separate finish kernels); partial counts pending
     bool fuse_dots = true;

@@ -23,6 +23,11 @@ constexpr int kDenseMaxRows = 4096;     // largest coarsest level (explicit inve
 int pick_lanes_per_row(double avg_row_len);
 
 // ---- setup kernels (k_setup.hip) ------------------------------------------
+// Column codes (amg_stream.hpp) of the rows of a validated matrix, one record
+// per 64 rows; *uncoded += the slices that need more than the record holds.
+struct SliceCode;
+size_t slice_code_bytes(int n);
+void launch_code_slices(int n, const int* rp, const int* ci, SliceCode* code, int* uncoded, hipStream_t s);
 void launch_validate(int n, int64_t nnz, const int* rp, const int* ci, const double* v, double* dinv, int* err,
                      hipStream_t s);
 void launch_dinv(int n, const int* rp, const int* ci, const double* v, double* dinv, int* err, hipStream_t s);
@@ -129,6 +134,7 @@ struct LevelView {
     const int* agg;   // [n] aggregate on level k+1
     const int4* mem;  // [n_{k+1}] members of coarse rows (for k < L)
     int lpr;          // lanes per row
+    const SliceCode* code;  // column codes of its rows, or null
 };
 
 struct Reducer {
@@ -164,6 +170,7 @@ struct VLevel {
     const int4* mem;  // members of level k+1 rows
     int lpr;
     int rb = 256;     // rows per block of the CSR-stream kernels: 128, 256 or 512
+    const SliceCode* code = nullptr;  // column codes of its rows: the CSR-stream kernels then read those
 };
 
 // ---- V-cycle kernels (k_vcycle.hip), T = double or float -------------------
@@ -201,7 +208,6 @@ void vc_dense_apply(int n, const double* ainv_t, const TIN* f, TOUT* x, const Sc
 void launch_cast_f32(int64_t n, const double* a, float* b, hipStream_t s);
 void launch_finish(int nparts, int nv, const Reducer& R, int slot0, int slot1, hipStream_t s);
 
-void launch_spmv(const LevelView& L, const double* x, double* y, hipStream_t s);
 // General smoothing path.
 void launch_jacobi_zero(int n, const double* dinv, const double* f, double w, double* x, hipStream_t s);
 void launch_jacobi(const LevelView& L, const double* f, const double* x, double w, double* xo, hipStream_t s);

@@ -2,8 +2,11 @@
 // matching (Algorithm 2) by prefix sum, the 0/1 Galerkin product P^T A P and
 // aggregate member lists.  The matching itself is in k_hem.hip, the coarsest
 // level's inverse in k_dense.hip.
+#include <climits>
+
 #include "amg_device.hpp"
 #include "amg_internal.hpp"
+#include "amg_stream.hpp"
 
 namespace amg {
 
@@ -57,6 +60,66 @@ __global__ __launch_bounds__(BS) void k_validate(int n, int64_t nnz, const int* 
 void launch_validate(int n, int64_t nnz, const int* rp, const int* ci, const double* v, double* dinv, int* err,
                      hipStream_t s) {
     hipLaunchKernelGGL(k_validate, dim3(blocks_for(n)), dim3(BS), 0, s, n, nnz, rp, ci, v, dinv, err);
+}
+
+// Column codes: a wave takes a slice of 64 rows, a lane a row, whose distances
+// from the diagonal it holds in registers, ascending.  Each step takes the
+// smallest distance of the wave and the lanes that have it.  Bound by the
+// columns' reads.
+__global__ __launch_bounds__(BS) void k_code_slices(int n, const int* __restrict__ rp, const int* __restrict__ ci,
+                                                    SliceCode* __restrict__ code, int* __restrict__ uncoded) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int slices = (n + kWave - 1) / kWave;
+    int bad = 0;
+    for (int sl = blockIdx.x * (BS / kWave) + threadIdx.x / kWave; sl < slices; sl += gridDim.x * (BS / kWave)) {
+        const int row = sl * kWave + lane;
+        const int b = row < n ? rp[row] : 0, len = row < n ? rp[row + 1] - b : 0;
+        int d[kCodeSlots];
+#pragma unroll
+        for (int k = 0; k < kCodeSlots; ++k) d[k] = k < len ? ci[b + k] - row : INT_MAX;
+        unsigned long long mask = 0;
+        int off = 0, cnt = 0;
+#pragma unroll
+        for (int k = 0; k < kCodeSlots; ++k) {
+            // any lane's distance, then one of the smaller ones while there are any:
+            // the lanes of a slice agree on nearly all of them
+            int m = INT_MAX;
+            for (unsigned long long less; (less = __ballot(d[0] < m)) != 0;)
+                m = __builtin_amdgcn_readlane(d[0], __builtin_ctzll(less));
+            const bool mine = m != INT_MAX && d[0] == m;
+            const unsigned long long who = __ballot(mine);
+            if (lane == k) {
+                mask = who;
+                off = who ? m : 0;
+            }
+            cnt += who != 0;
+#pragma unroll
+            for (int j = 0; j + 1 < kCodeSlots; ++j) d[j] = mine ? d[j + 1] : d[j];
+            if (mine) d[kCodeSlots - 1] = INT_MAX;
+        }
+        const bool over = __ballot(len > kCodeSlots || d[0] != INT_MAX) != 0;
+        bad += over;
+        SliceCode* c = code + sl;
+        if (lane < kCodeSlots) {
+            c->mask[lane] = mask;
+            c->off[lane] = off;
+        }
+        if (lane == 0) {
+            const int last = min(sl * kWave + kWave, n);
+            c->first = b;
+            c->total = rp[last] - b;
+            c->last = rp[last] - b - 1;
+            c->cnt = over ? -1 : cnt;
+        }
+    }
+    if (lane == 0 && bad) atomicAdd(uncoded, bad);
+}
+
+size_t slice_code_bytes(int n) { return sizeof(SliceCode) * (size_t)((n + kWave - 1) / kWave); }
+
+void launch_code_slices(int n, const int* rp, const int* ci, SliceCode* code, int* uncoded, hipStream_t s) {
+    const int nb = blocks_for(n);
+    hipLaunchKernelGGL(k_code_slices, dim3(nb < 2048 ? nb : 2048), dim3(BS), 0, s, n, rp, ci, code, uncoded);
 }
 
 __global__ __launch_bounds__(BS) void k_dinv(int n, const int* __restrict__ rp, const int* __restrict__ ci,

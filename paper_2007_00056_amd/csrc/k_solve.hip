@@ -52,8 +52,6 @@ int pick_lanes_per_row(double avg) {
         default: CALL(16); break;   \
     }
 
-using EntAxD = EntAx<double>;
-
 constexpr int FIN_BS = 1024;
 
 __global__ __launch_bounds__(FIN_BS) void k_finish(int nparts, int nv, const double* __restrict__ part,
@@ -76,21 +74,12 @@ __global__ __launch_bounds__(FIN_BS) void k_finish(int nparts, int nv, const dou
     }
 }
 
-// y = A x
-__global__ __launch_bounds__(BS) void k_stream_spmv(int n, const int* __restrict__ rp, EntAxD ent,
-                                                    double* __restrict__ y) {
-    __shared__ double prod[kStreamChunk];
-    for (int b = xcd_block(blockIdx.x, gridDim.x); b * BS < n; b += gridDim.x) {
-        const double s = stream_rows<double>(b * BS, n, rp, ent, prod);
-        const int row = b * BS + threadIdx.x;
-        if (row < n) y[row] = s;
-    }
-}
-
 inline int stream_blocks(int n) { return amg::stream_blocks(n, kRedBlocks); }
 
-void launch_spmv(const LevelView& L, const double* x, double* y, hipStream_t s) {
-    hipLaunchKernelGGL(k_stream_spmv, dim3(stream_blocks(L.n)), dim3(BS), 0, s, L.n, L.rp, EntAxD{L.v, L.ci, x}, y);
+// A row kernel on a level's coded rows where it has them, else on its CSR rows.
+template <bool CODED>
+RowSrc<double, CODED> row_src(const LevelView& L, const double* x) {
+    return RowSrc<double, CODED>{L.code, L.rp, EntAx<double>{L.v, L.ci, x}};
 }
 
 // ---------------------------------------------------------------------------
@@ -190,91 +179,104 @@ inline void finish(int nparts, int nv, const Reducer& R, int slot0, int slot1, h
 }
 
 // r = b - A x, partial (r, r)
-template <class TG>
-__global__ __launch_bounds__(BS) void k_stream_residual(int n, const int* __restrict__ rp, EntAxD ent,
-                                                        const double* __restrict__ b, double* __restrict__ r,
-                                                        const double* __restrict__ dinv, TG* __restrict__ g,
-                                                        double* part) {
+template <class TG, bool CODED>
+__global__ __launch_bounds__(BS) void k_stream_residual(int n, RowSrc<double, CODED> A, const double* __restrict__ b,
+                                                        double* __restrict__ r, const double* __restrict__ dinv,
+                                                        TG* __restrict__ g, double* part) {
     __shared__ double prod[kStreamChunk];
     double acc[1] = {0.0};
-    for (int blk = xcd_block(blockIdx.x, gridDim.x); blk * BS < n; blk += gridDim.x) {
-        const double s = stream_rows<double>(blk * BS, n, rp, ent, prod);
-        const int row = blk * BS + threadIdx.x;
-        if (row < n) {
-            const double ri = b[row] - s;
+    A.template rows<BS>(
+        n, prod, [&](int row) { return make_double2(b[row], dinv[row]); },
+        [&](int row, double s, const double2& in) {
+            const double ri = in.x - s;
             r[row] = ri;
-            if (g) g[row] = TG(dinv[row] * ri);
+            if (g) g[row] = TG(in.y * ri);
             acc[0] += ri * ri;
-        }
-    }
+        });
     block_partials<1, BS>(acc, part);
+}
+
+template <class TG, bool CODED>
+void residual_launch(const LevelView& A, const double* b, const double* x, double* r, void* gout, const Reducer& R,
+                     int g, hipStream_t s) {
+    hipLaunchKernelGGL((k_stream_residual<TG, CODED>), dim3(g), dim3(BS), 0, s, A.n, row_src<CODED>(A, x), b, r,
+                       A.dinv, static_cast<TG*>(gout), R.part);
 }
 
 void launch_residual(const LevelView& A, const double* b, const double* x, double* r, void* gout, bool g32,
                      const Reducer& R, int slot, hipStream_t s) {
     const int g = stream_blocks(A.n);
-    if (g32)
-        hipLaunchKernelGGL(k_stream_residual<float>, dim3(g), dim3(BS), 0, s, A.n, A.rp, EntAxD{A.v, A.ci, x}, b, r,
-                           A.dinv, static_cast<float*>(gout), R.part);
-    else
-        hipLaunchKernelGGL(k_stream_residual<double>, dim3(g), dim3(BS), 0, s, A.n, A.rp, EntAxD{A.v, A.ci, x}, b, r,
-                           A.dinv, static_cast<double*>(gout), R.part);
+    if (A.code) {
+        if (g32) residual_launch<float, true>(A, b, x, r, gout, R, g, s);
+        else residual_launch<double, true>(A, b, x, r, gout, R, g, s);
+    } else {
+        if (g32) residual_launch<float, false>(A, b, x, r, gout, R, g, s);
+        else residual_launch<double, false>(A, b, x, r, gout, R, g, s);
+    }
     finish(g, 1, R, slot, slot, s);
 }
 
 // q = A p, partial (d, q)
-__global__ __launch_bounds__(BS) void k_stream_spmv_dot(int n, const int* __restrict__ rp, EntAxD ent,
-                                                        double* __restrict__ q, const double* __restrict__ d,
-                                                        double* part) {
+template <bool CODED>
+__global__ __launch_bounds__(BS) void k_stream_spmv_dot(int n, RowSrc<double, CODED> A, double* __restrict__ q,
+                                                        const double* __restrict__ d, double* part) {
     __shared__ double prod[kStreamChunk];
     double acc[1] = {0.0};
-    for (int blk = xcd_block(blockIdx.x, gridDim.x); blk * BS < n; blk += gridDim.x) {
-        const double s = stream_rows<double>(blk * BS, n, rp, ent, prod);
-        const int row = blk * BS + threadIdx.x;
-        if (row < n) {
+    A.template rows<BS>(
+        n, prod, [&](int row) { return d[row]; },
+        [&](int row, double s, double di) {
             q[row] = s;
-            acc[0] += d[row] * s;
-        }
-    }
+            acc[0] += di * s;
+        });
     block_partials<1, BS>(acc, part);
+}
+
+void spmv_dot_launch(const LevelView& A, const double* p, double* q, const double* d, double* part, int g,
+                     hipStream_t s) {
+    if (A.code)
+        hipLaunchKernelGGL(k_stream_spmv_dot<true>, dim3(g), dim3(BS), 0, s, A.n, row_src<true>(A, p), q, d, part);
+    else
+        hipLaunchKernelGGL(k_stream_spmv_dot<false>, dim3(g), dim3(BS), 0, s, A.n, row_src<false>(A, p), q, d, part);
 }
 
 void launch_spmv_dot(const LevelView& A, const double* p, double* q, const double* d, const Reducer& R, int slot,
                      hipStream_t s) {
     const int g = stream_blocks(A.n);
-    hipLaunchKernelGGL(k_stream_spmv_dot, dim3(g), dim3(BS), 0, s, A.n, A.rp, EntAxD{A.v, A.ci, p}, q, d, R.part);
+    spmv_dot_launch(A, p, q, d, R.part, g, s);
     finish(g, 1, R, slot, slot, s);
 }
 
 int launch_spmv_dot_parts(const LevelView& A, const double* p, double* q, const double* d, double* part,
                           hipStream_t s) {
     const int g = amg::stream_blocks(A.n, kFusedParts);
-    hipLaunchKernelGGL(k_stream_spmv_dot, dim3(g), dim3(BS), 0, s, A.n, A.rp, EntAxD{A.v, A.ci, p}, q, d, part);
+    spmv_dot_launch(A, p, q, d, part, g, s);
     return g;
 }
 
 // t = A p, partials (t, t) and (t, sv)
-__global__ __launch_bounds__(BS) void k_stream_spmv_dot2(int n, const int* __restrict__ rp, EntAxD ent,
-                                                         double* __restrict__ t, const double* __restrict__ sv,
-                                                         double* part) {
+template <bool CODED>
+__global__ __launch_bounds__(BS) void k_stream_spmv_dot2(int n, RowSrc<double, CODED> A, double* __restrict__ t,
+                                                         const double* __restrict__ sv, double* part) {
     __shared__ double prod[kStreamChunk];
     double acc[2] = {0.0, 0.0};
-    for (int blk = xcd_block(blockIdx.x, gridDim.x); blk * BS < n; blk += gridDim.x) {
-        const double s = stream_rows<double>(blk * BS, n, rp, ent, prod);
-        const int row = blk * BS + threadIdx.x;
-        if (row < n) {
+    A.template rows<BS>(
+        n, prod, [&](int row) { return sv[row]; },
+        [&](int row, double s, double si) {
             t[row] = s;
             acc[0] += s * s;
-            acc[1] += s * sv[row];
-        }
-    }
+            acc[1] += s * si;
+        });
     block_partials<2, BS>(acc, part);
 }
 
 void launch_spmv_dot2(const LevelView& A, const double* p, double* t, const double* sv, const Reducer& R, int slot_tt,
                       int slot_ts, hipStream_t s) {
     const int g = stream_blocks(A.n);
-    hipLaunchKernelGGL(k_stream_spmv_dot2, dim3(g), dim3(BS), 0, s, A.n, A.rp, EntAxD{A.v, A.ci, p}, t, sv, R.part);
+    if (A.code)
+        hipLaunchKernelGGL(k_stream_spmv_dot2<true>, dim3(g), dim3(BS), 0, s, A.n, row_src<true>(A, p), t, sv, R.part);
+    else
+        hipLaunchKernelGGL(k_stream_spmv_dot2<false>, dim3(g), dim3(BS), 0, s, A.n, row_src<false>(A, p), t, sv,
+                           R.part);
     finish(g, 2, R, slot_tt, slot_ts, s);
 }
 

@@ -64,15 +64,12 @@ __device__ __forceinline__ T row_ax(int row, int lane, const int* __restrict__ r
 // Large levels (CSR-stream)
 // ---------------------------------------------------------------------------
 // r = f - w A g : residual after the zero-guess presmoothing sweep
-template <class T, class TIN, int RB>
-__global__ __launch_bounds__(RB) void k_vc_resid(int n, const int* __restrict__ rp, EntAx<T> ent,
-                                                 const TIN* __restrict__ f, T w, T* __restrict__ r) {
+template <class T, class TIN, int RB, bool CODED>
+__global__ __launch_bounds__(RB) void k_vc_resid(int n, RowSrc<T, CODED> A, const TIN* __restrict__ f, T w,
+                                                 T* __restrict__ r) {
     __shared__ T prod[kStreamChunk];
-    for (int b = xcd_block(blockIdx.x, gridDim.x); b * RB < n; b += gridDim.x) {
-        const T s = stream_rows<T, RB>(b * RB, n, rp, ent, prod);
-        const int row = b * RB + threadIdx.x;
-        if (row < n) r[row] = T(f[row]) - w * s;
-    }
+    A.template rows<RB>(
+        n, prod, [&](int row) { return T(f[row]); }, [&](int row, T s, T fi) { r[row] = fi - w * s; });
 }
 
 // f_c = P^T r (members added in ascending order) and g_c = D_c^{-1} f_c
@@ -95,48 +92,56 @@ __global__ __launch_bounds__(BS) void k_vc_restrict(int nc, const int4* __restri
 // in double; MODE 2 scatters z to the finer level's prolongated iterate.
 // GF: g = D^{-1} f is formed here from the level's right-hand side f (in
 // double, whoever wrote g formed exactly this product), so g is not read.
-template <class T, class TOUT, int MODE, int RB, bool GF>
-__global__ __launch_bounds__(RB) void k_vc_post(int n, const int* __restrict__ rp, EntAx<T> ent,
-                                                const T* __restrict__ g, const T* __restrict__ dinv, T w,
-                                                TOUT* __restrict__ z, const double* __restrict__ f, double* part,
-                                                ScatterT<T> sc) {
+template <class T, class TOUT, int MODE, int RB, bool GF, bool CODED>
+__global__ __launch_bounds__(RB) void k_vc_post(int n, RowSrc<T, CODED> A, const T* __restrict__ g,
+                                                const T* __restrict__ dinv, T w, TOUT* __restrict__ z,
+                                                const double* __restrict__ f, double* part, ScatterT<T> sc) {
     __shared__ T prod[kStreamChunk];
     double acc[1] = {0.0};
-    for (int b = xcd_block(blockIdx.x, gridDim.x); b * RB < n; b += gridDim.x) {
-        const T s = stream_rows<T, RB>(b * RB, n, rp, ent, prod);
-        const int row = b * RB + threadIdx.x;
-        if (row < n) {
+    struct In {
+        T x, di, g;
+        double f;
+    };
+    A.template rows<RB>(
+        n, prod,
+        [&](int row) {
+            const double fi = GF || MODE == 1 ? f[row] : 0.0;
             const T di = dinv[row];
-            const T gi = GF ? di * T(f[row]) : g[row];
-            const T zi = ent.x[row] + w * (gi - di * s);
+            return In{A.ent.x[row], di, GF ? di * T(fi) : g[row], fi};
+        },
+        [&](int row, T s, const In& in) {
+            const T zi = in.x + w * (in.g - in.di * s);
             z[row] = TOUT(zi);
-            if (MODE == 1) acc[0] += f[row] * double(zi);
+            if (MODE == 1) acc[0] += in.f * double(zi);
             if (MODE == 2) sc(row, zi);
-        }
-    }
+        });
     if (MODE == 1) block_partials<1, RB>(acc, part);
 }
 
-// The launchers pick the rows-per-block instantiation from the level.
-#define AMG_DISPATCH_RB(rb, CALL) \
-    switch (rb) {                 \
-        case 128: CALL(128); break; \
-        case 512: CALL(512); break; \
-        default: CALL(256); break;  \
-    }
+// The launchers pick the instantiation from the level: coded rows where it has
+// them (256 rows per block), else CSR rows with the level's rows per block.
+template <bool CODED, class T>
+RowSrc<T, CODED> row_src(const VLevel<T>& L, const T* x) {
+    return RowSrc<T, CODED>{L.code, L.rp, EntAx<T>{L.v, L.ci, x}};
+}
 
 inline int rb_blocks(int n, int rb) {
     const int b = (n + rb - 1) / rb;
     return b < kRedBlocks ? (b < 1 ? 1 : b) : kRedBlocks;
 }
 
+template <int RB, bool CODED, class T, class TIN>
+void resid_launch(const VLevel<T>& L, const TIN* f, const T* g, T w, T* r, hipStream_t s) {
+    hipLaunchKernelGGL((k_vc_resid<T, TIN, RB, CODED>), dim3(rb_blocks(L.n, RB)), dim3(RB), 0, s, L.n,
+                       row_src<CODED>(L, g), f, w, r);
+}
+
 template <class T, class TIN>
 void vc_stream_resid(const VLevel<T>& L, const TIN* f, const T* g, T w, T* r, hipStream_t s) {
-#define CALL(RB)                                                                                                \
-    hipLaunchKernelGGL((k_vc_resid<T, TIN, RB>), dim3(rb_blocks(L.n, RB)), dim3(RB), 0, s, L.n, L.rp,           \
-                       EntAx<T>{L.v, L.ci, g}, f, w, r)
-    AMG_DISPATCH_RB(L.rb, CALL)
-#undef CALL
+    if (L.code) resid_launch<256, true>(L, f, g, w, r, s);
+    else if (L.rb == 128) resid_launch<128, false>(L, f, g, w, r, s);
+    else if (L.rb == 512) resid_launch<512, false>(L, f, g, w, r, s);
+    else resid_launch<256, false>(L, f, g, w, r, s);
 }
 
 template <class T>
@@ -144,51 +149,49 @@ void vc_restrict(int nc, const int4* mem, const T* r, const T* dinv_c, T* fc, T*
     hipLaunchKernelGGL(k_vc_restrict<T>, dim3(level_blocks(nc, 1)), dim3(BS), 0, s, nc, mem, r, dinv_c, fc, gc);
 }
 
-template <class T, class TOUT, int MODE, int RB, bool GF>
-void post_launch(int gsz, hipStream_t s, hipEvent_t t0, hipEvent_t t1, int n, const int* rp, const EntAx<T>& ent,
-                 const T* g, const T* dinv, T w, TOUT* z, const double* f, double* part, const ScatterT<T>& sc) {
+template <class T, class TOUT, int MODE, bool GF, int RB, bool CODED>
+int post_launch(const VLevel<T>& L, const T* xp, const T* g, T w, TOUT* z, const double* f, double* part,
+                const ScatterT<T>& sc, int cap, hipStream_t s, hipEvent_t t0, hipEvent_t t1) {
+    const int nb = rb_blocks(L.n, RB), gsz = nb < cap ? nb : cap;
+    const RowSrc<T, CODED> A = row_src<CODED>(L, xp);
     // with t0/t1 the dispatch itself records the kernel's start and end
     if (t0)
-        hipExtLaunchKernelGGL((k_vc_post<T, TOUT, MODE, RB, GF>), dim3(gsz), dim3(RB), 0, s, t0, t1, 0, n, rp, ent, g,
-                              dinv, w, z, f, part, sc);
+        hipExtLaunchKernelGGL((k_vc_post<T, TOUT, MODE, RB, GF, CODED>), dim3(gsz), dim3(RB), 0, s, t0, t1, 0, L.n, A,
+                              g, L.dinv, w, z, f, part, sc);
     else
-        hipLaunchKernelGGL((k_vc_post<T, TOUT, MODE, RB, GF>), dim3(gsz), dim3(RB), 0, s, n, rp, ent, g, dinv, w, z, f,
-                           part, sc);
+        hipLaunchKernelGGL((k_vc_post<T, TOUT, MODE, RB, GF, CODED>), dim3(gsz), dim3(RB), 0, s, L.n, A, g, L.dinv, w,
+                           z, f, part, sc);
+    return gsz;
 }
 
 template <class T, class TOUT, int MODE, bool GF>
-int post_rb(int rb, int n, hipStream_t s, hipEvent_t t0, hipEvent_t t1, const int* rp, const EntAx<T>& ent,
-            const T* g, const T* dinv, T w, TOUT* z, const double* f, double* part, const ScatterT<T>& sc,
-            int cap = kRedBlocks) {
-    const int gsz = rb_blocks(n, rb) < cap ? rb_blocks(n, rb) : cap;
-    if (rb == 128) post_launch<T, TOUT, MODE, 128, GF>(gsz, s, t0, t1, n, rp, ent, g, dinv, w, z, f, part, sc);
-    else if (rb == 512) post_launch<T, TOUT, MODE, 512, GF>(gsz, s, t0, t1, n, rp, ent, g, dinv, w, z, f, part, sc);
-    else post_launch<T, TOUT, MODE, 256, GF>(gsz, s, t0, t1, n, rp, ent, g, dinv, w, z, f, part, sc);
-    return gsz;
+int post_rows(const VLevel<T>& L, const T* xp, const T* g, T w, TOUT* z, const double* f, double* part,
+              const ScatterT<T>& sc, hipStream_t s, hipEvent_t t0, hipEvent_t t1, int cap = kRedBlocks) {
+    if (L.code) return post_launch<T, TOUT, MODE, GF, 256, true>(L, xp, g, w, z, f, part, sc, cap, s, t0, t1);
+    if (L.rb == 128) return post_launch<T, TOUT, MODE, GF, 128, false>(L, xp, g, w, z, f, part, sc, cap, s, t0, t1);
+    if (L.rb == 512) return post_launch<T, TOUT, MODE, GF, 512, false>(L, xp, g, w, z, f, part, sc, cap, s, t0, t1);
+    return post_launch<T, TOUT, MODE, GF, 256, false>(L, xp, g, w, z, f, part, sc, cap, s, t0, t1);
 }
 
 template <class T, class TOUT>
 int vc_stream_post(const VLevel<T>& L, const T* xp, const T* g, T w, TOUT* z, const double* f, const Reducer* R,
                    int slot, const ScatterT<T>* sc, hipStream_t s, hipEvent_t t0, hipEvent_t t1) {
-    const int rb = L.rb == 128 || L.rb == 512 ? L.rb : 256;
-    const EntAx<T> ent{L.v, L.ci, xp};
     const ScatterT<T> none{nullptr, nullptr, nullptr, T(0)};
     // a double level 0 forms g = D^{-1} f itself instead of reading it
     constexpr bool kCanGF = std::is_same<T, double>::value && std::is_same<TOUT, double>::value;
     const bool gf = kCanGF && f != nullptr;
     if (R) {
         const int cap = slot == kPartialsOnly ? kFusedParts : kRedBlocks;
-        const int np =
-            gf ? post_rb<T, TOUT, 1, kCanGF>(rb, L.n, s, t0, t1, L.rp, ent, g, L.dinv, w, z, f, R->part, none, cap)
-               : post_rb<T, TOUT, 1, false>(rb, L.n, s, t0, t1, L.rp, ent, g, L.dinv, w, z, f, R->part, none, cap);
+        const int np = gf ? post_rows<T, TOUT, 1, kCanGF>(L, xp, g, w, z, f, R->part, none, s, t0, t1, cap)
+                          : post_rows<T, TOUT, 1, false>(L, xp, g, w, z, f, R->part, none, s, t0, t1, cap);
         if (slot == kPartialsOnly) return np;
         launch_finish(np, 1, *R, slot, slot, s);
     } else if (sc) {
-        post_rb<T, TOUT, 2, false>(rb, L.n, s, t0, t1, L.rp, ent, g, L.dinv, w, z, nullptr, nullptr, *sc);
+        post_rows<T, TOUT, 2, false>(L, xp, g, w, z, nullptr, nullptr, *sc, s, t0, t1);
     } else if (gf) {
-        post_rb<T, TOUT, 0, kCanGF>(rb, L.n, s, t0, t1, L.rp, ent, g, L.dinv, w, z, f, nullptr, none);
+        post_rows<T, TOUT, 0, kCanGF>(L, xp, g, w, z, f, nullptr, none, s, t0, t1);
     } else {
-        post_rb<T, TOUT, 0, false>(rb, L.n, s, t0, t1, L.rp, ent, g, L.dinv, w, z, nullptr, nullptr, none);
+        post_rows<T, TOUT, 0, false>(L, xp, g, w, z, nullptr, nullptr, none, s, t0, t1);
     }
     return 0;
 }
