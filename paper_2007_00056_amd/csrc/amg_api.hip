@@ -589,6 +589,54 @@ const float* dinv_of<float>(const Level& L) {
     return L.dinv32;
 }
 
+template <class T>
+TailArgs<T>& tail_of(amg_hier* h);
+template <>
+TailArgs<double>& tail_of<double>(amg_hier* h) {
+    return h->tail64;
+}
+template <>
+TailArgs<float>& tail_of<float>(amg_hier* h) {
+    return h->tail32;
+}
+
+// Finds the first level from which on the cycle fits in one workgroup and
+// packs its operators.
+template <class T>
+void build_tail(amg_hier* h, hipStream_t s) {
+    const int L = (int)h->lev.size() - 1;
+    TailArgs<T>& A = tail_of<T>(h);
+    std::vector<int> n, lpr;
+    std::vector<int64_t> nnz;
+    for (const Level& l : h->lev) {
+        n.push_back(l.n);
+        lpr.push_back(l.lpr);
+        nnz.push_back(l.nnz);
+    }
+    const char* e = getenv("HEMAMG_TAIL");
+    const int most = e ? atoi(e) : 1 << 30;  // tuning sweeps: LDS bytes
+    TailPack<T> K;
+    int k = 1;
+    for (; k < L; ++k) {
+        h->tail_lds = tail_layout<T>(&n[k], &nnz[k], &lpr[k], L - k, A, K.lev);
+        if (h->tail_lds > 0 && h->tail_lds <= most) break;
+    }
+    if (k >= L || !tail_prepare()) return;
+    h->tail = k;
+    K.blob = h->pool.get<char>(16 * (size_t)A.words);
+    for (int l = k; l < L; ++l) {
+        const VLevel<T> V = vlevel<T>(h->lev[l]);
+        K.src[l - k] = TailSrc<T>{V.rp, V.ci, V.v, V.dinv, V.mem, (int)nnz[l]};
+    }
+    launch_tail_pack<T>(K, L - k, s);
+    HIPCHK(hipGetLastError());
+    A.blob = reinterpret_cast<const uint4*>(K.blob);
+    A.ainv = h->ainv_t;
+    A.f = static_cast<const T*>(h->lev[k].f);
+    A.g = static_cast<const T*>(h->lev[k].g);
+    A.w = T(h->p.omega);
+}
+
 // Algorithm 1 with one pre- and one post-sweep, in value type T.  r and z are
 // double; g0 (T), if given, already holds D^{-1} r.  dot_slot >= 0 also stores
 // (r, z) there.  part 0 runs the whole cycle; part 1 everything but the
@@ -637,8 +685,8 @@ void run_vcycle_t(amg_hier* h, const double* r, double* z, hipStream_t s, const 
         }
         return;
     }
-    // down-sweep
-    for (int k = 0; k < L; ++k) {
+    const int down = h->tail ? h->tail : L;  // levels the level kernels take
+    for (int k = 0; k < down; ++k) {
         const Level& Lk = h->lev[k];
         const Level& Lc = h->lev[k + 1];
         const VLevel<T> V = vlevel<T>(Lk);
@@ -659,11 +707,12 @@ void run_vcycle_t(amg_hier* h, const double* r, double* z, hipStream_t s, const 
     // coarsest, then the up-sweep: each level's result is scattered to the
     // finer level's prolongated iterate, which that level's postsmoothing reads
     {
-        const ScatterT<T> sc = scatter_to(L - 1);
-        vc_dense_apply<T, T, T>(h->n_coarse, h->ainv_t, vec(h->lev[L].f), vec(h->lev[L].x), &sc, s);
+        const ScatterT<T> sc = scatter_to(down - 1);
+        if (h->tail) vc_tail<T>(tail_of<T>(h), h->tail_lds, sc, s);
+        else vc_dense_apply<T, T, T>(h->n_coarse, h->ainv_t, vec(h->lev[L].f), vec(h->lev[L].x), &sc, s);
     }
     bool dot_done = false;
-    for (int k = L - 1; k >= (part == 1 ? 1 : 0); --k) {
+    for (int k = down - 1; k >= (part == 1 ? 1 : 0); --k) {
         const Level& Lk = h->lev[k];
         const VLevel<T> V = vlevel<T>(Lk);
         if (k > 0) {
@@ -1279,6 +1328,8 @@ void setup_impl(const amg_csr* Ain, const amg_params* pin, const amg_allocator* 
             launch_cast_f32(L.n, L.dinv, L.dinv32, s);
         }
     }
+    if (fused && h->prec32) build_tail<float>(h.get(), s);
+    else if (fused) build_tail<double>(h.get(), s);
     h->g0 = P.get<char>(esz * h->lev[0].n);
     h->S = P.get<double>(S_COUNT);
     h->part = P.get<double>(2 * (size_t)kRedBlocks);

@@ -369,6 +369,11 @@ struct amg_hier {
     // 1.30 ms with and 1.33 ms without them at 4096 rows, 3.88 and 4.00 ms at
     // 110,592.
     int code_min = 4096;
+    // Levels tail .. coarsest run in one workgroup (0: none do).
+    int tail = 0;
+    int tail_lds = 0;
+    amg::TailArgs<double> tail64;
+    amg::TailArgs<float> tail32;
     // the PCG iteration's reductions are added by their consumer kernels
     // (HEMAMG_FUSE_DOTS=0: separate finish kernels); partial counts pending
     bool fuse_dots = true;

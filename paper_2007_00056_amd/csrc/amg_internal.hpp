@@ -204,6 +204,58 @@ void vc_scale_dinv(int n, const double* dinv, const double* f, T* g, hipStream_t
 template <class T, class TIN, class TOUT>
 void vc_dense_apply(int n, const double* ainv_t, const TIN* f, TOUT* x, const ScatterT<T>* sc, hipStream_t s);
 
+// The small levels in one workgroup (k_tail.hip).  Level l = 0 .. nl - 1
+// smooths, level nl is the coarsest; offsets are bytes in LDS, where the
+// packed block of the levels' operators comes first, headed by their records.
+constexpr int kTailLevels = 16;
+constexpr int kTailDense = 256;          // most coarsest rows: one CU reads the inverse, 8 bytes a square
+constexpr uint16_t kTailNone = 0xffff;   // no such member
+struct alignas(16) TailLevel {
+    int n, nc;                      // rows, rows of the next level
+    int v, dinv, ci, rec;           // operator, its rows by member of the next level's rows
+    int g, a;                       // D^{-1} f, then z; f, then xp
+    int cg, ca, cdinv;              // g, a and dinv of the next level
+    int lpr_log;                    // log2 of the lanes per row (1 or 2)
+    int pad[4];
+};
+static_assert(sizeof(TailLevel) == 64, "four 16-byte words");
+template <class T>
+struct TailArgs {
+    const uint4* blob;
+    const double* ainv;  // coarsest inverse, column-major
+    const T* f;          // right-hand side of level 0 and g = D^{-1} f
+    const T* g;
+    T w;
+    int words;           // 16-byte words of the block
+    int nl, n0, m;       // smoothing levels; finest and coarsest rows
+    int g0, a0, gm, am;  // their vectors
+    int dense_log, part; // log2 of the threads per column of the coarsest solve; its partial sums
+};
+template <class T>
+struct TailSrc {
+    const int* rp;
+    const int* ci;
+    const T* v;
+    const T* dinv;
+    const int4* mem;
+    int nnz;
+};
+template <class T>
+struct TailPack {
+    char* blob;
+    TailSrc<T> src[kTailLevels];
+    TailLevel lev[kTailLevels];
+};
+// n[0 .. nl], nnz and lanes per row [0 .. nl - 1]: the LDS bytes of the cycle on these levels, or
+// 0 when it does not fit; fills lev[0 .. nl - 1] and A (not its pointers).
+template <class T>
+int tail_layout(const int* n, const int64_t* nnz, const int* lpr, int nl, TailArgs<T>& A, TailLevel* lev);
+template <class T>
+void launch_tail_pack(const TailPack<T>& K, int nl, hipStream_t s);
+template <class T>
+void vc_tail(const TailArgs<T>& A, int lds, const ScatterT<T>& sc, hipStream_t s);
+bool tail_prepare();  // whether the device takes the tail kernels
+
 // S[slot0] (and S[slot1] when nv = 2) = fixed-order sums of the partials.
 void launch_cast_f32(int64_t n, const double* a, float* b, hipStream_t s);
 void launch_finish(int nparts, int nv, const Reducer& R, int slot0, int slot1, hipStream_t s);
