@@ -560,23 +560,34 @@ void timed_end(amg_hier* h, int cls, hipStream_t s, bool recorded = false) {
     }
 }
 
-// Whether level L runs the CSR-stream kernels (else the lane-group kernels).
-inline bool streamed(const amg_hier* h, const Level& L) { return L.sched < 0 ? L.n >= h->stream_min : L.sched == 0; }
+// The order of additions of the CSR-stream kernels on level L, or -1 where the
+// lane-group kernels run.  A double level 0 with column codes reads those, in
+// entry order.
+inline int stream_order(const amg_hier* h, const Level& L) {
+    if (L.sched >= 0) return L.sched == 0 ? 0 : -1;
+    if (L.n >= h->stream_min) return 0;
+    if (L.n < h->mid_min) return -1;
+    if (L.code && !h->prec32) return 0;
+    return L.lpr == 4 || L.lpr == 8 ? L.lpr : -1;
+}
+inline bool streamed(const amg_hier* h, const Level& L) { return stream_order(h, L) >= 0; }
 
 // Whether the level-0 postsmoothing can run as a separate step (part 2).
 bool vcycle_splits(const amg_hier* h) { return h->lev.size() > 1 && h->p.pre == 1 && h->p.post == 1; }
 
 template <class T>
-VLevel<T> vlevel(const Level& L);
+VLevel<T> vlevel(const amg_hier* h, const Level& L);
 template <>
-VLevel<double> vlevel<double>(const Level& L) {
+VLevel<double> vlevel<double>(const amg_hier* h, const Level& L) {
+    const int order = stream_order(h, L);
     return VLevel<double>{L.n, L.rp, L.ci, L.v, L.dinv, L.mem, L.sched > 0 ? L.sched : L.lpr, L.rb,
-                          L.code};
+                          order == 0 ? L.code : nullptr, order};
 }
 template <>
-VLevel<float> vlevel<float>(const Level& L) {
+VLevel<float> vlevel<float>(const amg_hier* h, const Level& L) {
+    const int order = stream_order(h, L);
     return VLevel<float>{L.n, L.rp, L.ci, L.v32, L.dinv32, L.mem, L.sched > 0 ? L.sched : L.lpr, L.rb,
-                          L.code};
+                         order == 0 ? L.code : nullptr, order};
 }
 template <class T>
 const T* dinv_of(const Level& L);
@@ -625,7 +636,7 @@ void build_tail(amg_hier* h, hipStream_t s) {
     h->tail = k;
     K.blob = h->pool.get<char>(16 * (size_t)A.words);
     for (int l = k; l < L; ++l) {
-        const VLevel<T> V = vlevel<T>(h->lev[l]);
+        const VLevel<T> V = vlevel<T>(h, h->lev[l]);
         K.src[l - k] = TailSrc<T>{V.rp, V.ci, V.v, V.dinv, V.mem, (int)nnz[l]};
     }
     launch_tail_pack<T>(K, L - k, s);
@@ -663,7 +674,7 @@ void run_vcycle_t(amg_hier* h, const double* r, double* z, hipStream_t s, const 
         return ScatterT<T>{h->lev[k].mem, gk(k), vec(h->lev[k].xp), w};
     };
     if (part == 2) {  // level-0 postsmoothing (+ (r, z)) only
-        const VLevel<T> V = vlevel<T>(L0);
+        const VLevel<T> V = vlevel<T>(h, L0);
         h->rz_np = 0;
         if (streamed(h, L0)) {
             hipEvent_t t0, t1;
@@ -689,7 +700,7 @@ void run_vcycle_t(amg_hier* h, const double* r, double* z, hipStream_t s, const 
     for (int k = 0; k < down; ++k) {
         const Level& Lk = h->lev[k];
         const Level& Lc = h->lev[k + 1];
-        const VLevel<T> V = vlevel<T>(Lk);
+        const VLevel<T> V = vlevel<T>(h, Lk);
         T* fc = vec(Lc.f);
         T* gc = vec(Lc.g);
         if (k == 0) timed_begin(h, 1, s);
@@ -714,7 +725,7 @@ void run_vcycle_t(amg_hier* h, const double* r, double* z, hipStream_t s, const 
     bool dot_done = false;
     for (int k = down - 1; k >= (part == 1 ? 1 : 0); --k) {
         const Level& Lk = h->lev[k];
-        const VLevel<T> V = vlevel<T>(Lk);
+        const VLevel<T> V = vlevel<T>(h, Lk);
         if (k > 0) {
             const ScatterT<T> sc = scatter_to(k - 1);
             if (streamed(h, Lk))
@@ -1307,7 +1318,8 @@ void setup_impl(const amg_csr* Ain, const amg_params* pin, const amg_allocator* 
     const bool fused = p.pre == 1 && p.post == 1;
     h->prec32 = p.precond_fp32 != 0;
     const size_t esz = h->prec32 ? sizeof(float) : sizeof(double);
-    if (const char* e = getenv("HEMAMG_STREAM_MIN")) h->stream_min = atoi(e);  // tuning sweeps
+    if (const char* e = getenv("HEMAMG_STREAM_MIN")) h->stream_min = atoi(e);  // tuning sweeps and tests
+    if (const char* e = getenv("HEMAMG_MID_MIN")) h->mid_min = atoi(e);
     if (const char* e = getenv("HEMAMG_RB"))
         for (Level& L : h->lev) L.rb = atoi(e);
     if (const char* e = getenv("HEMAMG_GRAPHS")) h->use_graphs = atoi(e) != 0;
@@ -1365,7 +1377,7 @@ void tune_level_steps(amg_hier* h, int k, hipStream_t s) {
     auto vec = [](void* p) { return static_cast<T*>(p); };
     Level& Lk = h->lev[k];
     const Level& Lc = h->lev[k + 1];
-    const VLevel<T> V = vlevel<T>(Lk);
+    const VLevel<T> V = vlevel<T>(h, Lk);
     const T* g = k == 0 ? vec(h->g0) : vec(Lk.g);
     T* fk = k == 0 ? nullptr : vec(Lk.f);
     if (streamed(h, Lk)) {

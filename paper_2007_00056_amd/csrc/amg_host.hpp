@@ -364,6 +364,14 @@ struct amg_hier {
     double* part = nullptr;
     int* err = nullptr;
     int stream_min = 262144;  // levels with at least this many rows use CSR-stream kernels
+    // Levels below that and from this many rows on use the CSR-stream kernels
+    // in the lane-group kernels' order of additions.  64 rows a wave in place of
+    // 8 or 16 take fewer rounds of dependent loads: a V-cycle whose level 1 has
+    // 218,265 rows of 11.3 entries (97 x 101 x 89, single precision) takes
+    // 103.5 us (118.2 with lane groups there), one with 216,611 rows on a double
+    // level 0 72.2 (82.0).  Levels of 54,000 to 64,000 rows gain nothing (73.2
+    // against 72.2), smaller ones lose the fused restriction.
+    int mid_min = 65536;
     // Level 0 from this many rows on is given column codes.  Writing them takes
     // 5-10 us at 4096-175,000 rows (47 us at 2.1M); a PCG solve to 1e-8 is
     // 1.30 ms with and 1.33 ms without them at 4096 rows, 3.88 and 4.00 ms at

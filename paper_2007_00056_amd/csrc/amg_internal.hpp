@@ -171,6 +171,7 @@ struct VLevel {
     int lpr;
     int rb = 256;     // rows per block of the CSR-stream kernels: 128, 256 or 512
     const SliceCode* code = nullptr;  // column codes of its rows: the CSR-stream kernels then read those
+    int order = 0;    // CSR-stream kernels: 4 or 8 adds as the lane-group kernels with that many lanes
 };
 
 // ---- V-cycle kernels (k_vcycle.hip), T = double or float -------------------

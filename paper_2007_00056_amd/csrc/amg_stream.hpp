@@ -1,10 +1,5 @@
-// CSR-stream building block shared by the level and Krylov kernels.
-//
-// A block of RB threads (256 by default) owns RB consecutive rows.  It reads their contiguous
-// entry range with coalesced, independent loads (values, columns and the
-// gathered vector), stages the products in LDS, and then each thread adds
-// its own row's products in entry order.  Entries are processed in LDS chunks,
-// so rows of any length are handled.
+// Row sums of CSR matrices, shared by the level and Krylov kernels: a wave owns
+// 64 consecutive rows, a lane one of them.
 #pragma once
 
 #include "amg_device.hpp"
@@ -12,36 +7,125 @@
 namespace amg {
 
 constexpr int kStreamBS = 256;
-constexpr int kStreamChunk = 2048;  // products per LDS chunk
+// entries a wave stages at a time: what its registers hold with enough waves on
+// the CU (all of a chunk's loads are in flight together)
+template <class T>
+constexpr int kWaveChunk = sizeof(T) == 8 ? 512 : 1024;
 
 template <class T>
-struct EntAx {  // a_ij x_j
+struct EntAx {  // the entries of A and the x they are applied to
     const T* __restrict__ v;
     const int* __restrict__ ci;
     const T* __restrict__ x;
     __device__ __forceinline__ T operator()(int e) const { return v[e] * x[ci[e]]; }
 };
 
-// RB rows per block (the block has RB threads); a row's sum does not depend
-// on RB.
-template <class T, int RB = kStreamBS, class Ent>
-__device__ __forceinline__ T stream_rows(int r0, int n, const int* __restrict__ rp, const Ent& ent, T* prod) {
-    constexpr int BS = RB;
-    const int r1 = min(r0 + BS, n);
-    const int e0 = rp[r0], e1 = rp[r1];
-    const int row = r0 + threadIdx.x;
-    const int rb = row < r1 ? rp[row] : 0, re = row < r1 ? rp[row + 1] : 0;
-    T acc = T(0);
-    for (int c0 = e0; c0 < e1; c0 += kStreamChunk) {
-        const int c1 = min(c0 + kStreamChunk, e1);
-#pragma unroll 4
-        for (int e = c0 + threadIdx.x; e < c1; e += BS) prod[e - c0] = ent(e);
-        __syncthreads();
-        const int lo = max(rb, c0), hi = min(re, c1);
-        for (int e = lo; e < hi; ++e) acc += prod[e - c0];
-        __syncthreads();
+// ---------------------------------------------------------------------------
+// CSR rows.  The entries of a wave's rows are contiguous: they are read with
+// coalesced loads, all values and columns of a chunk in flight together and
+// then all of its x, and staged in the wave's own part of LDS, from where each
+// lane takes its row's.  No barrier, and one chain of three loads a chunk.
+//
+// ORDER 0: products, rounded, are added in entry order.  ORDER 4 and 8: the
+// order of the lane-group kernels with that many lanes a row, one fused sum
+// for each lane over every 4th (8th) entry, the sums added as a butterfly adds
+// them; such a row is the same bit for bit in either kernel.
+//
+// Bound by memory on large levels (1.02M rows of 11.5 entries in single
+// precision: residual 30.6 us for 106 MB; 33.6 when blocks of 256 rows shared
+// the staging with barriers), by the chain of loads on smaller ones.
+// ---------------------------------------------------------------------------
+template <int K, int ORDER, class T>
+__device__ __forceinline__ void stage_chunk(const EntAx<T>& ent, int c0, int last, T* lds) {
+    const int lane = threadIdx.x & (kWave - 1);
+    T a[K], x[K];
+    int c[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int e = min(c0 + k * kWave + lane, last);
+        a[k] = ent.v[e];
+        c[k] = ent.ci[e];
     }
-    return acc;
+#pragma unroll
+    for (int k = 0; k < K; ++k) x[k] = ent.x[c[k]];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        if (ORDER == 0) {
+            lds[k * kWave + lane] = a[k] * x[k];
+        } else {
+            lds[k * kWave + lane] = a[k];
+            lds[kWaveChunk<T> + k * kWave + lane] = x[k];
+        }
+    }
+}
+
+// LDS values a wave of the kernel needs
+template <class T, int ORDER>
+constexpr int kWaveLds = ORDER == 0 ? kWaveChunk<T> : 2 * kWaveChunk<T>;
+
+// Sums of rows row0 .. row0 + 63 below n (a lane each); lds is this wave's.
+template <int ORDER = 0, class T>
+__device__ __forceinline__ T wave_rows(int row0, int n, const int* __restrict__ rp, const EntAx<T>& ent, T* lds) {
+    static_assert(ORDER == 0 || ORDER == 4 || ORDER == 8, "");
+    if (row0 >= n) return T(0);
+    const int row = row0 + (int)(threadIdx.x & (kWave - 1));
+    const int rb = rp[min(row, n)], re = rp[min(row + 1, n)];
+    const int e0 = __builtin_amdgcn_readfirstlane(rb), e1 = __builtin_amdgcn_readlane(re, kWave - 1);
+    constexpr int NS = ORDER == 0 ? 1 : ORDER;
+    T s[NS];
+#pragma unroll
+    for (int u = 0; u < NS; ++u) s[u] = T(0);
+    for (int c0 = e0; c0 < e1; c0 += kWaveChunk<T>) {
+        const int cnt = min(kWaveChunk<T>, e1 - c0), last = c0 + cnt - 1;
+        if (cnt <= 5 * kWave) stage_chunk<5, ORDER>(ent, c0, last, lds);
+        else if (cnt <= 8 * kWave) stage_chunk<8, ORDER>(ent, c0, last, lds);
+        else if constexpr (kWaveChunk<T> > 8 * kWave) {
+            if (cnt <= 12 * kWave) stage_chunk<12, ORDER>(ent, c0, last, lds);
+            else stage_chunk<16, ORDER>(ent, c0, last, lds);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const int lo = max(rb, c0) - c0, hi = min(re, last + 1) - c0;
+        if (ORDER == 0) {
+            for (int e = lo; e < hi; e += 4) {
+                T p[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) p[u] = lds[min(e + u, hi - 1)];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const T t = s[0] + p[u];
+                    s[0] = e + u < hi ? t : s[0];
+                }
+            }
+        } else if (lo < hi) {
+            const int b = rb - c0;  // below 0 when the row began in the last chunk
+            for (int t = b + (lo - b) / NS * NS; t < hi; t += NS) {
+                T a[NS], x[NS];
+#pragma unroll
+                for (int u = 0; u < NS; ++u) {
+                    const int e = min(max(t + u, lo), hi - 1);
+                    a[u] = lds[e];
+                    x[u] = lds[kWaveChunk<T> + e];
+                }
+#pragma unroll
+                for (int u = 0; u < NS; ++u) {
+                    const T q = fma(a[u], x[u], s[u]);
+                    s[u] = t + u >= lo && t + u < hi ? q : s[u];
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    if constexpr (ORDER == 8) return ((s[0] + s[4]) + (s[2] + s[6])) + ((s[1] + s[5]) + (s[3] + s[7]));
+    else if constexpr (ORDER == 4) return (s[0] + s[2]) + (s[1] + s[3]);
+    else return s[0];
+}
+
+// Sums of RB consecutive rows from r0 on by a block of RB threads;
+// lds: RB / 64 * kWaveLds<T, ORDER> values.
+template <class T, int RB = kStreamBS, int ORDER = 0>
+__device__ __forceinline__ T stream_rows(int r0, int n, const int* __restrict__ rp, const EntAx<T>& ent, T* lds) {
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    return wave_rows<ORDER>(r0 + w * kWave, n, rp, ent, lds + w * kWaveLds<T, ORDER>);
 }
 
 // ---------------------------------------------------------------------------
@@ -161,9 +245,14 @@ __device__ __forceinline__ T coded_row(const SliceCode& c, int row, int n, const
 }
 
 // What a row kernel reads its matrix rows from: a CSR matrix with the x it is
-// applied to, and the codes of its rows when CODED.
-template <class T, bool CODED>
+// applied to, and the codes of its rows when KIND is kCoded; else KIND is the
+// order of additions.
+constexpr int kCoded = 1;
+template <class T, int KIND>
 struct RowSrc {
+    // LDS values of a block of RB threads
+    template <int RB>
+    static constexpr int lds = RB / kWave * (KIND == kCoded ? kCodeSlots * kWave : kWaveLds<T, KIND == kCoded ? 0 : KIND>);
     const SliceCode* code;
     const int* __restrict__ rp;
     EntAx<T> ent;
@@ -173,14 +262,13 @@ struct RowSrc {
     // part of the rows, also where its blocks make several steps: x lines that
     // neighbouring rows share are read into one L2.
     template <int RB, class Pre, class Body>
-    __device__ __forceinline__ void rows(int n, T* prod, Pre pre, Body body) const {
+    __device__ __forceinline__ void rows(int n, T* lds, Pre pre, Body body) const {
         const int nb = (n + RB - 1) / RB;
         const int xcd = blockIdx.x % kNumXcd, per = nb / kNumXcd, rem = nb % kNumXcd;
         const int end = (xcd + 1) * per + min(xcd + 1, rem);
         const int step = gridDim.x / kNumXcd + (xcd < (int)gridDim.x % kNumXcd);  // blocks on this XCD
         int b = xcd * per + min(xcd, rem) + blockIdx.x / kNumXcd;
-        if constexpr (CODED) {
-            static_assert(RB * kCodeSlots <= kStreamChunk, "a wave's part of prod");
+        if constexpr (KIND == kCoded) {
             const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
             const int last = (n - 1) / kWave;
             SliceCode c = load_code(code, min(b * (RB / kWave) + w, last));
@@ -190,7 +278,7 @@ struct RowSrc {
                 const auto in = pre(min(row, n - 1));
                 // the next slice's record arrives during this slice's loads
                 SliceCode next = load_code(code, min((b + step) * (RB / kWave) + w, last));
-                const T s = coded_row<T>(c, row, n, rp, ent, prod + w * kCodeSlots * kWave);
+                const T s = coded_row<T>(c, row, n, rp, ent, lds + w * kCodeSlots * kWave);
                 // every load has been used: said here, the loop has no wait for
                 // the last slice's store at its head
                 __builtin_amdgcn_s_waitcnt(0x0f70);
@@ -202,7 +290,7 @@ struct RowSrc {
             for (; b < end; b += step) {
                 const int row = b * RB + threadIdx.x;
                 const auto in = pre(min(row, n - 1));
-                const T s = stream_rows<T, RB>(b * RB, n, rp, ent, prod);
+                const T s = stream_rows<T, RB, KIND>(b * RB, n, rp, ent, lds);
                 if (row < n) body(row, s, in);
             }
         }

@@ -30,14 +30,14 @@ __device__ __forceinline__ double slotv(const double* S, int seg, int k) { retur
 __global__ __launch_bounds__(BS) void k_bspmv_dot(BatchTab T, const int* __restrict__ rp, EntAx<double> ent,
                                                   double* __restrict__ q, const double* __restrict__ d,
                                                   double* part) {
-    __shared__ double prod[kStreamChunk];
+    __shared__ double lds[BS / kWave * kWaveLds<double, 0>];
     const int2 b = T.blk[blockIdx.x];
     if (!T.mask[b.x]) {
         if (threadIdx.x == 0) part[blockIdx.x] = 0.0;
         return;
     }
     const int end = T.seg_end[b.x];
-    const double s = stream_rows<double>(b.y, end, rp, ent, prod);
+    const double s = stream_rows<double>(b.y, end, rp, ent, lds);
     const int row = b.y + threadIdx.x;
     double acc[1] = {0.0};
     if (row < end) {
@@ -52,14 +52,14 @@ template <class TG>
 __global__ __launch_bounds__(BS) void k_bresidual(BatchTab T, const int* __restrict__ rp, EntAx<double> ent,
                                                   const double* __restrict__ b, double* __restrict__ r,
                                                   const double* __restrict__ dinv, TG* __restrict__ g, double* part) {
-    __shared__ double prod[kStreamChunk];
+    __shared__ double lds[BS / kWave * kWaveLds<double, 0>];
     const int2 bk = T.blk[blockIdx.x];
     if (!T.mask[bk.x]) {
         if (threadIdx.x == 0) part[blockIdx.x] = 0.0;
         return;
     }
     const int end = T.seg_end[bk.x];
-    const double s = stream_rows<double>(bk.y, end, rp, ent, prod);
+    const double s = stream_rows<double>(bk.y, end, rp, ent, lds);
     const int row = bk.y + threadIdx.x;
     double acc[1] = {0.0};
     if (row < end) {
@@ -150,12 +150,12 @@ __global__ __launch_bounds__(BS) void k_bbicg_s(BatchTab T, const double* __rest
 __global__ __launch_bounds__(BS) void k_bspmv_dot2(BatchTab T, const int* __restrict__ rp, EntAx<double> ent,
                                                    double* __restrict__ t, const double* __restrict__ sv,
                                                    double* part) {
-    __shared__ double prod[kStreamChunk];
+    __shared__ double lds[BS / kWave * kWaveLds<double, 0>];
     const int2 bk = T.blk[blockIdx.x];
     double acc[2] = {0.0, 0.0};
     if (T.mask[bk.x]) {  // uniform per block
         const int end = T.seg_end[bk.x];
-        const double s = stream_rows<double>(bk.y, end, rp, ent, prod);
+        const double s = stream_rows<double>(bk.y, end, rp, ent, lds);
         const int row = bk.y + threadIdx.x;
         if (row < end) {
             t[row] = s;

@@ -77,9 +77,9 @@ __global__ __launch_bounds__(FIN_BS) void k_finish(int nparts, int nv, const dou
 inline int stream_blocks(int n) { return amg::stream_blocks(n, kRedBlocks); }
 
 // A row kernel on a level's coded rows where it has them, else on its CSR rows.
-template <bool CODED>
-RowSrc<double, CODED> row_src(const LevelView& L, const double* x) {
-    return RowSrc<double, CODED>{L.code, L.rp, EntAx<double>{L.v, L.ci, x}};
+template <int KIND>
+RowSrc<double, KIND> row_src(const LevelView& L, const double* x) {
+    return RowSrc<double, KIND>{L.code, L.rp, EntAx<double>{L.v, L.ci, x}};
 }
 
 // ---------------------------------------------------------------------------
@@ -179,14 +179,14 @@ inline void finish(int nparts, int nv, const Reducer& R, int slot0, int slot1, h
 }
 
 // r = b - A x, partial (r, r)
-template <class TG, bool CODED>
-__global__ __launch_bounds__(BS) void k_stream_residual(int n, RowSrc<double, CODED> A, const double* __restrict__ b,
+template <class TG, int KIND>
+__global__ __launch_bounds__(BS) void k_stream_residual(int n, RowSrc<double, KIND> A, const double* __restrict__ b,
                                                         double* __restrict__ r, const double* __restrict__ dinv,
                                                         TG* __restrict__ g, double* part) {
-    __shared__ double prod[kStreamChunk];
+    __shared__ double lds[RowSrc<double, KIND>::template lds<BS>];
     double acc[1] = {0.0};
     A.template rows<BS>(
-        n, prod, [&](int row) { return make_double2(b[row], dinv[row]); },
+        n, lds, [&](int row) { return make_double2(b[row], dinv[row]); },
         [&](int row, double s, const double2& in) {
             const double ri = in.x - s;
             r[row] = ri;
@@ -196,10 +196,10 @@ __global__ __launch_bounds__(BS) void k_stream_residual(int n, RowSrc<double, CO
     block_partials<1, BS>(acc, part);
 }
 
-template <class TG, bool CODED>
+template <class TG, int KIND>
 void residual_launch(const LevelView& A, const double* b, const double* x, double* r, void* gout, const Reducer& R,
                      int g, hipStream_t s) {
-    hipLaunchKernelGGL((k_stream_residual<TG, CODED>), dim3(g), dim3(BS), 0, s, A.n, row_src<CODED>(A, x), b, r,
+    hipLaunchKernelGGL((k_stream_residual<TG, KIND>), dim3(g), dim3(BS), 0, s, A.n, row_src<KIND>(A, x), b, r,
                        A.dinv, static_cast<TG*>(gout), R.part);
 }
 
@@ -207,23 +207,23 @@ void launch_residual(const LevelView& A, const double* b, const double* x, doubl
                      const Reducer& R, int slot, hipStream_t s) {
     const int g = stream_blocks(A.n);
     if (A.code) {
-        if (g32) residual_launch<float, true>(A, b, x, r, gout, R, g, s);
-        else residual_launch<double, true>(A, b, x, r, gout, R, g, s);
+        if (g32) residual_launch<float, kCoded>(A, b, x, r, gout, R, g, s);
+        else residual_launch<double, kCoded>(A, b, x, r, gout, R, g, s);
     } else {
-        if (g32) residual_launch<float, false>(A, b, x, r, gout, R, g, s);
-        else residual_launch<double, false>(A, b, x, r, gout, R, g, s);
+        if (g32) residual_launch<float, 0>(A, b, x, r, gout, R, g, s);
+        else residual_launch<double, 0>(A, b, x, r, gout, R, g, s);
     }
     finish(g, 1, R, slot, slot, s);
 }
 
 // q = A p, partial (d, q)
-template <bool CODED>
-__global__ __launch_bounds__(BS) void k_stream_spmv_dot(int n, RowSrc<double, CODED> A, double* __restrict__ q,
+template <int KIND>
+__global__ __launch_bounds__(BS) void k_stream_spmv_dot(int n, RowSrc<double, KIND> A, double* __restrict__ q,
                                                         const double* __restrict__ d, double* part) {
-    __shared__ double prod[kStreamChunk];
+    __shared__ double lds[RowSrc<double, KIND>::template lds<BS>];
     double acc[1] = {0.0};
     A.template rows<BS>(
-        n, prod, [&](int row) { return d[row]; },
+        n, lds, [&](int row) { return d[row]; },
         [&](int row, double s, double di) {
             q[row] = s;
             acc[0] += di * s;
@@ -234,9 +234,9 @@ __global__ __launch_bounds__(BS) void k_stream_spmv_dot(int n, RowSrc<double, CO
 void spmv_dot_launch(const LevelView& A, const double* p, double* q, const double* d, double* part, int g,
                      hipStream_t s) {
     if (A.code)
-        hipLaunchKernelGGL(k_stream_spmv_dot<true>, dim3(g), dim3(BS), 0, s, A.n, row_src<true>(A, p), q, d, part);
+        hipLaunchKernelGGL(k_stream_spmv_dot<kCoded>, dim3(g), dim3(BS), 0, s, A.n, row_src<kCoded>(A, p), q, d, part);
     else
-        hipLaunchKernelGGL(k_stream_spmv_dot<false>, dim3(g), dim3(BS), 0, s, A.n, row_src<false>(A, p), q, d, part);
+        hipLaunchKernelGGL(k_stream_spmv_dot<0>, dim3(g), dim3(BS), 0, s, A.n, row_src<0>(A, p), q, d, part);
 }
 
 void launch_spmv_dot(const LevelView& A, const double* p, double* q, const double* d, const Reducer& R, int slot,
@@ -254,13 +254,13 @@ int launch_spmv_dot_parts(const LevelView& A, const double* p, double* q, const 
 }
 
 // t = A p, partials (t, t) and (t, sv)
-template <bool CODED>
-__global__ __launch_bounds__(BS) void k_stream_spmv_dot2(int n, RowSrc<double, CODED> A, double* __restrict__ t,
+template <int KIND>
+__global__ __launch_bounds__(BS) void k_stream_spmv_dot2(int n, RowSrc<double, KIND> A, double* __restrict__ t,
                                                          const double* __restrict__ sv, double* part) {
-    __shared__ double prod[kStreamChunk];
+    __shared__ double lds[RowSrc<double, KIND>::template lds<BS>];
     double acc[2] = {0.0, 0.0};
     A.template rows<BS>(
-        n, prod, [&](int row) { return sv[row]; },
+        n, lds, [&](int row) { return sv[row]; },
         [&](int row, double s, double si) {
             t[row] = s;
             acc[0] += s * s;
@@ -273,9 +273,9 @@ void launch_spmv_dot2(const LevelView& A, const double* p, double* t, const doub
                       int slot_ts, hipStream_t s) {
     const int g = stream_blocks(A.n);
     if (A.code)
-        hipLaunchKernelGGL(k_stream_spmv_dot2<true>, dim3(g), dim3(BS), 0, s, A.n, row_src<true>(A, p), t, sv, R.part);
+        hipLaunchKernelGGL(k_stream_spmv_dot2<kCoded>, dim3(g), dim3(BS), 0, s, A.n, row_src<kCoded>(A, p), t, sv, R.part);
     else
-        hipLaunchKernelGGL(k_stream_spmv_dot2<false>, dim3(g), dim3(BS), 0, s, A.n, row_src<false>(A, p), t, sv,
+        hipLaunchKernelGGL(k_stream_spmv_dot2<0>, dim3(g), dim3(BS), 0, s, A.n, row_src<0>(A, p), t, sv,
                            R.part);
     finish(g, 2, R, slot_tt, slot_ts, s);
 }

@@ -64,12 +64,12 @@ __device__ __forceinline__ T row_ax(int row, int lane, const int* __restrict__ r
 // Large levels (CSR-stream)
 // ---------------------------------------------------------------------------
 // r = f - w A g : residual after the zero-guess presmoothing sweep
-template <class T, class TIN, int RB, bool CODED>
-__global__ __launch_bounds__(RB) void k_vc_resid(int n, RowSrc<T, CODED> A, const TIN* __restrict__ f, T w,
+template <class T, class TIN, int RB, int KIND>
+__global__ __launch_bounds__(RB) void k_vc_resid(int n, RowSrc<T, KIND> A, const TIN* __restrict__ f, T w,
                                                  T* __restrict__ r) {
-    __shared__ T prod[kStreamChunk];
+    __shared__ T lds[RowSrc<T, KIND>::template lds<RB>];
     A.template rows<RB>(
-        n, prod, [&](int row) { return T(f[row]); }, [&](int row, T s, T fi) { r[row] = fi - w * s; });
+        n, lds, [&](int row) { return T(f[row]); }, [&](int row, T s, T fi) { r[row] = fi - w * s; });
 }
 
 // f_c = P^T r (members added in ascending order) and g_c = D_c^{-1} f_c
@@ -92,18 +92,18 @@ __global__ __launch_bounds__(BS) void k_vc_restrict(int nc, const int4* __restri
 // in double; MODE 2 scatters z to the finer level's prolongated iterate.
 // GF: g = D^{-1} f is formed here from the level's right-hand side f (in
 // double, whoever wrote g formed exactly this product), so g is not read.
-template <class T, class TOUT, int MODE, int RB, bool GF, bool CODED>
-__global__ __launch_bounds__(RB) void k_vc_post(int n, RowSrc<T, CODED> A, const T* __restrict__ g,
+template <class T, class TOUT, int MODE, int RB, bool GF, int KIND>
+__global__ __launch_bounds__(RB) void k_vc_post(int n, RowSrc<T, KIND> A, const T* __restrict__ g,
                                                 const T* __restrict__ dinv, T w, TOUT* __restrict__ z,
                                                 const double* __restrict__ f, double* part, ScatterT<T> sc) {
-    __shared__ T prod[kStreamChunk];
+    __shared__ T lds[RowSrc<T, KIND>::template lds<RB>];
     double acc[1] = {0.0};
     struct In {
         T x, di, g;
         double f;
     };
     A.template rows<RB>(
-        n, prod,
+        n, lds,
         [&](int row) {
             const double fi = GF || MODE == 1 ? f[row] : 0.0;
             const T di = dinv[row];
@@ -120,9 +120,9 @@ __global__ __launch_bounds__(RB) void k_vc_post(int n, RowSrc<T, CODED> A, const
 
 // The launchers pick the instantiation from the level: coded rows where it has
 // them (256 rows per block), else CSR rows with the level's rows per block.
-template <bool CODED, class T>
-RowSrc<T, CODED> row_src(const VLevel<T>& L, const T* x) {
-    return RowSrc<T, CODED>{L.code, L.rp, EntAx<T>{L.v, L.ci, x}};
+template <int KIND, class T>
+RowSrc<T, KIND> row_src(const VLevel<T>& L, const T* x) {
+    return RowSrc<T, KIND>{L.code, L.rp, EntAx<T>{L.v, L.ci, x}};
 }
 
 inline int rb_blocks(int n, int rb) {
@@ -130,18 +130,20 @@ inline int rb_blocks(int n, int rb) {
     return b < kRedBlocks ? (b < 1 ? 1 : b) : kRedBlocks;
 }
 
-template <int RB, bool CODED, class T, class TIN>
+template <int RB, int KIND, class T, class TIN>
 void resid_launch(const VLevel<T>& L, const TIN* f, const T* g, T w, T* r, hipStream_t s) {
-    hipLaunchKernelGGL((k_vc_resid<T, TIN, RB, CODED>), dim3(rb_blocks(L.n, RB)), dim3(RB), 0, s, L.n,
-                       row_src<CODED>(L, g), f, w, r);
+    hipLaunchKernelGGL((k_vc_resid<T, TIN, RB, KIND>), dim3(rb_blocks(L.n, RB)), dim3(RB), 0, s, L.n,
+                       row_src<KIND>(L, g), f, w, r);
 }
 
 template <class T, class TIN>
 void vc_stream_resid(const VLevel<T>& L, const TIN* f, const T* g, T w, T* r, hipStream_t s) {
-    if (L.code) resid_launch<256, true>(L, f, g, w, r, s);
-    else if (L.rb == 128) resid_launch<128, false>(L, f, g, w, r, s);
-    else if (L.rb == 512) resid_launch<512, false>(L, f, g, w, r, s);
-    else resid_launch<256, false>(L, f, g, w, r, s);
+    if (L.code) resid_launch<256, kCoded>(L, f, g, w, r, s);
+    else if (L.order == 4) resid_launch<256, 4>(L, f, g, w, r, s);
+    else if (L.order == 8) resid_launch<256, 8>(L, f, g, w, r, s);
+    else if (L.rb == 128) resid_launch<128, 0>(L, f, g, w, r, s);
+    else if (L.rb == 512) resid_launch<512, 0>(L, f, g, w, r, s);
+    else resid_launch<256, 0>(L, f, g, w, r, s);
 }
 
 template <class T>
@@ -149,17 +151,17 @@ void vc_restrict(int nc, const int4* mem, const T* r, const T* dinv_c, T* fc, T*
     hipLaunchKernelGGL(k_vc_restrict<T>, dim3(level_blocks(nc, 1)), dim3(BS), 0, s, nc, mem, r, dinv_c, fc, gc);
 }
 
-template <class T, class TOUT, int MODE, bool GF, int RB, bool CODED>
+template <class T, class TOUT, int MODE, bool GF, int RB, int KIND>
 int post_launch(const VLevel<T>& L, const T* xp, const T* g, T w, TOUT* z, const double* f, double* part,
                 const ScatterT<T>& sc, int cap, hipStream_t s, hipEvent_t t0, hipEvent_t t1) {
     const int nb = rb_blocks(L.n, RB), gsz = nb < cap ? nb : cap;
-    const RowSrc<T, CODED> A = row_src<CODED>(L, xp);
+    const RowSrc<T, KIND> A = row_src<KIND>(L, xp);
     // with t0/t1 the dispatch itself records the kernel's start and end
     if (t0)
-        hipExtLaunchKernelGGL((k_vc_post<T, TOUT, MODE, RB, GF, CODED>), dim3(gsz), dim3(RB), 0, s, t0, t1, 0, L.n, A,
+        hipExtLaunchKernelGGL((k_vc_post<T, TOUT, MODE, RB, GF, KIND>), dim3(gsz), dim3(RB), 0, s, t0, t1, 0, L.n, A,
                               g, L.dinv, w, z, f, part, sc);
     else
-        hipLaunchKernelGGL((k_vc_post<T, TOUT, MODE, RB, GF, CODED>), dim3(gsz), dim3(RB), 0, s, L.n, A, g, L.dinv, w,
+        hipLaunchKernelGGL((k_vc_post<T, TOUT, MODE, RB, GF, KIND>), dim3(gsz), dim3(RB), 0, s, L.n, A, g, L.dinv, w,
                            z, f, part, sc);
     return gsz;
 }
@@ -167,19 +169,22 @@ int post_launch(const VLevel<T>& L, const T* xp, const T* g, T w, TOUT* z, const
 template <class T, class TOUT, int MODE, bool GF>
 int post_rows(const VLevel<T>& L, const T* xp, const T* g, T w, TOUT* z, const double* f, double* part,
               const ScatterT<T>& sc, hipStream_t s, hipEvent_t t0, hipEvent_t t1, int cap = kRedBlocks) {
-    if (L.code) return post_launch<T, TOUT, MODE, GF, 256, true>(L, xp, g, w, z, f, part, sc, cap, s, t0, t1);
-    if (L.rb == 128) return post_launch<T, TOUT, MODE, GF, 128, false>(L, xp, g, w, z, f, part, sc, cap, s, t0, t1);
-    if (L.rb == 512) return post_launch<T, TOUT, MODE, GF, 512, false>(L, xp, g, w, z, f, part, sc, cap, s, t0, t1);
-    return post_launch<T, TOUT, MODE, GF, 256, false>(L, xp, g, w, z, f, part, sc, cap, s, t0, t1);
+    if (L.code) return post_launch<T, TOUT, MODE, GF, 256, kCoded>(L, xp, g, w, z, f, part, sc, cap, s, t0, t1);
+    if (L.order == 4) return post_launch<T, TOUT, MODE, GF, 256, 4>(L, xp, g, w, z, f, part, sc, cap, s, t0, t1);
+    if (L.order == 8) return post_launch<T, TOUT, MODE, GF, 256, 8>(L, xp, g, w, z, f, part, sc, cap, s, t0, t1);
+    if (L.rb == 128) return post_launch<T, TOUT, MODE, GF, 128, 0>(L, xp, g, w, z, f, part, sc, cap, s, t0, t1);
+    if (L.rb == 512) return post_launch<T, TOUT, MODE, GF, 512, 0>(L, xp, g, w, z, f, part, sc, cap, s, t0, t1);
+    return post_launch<T, TOUT, MODE, GF, 256, 0>(L, xp, g, w, z, f, part, sc, cap, s, t0, t1);
 }
 
 template <class T, class TOUT>
 int vc_stream_post(const VLevel<T>& L, const T* xp, const T* g, T w, TOUT* z, const double* f, const Reducer* R,
                    int slot, const ScatterT<T>* sc, hipStream_t s, hipEvent_t t0, hipEvent_t t1) {
     const ScatterT<T> none{nullptr, nullptr, nullptr, T(0)};
-    // a double level 0 forms g = D^{-1} f itself instead of reading it
+    // a double level 0 forms g = D^{-1} f itself instead of reading it (and may
+    // fuse the product, so not where it has to give the lane-group kernels' bits)
     constexpr bool kCanGF = std::is_same<T, double>::value && std::is_same<TOUT, double>::value;
-    const bool gf = kCanGF && f != nullptr;
+    const bool gf = kCanGF && f != nullptr && L.order == 0;
     if (R) {
         const int cap = slot == kPartialsOnly ? kFusedParts : kRedBlocks;
         const int np = gf ? post_rows<T, TOUT, 1, kCanGF>(L, xp, g, w, z, f, R->part, none, s, t0, t1, cap)
