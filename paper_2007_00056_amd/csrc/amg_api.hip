@@ -450,7 +450,7 @@ Csr galerkin(const Csr& B, Pass& P, SetupWork& W, DevPool& out, hipStream_t s, c
     const int nmax = P.n;  // coarse rows <= fine rows
     const int* ncp = W.ids + P.n;
     HIPCHK(hipMemsetAsync(W.novf, 0, sizeof(int), s));
-    launch_rap_count(nmax, ncp, P.lead, P.mate, B.rp, B.ci, P.agg, W.rowcnt, W.ovf, W.novf, s);
+    launch_rap_count(nmax, B.nnz, ncp, P.lead, P.mate, B.rp, B.ci, P.agg, W.rowcnt, W.ovf, W.novf, s);
     launch_rap_count_slow(nmax, W.ovf, W.novf, P.lead, P.mate, B.rp, B.ci, P.agg, W.rowcnt, s);
     Csr C;
     if (!crp) crp = out.get<int>((size_t)nmax + 1);
@@ -459,7 +459,7 @@ Csr galerkin(const Csr& B, Pass& P, SetupWork& W, DevPool& out, hipStream_t s, c
     HIPCHK(hipGetLastError());
     int* dw = nullptr;
     int* hw = pinned_words(&dw);
-    launch_pass_words(dw, P.cnt, ncp, C.rp + nmax, err, s);  // one launch in place of four copies
+    launch_pass_words(dw, P.cnt, ncp, C.rp + nmax, err, W.novf, s);  // one launch in place of four copies
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(s));
     raise_err_word(hw[10], "amg_setup");
@@ -472,8 +472,9 @@ Csr galerkin(const Csr& B, Pass& P, SetupWork& W, DevPool& out, hipStream_t s, c
     C.nnz = hw[9];
     C.ci = out.get<int>((size_t)C.nnz);
     C.v = out.get<double>((size_t)C.nnz);
-    launch_rap_fill(P.nc, P.lead, P.mate, B.rp, B.ci, B.v, P.agg, C.rp, C.ci, C.v, s);
-    launch_rap_fill_slow(P.nc, W.ovf, W.novf, P.lead, P.mate, B.rp, B.ci, B.v, P.agg, C.rp, C.ci, C.v, s);
+    launch_rap_fill(P.nc, B.n, B.nnz, P.lead, P.mate, B.rp, B.ci, B.v, P.agg, C.rp, C.ci, C.v, s);
+    if (hw[11] > 0)
+        launch_rap_fill_slow(P.nc, W.ovf, W.novf, P.lead, P.mate, B.rp, B.ci, B.v, P.agg, C.rp, C.ci, C.v, s);
     HIPCHK(hipGetLastError());
     return C;
 }

@@ -70,19 +70,21 @@ void launch_ehem_round(int r, int n, const int* rp, const int* ci, HemWork& w, h
 size_t scan_tmp_ints(int n);
 // out[0..7] = cnt[0..7], out[8] = *ncp, out[9] = *nnzc, out[10] = *err (out: a
 // device address of mapped host memory).
-void launch_pass_words(int* out, const int* cnt, const int* ncp, const int* nnzc, const int* err, hipStream_t s);
+void launch_pass_words(int* out, const int* cnt, const int* ncp, const int* nnzc, const int* err, const int* novf,
+                       hipStream_t s);
 void launch_scan(const int* in, int n, int* out, int* tmp, hipStream_t s);
 void launch_leader_flags(int n, const int* mate, int* flag, hipStream_t s);
 // agg[v] = id of v's aggregate; lead[id] = smaller vertex of the aggregate.
 void launch_assign_ids(int n, const int* mate, const int* ids, int* agg, int* lead, hipStream_t s);
 
 // Galerkin product of one matching pass (aggregates of size <= 2).
-void launch_rap_count(int nmax, const int* ncp, const int* lead, const int* mate, const int* rp, const int* ci,
-                      const int* agg, int* rowcnt, int* ovf, int* novf, hipStream_t s);
+// n, nnz: rows and entries of the fine operator
+void launch_rap_count(int nmax, int64_t nnz, const int* ncp, const int* lead, const int* mate, const int* rp,
+                      const int* ci, const int* agg, int* rowcnt, int* ovf, int* novf, hipStream_t s);
 void launch_rap_count_slow(int nc, const int* ovf, const int* novf, const int* lead, const int* mate, const int* rp,
                            const int* ci, const int* agg, int* rowcnt, hipStream_t s);
-void launch_rap_fill(int nc, const int* lead, const int* mate, const int* rp, const int* ci, const double* v,
-                     const int* agg, const int* crp, int* cci, double* cv, hipStream_t s);
+void launch_rap_fill(int nc, int n, int64_t nnz, const int* lead, const int* mate, const int* rp, const int* ci,
+                     const double* v, const int* agg, const int* crp, int* cci, double* cv, hipStream_t s);
 void launch_rap_fill_slow(int nc, const int* ovf, const int* novf, const int* lead, const int* mate, const int* rp,
                           const int* ci, const double* v, const int* agg, const int* crp, int* cci, double* cv,
                           hipStream_t s);

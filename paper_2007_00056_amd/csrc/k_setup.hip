@@ -3,6 +3,7 @@
 // aggregate member lists.  The matching itself is in k_hem.hip, the coarsest
 // level's inverse in k_dense.hip.
 #include <climits>
+#include <type_traits>
 
 #include "amg_device.hpp"
 #include "amg_internal.hpp"
@@ -213,19 +214,22 @@ __global__ __launch_bounds__(BS) void k_scan_apply(const int* __restrict__ in, i
 }
 
 // The words a pass hands to the host, gathered by one small launch: the
-// matching's 8 counters, the coarse row count, the coarse entry count and the
-// error word.
+// matching's 8 counters, the coarse row count, the coarse entry count, the
+// error word and the Galerkin product's overflow rows.
 __global__ void k_pass_words(int* __restrict__ out, const int* __restrict__ cnt, const int* __restrict__ ncp,
-                             const int* __restrict__ nnzc, const int* __restrict__ err) {
+                             const int* __restrict__ nnzc, const int* __restrict__ err,
+                             const int* __restrict__ novf) {
     const int t = threadIdx.x;
     if (t < 8) out[t] = cnt[t];
     else if (t == 8) out[8] = *ncp;
     else if (t == 9) out[9] = *nnzc;
     else if (t == 10) out[10] = *err;
+    else if (t == 11) out[11] = *novf;
 }
 
-void launch_pass_words(int* out, const int* cnt, const int* ncp, const int* nnzc, const int* err, hipStream_t s) {
-    hipLaunchKernelGGL(k_pass_words, dim3(1), dim3(kWave), 0, s, out, cnt, ncp, nnzc, err);
+void launch_pass_words(int* out, const int* cnt, const int* ncp, const int* nnzc, const int* err, const int* novf,
+                       hipStream_t s) {
+    hipLaunchKernelGGL(k_pass_words, dim3(1), dim3(kWave), 0, s, out, cnt, ncp, nnzc, err, novf);
 }
 
 size_t scan_tmp_ints(int n) { return (size_t)(n + SCAN_TILE - 1) / SCAN_TILE + 1; }
@@ -271,125 +275,126 @@ void launch_assign_ids(int n, const int* mate, const int* ids, int* agg, int* le
 // (Section 2.1.1).  Coarse row I has members lead[I] < mate[lead[I]]; entry
 // (I,J) sums b_ij over the members in ascending order and, within a member,
 // over its columns in ascending order, the first term initialising the sum.
-// The fixed order makes the values bit-identical on every run.  A thread owns
-// one coarse row and keeps its sorted (column, sum) list in its own LDS
-// columns (a list this long indexed by position does not stay in registers);
-// rows with more than RAP_CAP distinct columns go to a slower in-place path.
+// The fixed order makes the values bit-identical on every run.
+//
+// G lanes (16 or 32) take a coarse row, a lane one entry of its members, or
+// two.  The entries' coarse columns go through LDS, where each lane compares
+// its own with all of the row's: the bits of the equal and of the smaller ones.
+// An entry with no equal one before it leads its column, whose rank is the
+// number of smaller leaders, and adds the values of the equal ones in order.
+// Rows of more than 2 G entries go to a slower path.
+//
+// Bound by the chain of loads up to the coarse columns and, on large levels,
+// by the comparisons.  A thread a coarse row, inserting into a sorted list in
+// LDS, took 40-50 us to count and 50-60 to fill on any small level of 15-30
+// entries a row; this takes 5-8 and 7-15.  On 27,700 rows of 17 entries
+// 41 + 51 us became 11 + 18, on 218,000 of 12 23 + 51 became 19 + 29; on 2.1M
+// rows of 7 38 + 129 became 73 + 119.
 // ---------------------------------------------------------------------------
 namespace {
-constexpr int RAP_CAP = 32;
-constexpr int RAP_BS = 128;
-constexpr int RAP_WIN = 8;
+constexpr int RAP_BS = 256;
+constexpr int RAP_MAX = 4096;  // blocks: two rounds of the chip
+inline int rap_lanes(int n, int64_t nnz) { return nnz <= 8 * (int64_t)n ? 16 : 32; }
 
-// Sorted (column, sum) list of one thread: entry t at key[t * RAP_BS] (the
-// threads of a block interleave, so a wave's accesses hit distinct banks).
-// The first value added for a column initialises its sum; later values are
-// added in call order.
-template <bool WITH_VAL>
-struct LdsAcc {
-    int* key;
-    double* val;
-    int len;
-
-    __device__ __forceinline__ int& k(int t) const { return key[t * RAP_BS]; }
-    __device__ __forceinline__ double& x(int t) const { return val[t * RAP_BS]; }
-
-    // false (list unchanged) when a new column does not fit
-    __device__ __forceinline__ bool add(int J, double v) {
-        int lo = 0, hi = len;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (k(mid) < J) lo = mid + 1;
-            else hi = mid;
-        }
-        if (lo < len && k(lo) == J) {
-            if (WITH_VAL) x(lo) += v;
-            return true;
-        }
-        if (len == RAP_CAP) return false;
-        for (int t = len; t > lo; --t) {
-            k(t) = k(t - 1);
-            if (WITH_VAL) x(t) = x(t - 1);
-        }
-        k(lo) = J;
-        if (WITH_VAL) x(lo) = v;
-        ++len;
-        return true;
+// The row's L <= G * E entries from b0 on (l0 of them) and from b1 on; key and
+// val are the row's places in LDS.  Returns the distinct columns.
+template <int G, int E, bool FILL>
+__device__ __forceinline__ int rap_row(int l0, int b0, int b1, int L, const int* __restrict__ ci,
+                                       const double* __restrict__ v, const int* __restrict__ agg, int* key,
+                                       double* val, int o, int* __restrict__ cci, double* __restrict__ cv) {
+    using Bits = std::conditional_t<(G * E > 32), unsigned long long, unsigned>;
+    const int lane = threadIdx.x & (G - 1), base = threadIdx.x & (kWave - 1) & ~(G - 1);
+    int c[E], J[E];
+    double x[E];
+#pragma unroll
+    for (int t = 0; t < E; ++t) {
+        const int k = lane + G * t, e = k < l0 ? b0 + k : b1 + (k - l0);
+        c[t] = k < L ? ci[e] : -1;
+        x[t] = FILL && k < L ? v[e] : 0.0;
     }
-};
+#pragma unroll
+    for (int t = 0; t < E; ++t) J[t] = c[t] >= 0 ? agg[c[t]] : INT_MAX;
+#pragma unroll
+    for (int t = 0; t < E; ++t) {
+        key[lane + G * t] = J[t];
+        if (FILL) val[lane + G * t] = x[t];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    Bits eq[E], lt[E];
+#pragma unroll
+    for (int t = 0; t < E; ++t) eq[t] = lt[t] = 0;
+    for (int j = 0; j < L; j += 4) {
+        const int4 q = *reinterpret_cast<const int4*>(key + j);
+#pragma unroll
+        for (int t = 0; t < E; ++t) {
+            eq[t] |= Bits((q.x == J[t]) | (q.y == J[t]) << 1 | (q.z == J[t]) << 2 | (q.w == J[t]) << 3) << j;
+            lt[t] |= Bits((q.x < J[t]) | (q.y < J[t]) << 1 | (q.z < J[t]) << 2 | (q.w < J[t]) << 3) << j;
+        }
+    }
+    Bits leaders = 0;
+    bool lead[E];
+#pragma unroll
+    for (int t = 0; t < E; ++t) {
+        const int k = lane + G * t;
+        lead[t] = k < L && (eq[t] & ((Bits(1) << k) - 1)) == 0;
+        const unsigned b = unsigned(__ballot(lead[t]) >> base) & unsigned((1ull << G) - 1);
+        leaders |= Bits(b) << (G * t);
+    }
+    const int count = sizeof(Bits) == 8 ? __popcll(leaders) : __popc(unsigned(leaders));
+    if (FILL) {
+#pragma unroll
+        for (int t = 0; t < E; ++t) {
+            if (!lead[t]) continue;
+            double sum = x[t];
+            for (Bits m = eq[t] & (eq[t] - 1); m != 0; m &= m - 1)
+                sum += val[sizeof(Bits) == 8 ? __builtin_ctzll(m) : __builtin_ctz(unsigned(m))];
+            const Bits below = lt[t] & leaders;
+            const int r = o + (sizeof(Bits) == 8 ? __popcll(below) : __popc(unsigned(below)));
+            cci[r] = J[t];
+            cv[r] = sum;
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    return count;
+}
 }  // namespace
 
-// Entries of a member row are taken in windows of RAP_WIN whose column and
-// aggregate loads are issued together, then added in entry order.
-template <bool WITH_VAL>
-__device__ __forceinline__ bool rap_row(LdsAcc<WITH_VAL>& acc, int e0, int e1, const int* __restrict__ ci,
-                                        const double* __restrict__ v, const int* __restrict__ agg) {
-    for (int b = e0; b < e1; b += RAP_WIN) {
-        int c[RAP_WIN], J[RAP_WIN];
-        double x[RAP_WIN];
-#pragma unroll
-        for (int t = 0; t < RAP_WIN; ++t) c[t] = b + t < e1 ? ci[b + t] : -1;
-#pragma unroll
-        for (int t = 0; t < RAP_WIN; ++t) {
-            J[t] = c[t] >= 0 ? agg[c[t]] : -1;
-            x[t] = (WITH_VAL && c[t] >= 0) ? v[b + t] : 0.0;
+// FILL: rows below nmax get their columns and values from crp on.  Else they
+// are counted up to nmax (an upper bound of the coarse size *ncp); rows past
+// the coarse size count zero, so a scan over nmax rows gives the offsets.
+template <int G, bool FILL>
+__global__ __launch_bounds__(RAP_BS) void k_rap(int nmax, const int* __restrict__ ncp, const int* __restrict__ lead,
+                                                const int* __restrict__ mate, const int* __restrict__ rp,
+                                                const int* __restrict__ ci, const double* __restrict__ v,
+                                                const int* __restrict__ agg, int* __restrict__ rowcnt,
+                                                int* __restrict__ ovf, int* novf, const int* __restrict__ crp,
+                                                int* __restrict__ cci, double* __restrict__ cv) {
+    __shared__ __align__(16) int skey[2 * RAP_BS];
+    __shared__ double sval[FILL ? 2 * RAP_BS : 1];
+    const int g = threadIdx.x / G, lane = threadIdx.x & (G - 1);
+    int* key = skey + g * 2 * G;
+    double* val = sval + (FILL ? g * 2 * G : 0);
+    const int nc = FILL ? nmax : *ncp;
+    for (int I = blockIdx.x * (RAP_BS / G) + g; I < nc; I += gridDim.x * (RAP_BS / G)) {
+        const int m0 = lead[I];
+        const int m1 = mate[m0];
+        const int b0 = rp[m0], l0 = rp[m0 + 1] - b0;
+        const int b1 = m1 >= 0 ? rp[m1] : 0, L = l0 + (m1 >= 0 ? rp[m1 + 1] - b1 : 0);
+        int cnt = 0;
+        if (L > 2 * G) {  // the slow path's
+            if (!FILL && lane == 0) ovf[atomicAdd(novf, 1)] = I;
+        } else {
+            const int o = FILL ? crp[I] : 0;
+            cnt = L <= G ? rap_row<G, 1, FILL>(l0, b0, b1, L, ci, v, agg, key, val, o, cci, cv)
+                         : rap_row<G, 2, FILL>(l0, b0, b1, L, ci, v, agg, key, val, o, cci, cv);
         }
-#pragma unroll
-        for (int t = 0; t < RAP_WIN; ++t)
-            if (J[t] >= 0 && !acc.add(J[t], x[t])) return false;
+        if (!FILL && lane == 0) rowcnt[I] = cnt;
     }
-    return true;
+    if (!FILL)
+        for (int I = nc + blockIdx.x * RAP_BS + threadIdx.x; I < nmax; I += gridDim.x * RAP_BS) rowcnt[I] = 0;
 }
 
-// Rows are counted up to nmax (an upper bound of the coarse size *ncp); rows
-// past the coarse size count zero, so a scan over nmax rows gives the offsets.
-__global__ __launch_bounds__(RAP_BS) void k_rap_count(int nmax, const int* __restrict__ ncp,
-                                                      const int* __restrict__ lead, const int* __restrict__ mate,
-                                                      const int* __restrict__ rp, const int* __restrict__ ci,
-                                                      const int* __restrict__ agg, int* __restrict__ rowcnt,
-                                                      int* __restrict__ ovf, int* novf) {
-    const int I = blockIdx.x * RAP_BS + threadIdx.x;
-    if (I >= nmax) return;
-    if (I >= *ncp) {
-        rowcnt[I] = 0;
-        return;
-    }
-    __shared__ int skey[RAP_CAP * RAP_BS];
-    const int m0 = lead[I];
-    const int m1 = mate[m0];
-    LdsAcc<false> acc{skey + threadIdx.x, nullptr, 0};
-    bool ok = rap_row<false>(acc, rp[m0], rp[m0 + 1], ci, nullptr, agg);
-    if (ok && m1 >= 0) ok = rap_row<false>(acc, rp[m1], rp[m1 + 1], ci, nullptr, agg);
-    if (ok) {
-        rowcnt[I] = acc.len;
-    } else {
-        rowcnt[I] = 0;
-        ovf[atomicAdd(novf, 1)] = I;
-    }
-}
-
-__global__ __launch_bounds__(RAP_BS) void k_rap_fill(int nc, const int* __restrict__ lead,
-                                                     const int* __restrict__ mate, const int* __restrict__ rp,
-                                                     const int* __restrict__ ci, const double* __restrict__ v,
-                                                     const int* __restrict__ agg, const int* __restrict__ crp,
-                                                     int* __restrict__ cci, double* __restrict__ cv) {
-    const int I = blockIdx.x * RAP_BS + threadIdx.x;
-    if (I >= nc) return;
-    __shared__ int skey[RAP_CAP * RAP_BS];
-    __shared__ double sval[RAP_CAP * RAP_BS];
-    const int m0 = lead[I];
-    const int m1 = mate[m0];
-    LdsAcc<true> acc{skey + threadIdx.x, sval + threadIdx.x, 0};
-    if (!rap_row<true>(acc, rp[m0], rp[m0 + 1], ci, v, agg)) return;  // overflow row: slow path
-    if (m1 >= 0 && !rap_row<true>(acc, rp[m1], rp[m1 + 1], ci, v, agg)) return;
-    const int o = crp[I];
-    for (int t = 0; t < acc.len; ++t) {
-        cci[o + t] = acc.k(t);
-        cv[o + t] = acc.x(t);
-    }
-}
-
-// Overflow rows (more than RAP_CAP distinct coarse columns): one wave per
+// Overflow rows (more than two entries a lane): one wave per
 // row.  The row's entries, in member-then-column order, are staged in LDS
 // with their coarse columns; a stable rank (by column, then entry order)
 // sorts them, and the first lane of each run of equal columns adds the run
@@ -526,10 +531,16 @@ __global__ __launch_bounds__(kWave) void k_rap_slow(const int* __restrict__ ovf,
     }
 }
 
-void launch_rap_count(int nmax, const int* ncp, const int* lead, const int* mate, const int* rp, const int* ci,
-                      const int* agg, int* rowcnt, int* ovf, int* novf, hipStream_t s) {
-    hipLaunchKernelGGL(k_rap_count, dim3(blocks_for(nmax, RAP_BS)), dim3(RAP_BS), 0, s, nmax, ncp, lead, mate, rp, ci,
-                       agg, rowcnt, ovf, novf);
+void launch_rap_count(int nmax, int64_t nnz, const int* ncp, const int* lead, const int* mate, const int* rp,
+                      const int* ci, const int* agg, int* rowcnt, int* ovf, int* novf, hipStream_t s) {
+    const int G = rap_lanes(nmax, nnz);
+    const dim3 g(blocks_for(nmax, RAP_BS / G, RAP_MAX));
+    if (G == 16)
+        hipLaunchKernelGGL((k_rap<16, false>), g, dim3(RAP_BS), 0, s, nmax, ncp, lead, mate, rp, ci, nullptr, agg,
+                           rowcnt, ovf, novf, nullptr, nullptr, nullptr);
+    else
+        hipLaunchKernelGGL((k_rap<32, false>), g, dim3(RAP_BS), 0, s, nmax, ncp, lead, mate, rp, ci, nullptr, agg,
+                           rowcnt, ovf, novf, nullptr, nullptr, nullptr);
 }
 
 void launch_rap_count_slow(int nc, const int* ovf, const int* novf, const int* lead, const int* mate, const int* rp,
@@ -538,10 +549,16 @@ void launch_rap_count_slow(int nc, const int* ovf, const int* novf, const int* l
                        ci, nullptr, agg, rowcnt, nullptr, nullptr, nullptr);
 }
 
-void launch_rap_fill(int nc, const int* lead, const int* mate, const int* rp, const int* ci, const double* v,
-                     const int* agg, const int* crp, int* cci, double* cv, hipStream_t s) {
-    hipLaunchKernelGGL(k_rap_fill, dim3(blocks_for(nc, RAP_BS)), dim3(RAP_BS), 0, s, nc, lead, mate, rp, ci, v, agg,
-                       crp, cci, cv);
+void launch_rap_fill(int nc, int n, int64_t nnz, const int* lead, const int* mate, const int* rp, const int* ci,
+                     const double* v, const int* agg, const int* crp, int* cci, double* cv, hipStream_t s) {
+    const int G = rap_lanes(n, nnz);  // the rows left out are those the count left out
+    const dim3 g(blocks_for(nc, RAP_BS / G, RAP_MAX));
+    if (G == 16)
+        hipLaunchKernelGGL((k_rap<16, true>), g, dim3(RAP_BS), 0, s, nc, nullptr, lead, mate, rp, ci, v, agg, nullptr,
+                           nullptr, nullptr, crp, cci, cv);
+    else
+        hipLaunchKernelGGL((k_rap<32, true>), g, dim3(RAP_BS), 0, s, nc, nullptr, lead, mate, rp, ci, v, agg, nullptr,
+                           nullptr, nullptr, crp, cci, cv);
 }
 
 void launch_rap_fill_slow(int nc, const int* ovf, const int* novf, const int* lead, const int* mate, const int* rp,
