@@ -84,14 +84,14 @@ constexpr int kRowEnt = 31;
 __device__ __forceinline__ unsigned low_bits(int p) { return (1u << p) - 1u; }
 }  // namespace
 
-// Per vertex y of a pass: its record (the first R higher edge-neighbours by
+// Per vertex y of a pass: its record (the first 4, 16 or 32 higher edge-neighbours by
 // |a_yj| descending, column ascending on ties), deg = (number of lower stored
 // entries or extension offset | kWideFlag, number of higher edge-neighbours |
 // kZeroFlag), its word for the other tiles (0) and mate (-1).
 // counters: cnt[1] words of the extension array used, cnt[5] sum over rows of
 // (#upper - #lower) entries; err: an upper entry whose mirror image is not
 // stored.  Together these are zero exactly for a symmetric pattern.
-template <int R>
+constexpr int kInitList = 4;
 __global__ __launch_bounds__(BS) void k_hem_init(int n, const int* __restrict__ rp, const int* __restrict__ ci,
                                                  const double* __restrict__ v, int* __restrict__ rec,
                                                  int2* __restrict__ deg, unsigned* __restrict__ gw,
@@ -103,10 +103,10 @@ __global__ __launch_bounds__(BS) void k_hem_init(int n, const int* __restrict__ 
         mate[y] = -1;
         gw[y] = 0u;
         int nh = 0, bad = 0, zero = 0;
-        int ent[R];
-        double wt[R];
+        int ent[kInitList];
+        double wt[kInitList];
 #pragma unroll
-        for (int t = 0; t < R; ++t) {
+        for (int t = 0; t < kInitList; ++t) {
             ent[t] = 0;
             wt[t] = 0.0;
         }
@@ -155,25 +155,25 @@ __global__ __launch_bounds__(BS) void k_hem_init(int n, const int* __restrict__ 
                 const int code = wide[q] || delta >= kMaxDelta ? kRowEnt : (delta << 5) | pos[q];
                 int at = 0;  // by |a| descending; columns arrive ascending
 #pragma unroll
-                for (int t = 0; t < R; ++t)
+                for (int t = 0; t < kInitList; ++t)
                     if (t < nh - 1 && wt[t] >= w) at = t + 1;
 #pragma unroll
-                for (int t = R - 1; t > 0; --t)
+                for (int t = kInitList - 1; t > 0; --t)
                     if (t > at) {  // a full list drops its last entry
                         wt[t] = wt[t - 1];
                         ent[t] = ent[t - 1];
                     }
 #pragma unroll
-                for (int t = 0; t < R; ++t)
+                for (int t = 0; t < kInitList; ++t)
                     if (t == at) {
                         wt[t] = w;
                         ent[t] = code;
                     }
             }
         }
-        int4* out = reinterpret_cast<int4*>(rec) + (size_t)y * (R / 4);
+        int4* out = reinterpret_cast<int4*>(rec) + (size_t)y * (kInitList / 4);
 #pragma unroll
-        for (int t = 0; t < R; t += 4) out[t / 4] = make_int4(ent[t], ent[t + 1], ent[t + 2], ent[t + 3]);
+        for (int t = 0; t < kInitList; t += 4) out[t / 4] = make_int4(ent[t], ent[t + 1], ent[t + 2], ent[t + 3]);
         int low = nlow;
         if (nlow > kWordEdges) {  // extension: the number of lower entries, then their bits
             const int words = (nlow + 31) / 32;
@@ -201,6 +201,176 @@ __global__ __launch_bounds__(BS) void k_hem_init(int n, const int* __restrict__ 
 #pragma unroll
         for (int k = 0; k < BS / kWave; ++k) d += s_diff[k];
         if (d != 0) atomicAdd(&cnt[5], d);
+    }
+}
+
+// The same with G lanes a row, an entry a lane or two; for all but the largest
+// regular levels, where a thread a row above is faster.  An entry's place in
+// the record is its rank among the row's, counted through LDS (weights compare
+// as their bit patterns: a strict order, with the column, whatever they are).
+// Rows of more than 2 G entries are ranked by taking the largest R times.
+// Every entry's mirror image is looked for, the lower ones' by lanes that would
+// wait, so no sum over the rows is needed: with one add a block to a single
+// word a pass of 65,536 rows took 53 us instead of 13.
+//
+// Bound by the chain of loads down to the neighbours' rows.  With a thread a
+// row, inserting into a list of 16 or 32 in registers, any small level of 12-20
+// entries a row took 45-80 us; this takes 6-12, and 22 at 55,000 rows (57), 28 at
+// 110,000 (39).
+namespace {
+struct InitRow {  // what a row's lanes find together
+    int nlow, nh;
+    bool zero, bad;
+};
+
+// code of y's record entry for its higher neighbour u; false: u's row has no y
+__device__ __forceinline__ bool init_code(const int* __restrict__ rp, const int* __restrict__ ci, int y, int u,
+                                          int& code) {
+    const int b = rp[u], e = rp[u + 1];
+    const int at = find_col_short(ci, b, e, y);
+    const int delta = u - y;
+    code = wide_row(ci, b, e, u) || delta >= kMaxDelta ? kRowEnt : (delta << 5) | (at - b);
+    return at >= 0;
+}
+
+__device__ __forceinline__ unsigned long long weight_bits(double a) { return (unsigned long long)__double_as_longlong(fabs(a)); }
+
+template <int R, int G, int E>
+__device__ __forceinline__ InitRow init_row(int y, int e0, int L, const int* __restrict__ rp,
+                                            const int* __restrict__ ci, const double* __restrict__ v,
+                                            unsigned long long* key, int* __restrict__ out) {
+    const int lane = threadIdx.x & (G - 1), base = threadIdx.x & (kWave - 1) & ~(G - 1);
+    const unsigned group = unsigned((1ull << G) - 1);
+    int u[E], code[E];
+    double a[E];
+    unsigned long long w[E];
+#pragma unroll
+    for (int t = 0; t < E; ++t) {
+        const int k = lane + G * t;
+        u[t] = k < L ? ci[e0 + k] : y;
+        a[t] = k < L ? v[e0 + k] : 0.0;
+    }
+    InitRow r{0, 0, false, false};
+#pragma unroll
+    for (int t = 0; t < E; ++t) {
+        code[t] = 0;
+        const bool off = u[t] != y;
+        const bool ok = off && init_code(rp, ci, y, u[t], code[t]);
+        const bool up = ok && u[t] > y;
+        w[t] = up ? weight_bits(a[t]) : 0;
+        key[lane + G * t] = w[t];
+        r.nlow += __popc(unsigned(__ballot(u[t] < y) >> base) & group);
+        r.nh += __popc(unsigned(__ballot(w[t] != 0) >> base) & group);
+        r.zero |= (unsigned(__ballot(up && w[t] == 0) >> base) & group) != 0;
+        r.bad |= (unsigned(__ballot(off && !ok) >> base) & group) != 0;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    int rank[E] = {};
+    for (int j = 0; j < L; j += 2) {  // a place past the row holds 0
+        const ulonglong2 q = *reinterpret_cast<const ulonglong2*>(key + j);
+#pragma unroll
+        for (int t = 0; t < E; ++t) {
+            const int k = lane + G * t;
+            rank[t] += (q.x > w[t] || (q.x == w[t] && j < k)) + (q.y > w[t] || (q.y == w[t] && j + 1 < k));
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < E; ++t)
+        if (w[t] != 0 && rank[t] < R) out[rank[t]] = code[t];
+    for (int q = lane; q < R; q += G)
+        if (q >= r.nh) out[q] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    return r;
+}
+
+template <int R, int G>
+__device__ __forceinline__ InitRow init_long_row(int y, int e0, int L, const int* __restrict__ rp,
+                                                 const int* __restrict__ ci, const double* __restrict__ v,
+                                                 int* __restrict__ out) {
+    const int lane = threadIdx.x & (G - 1);
+    InitRow r{0, 0, false, false};
+    for (int k = lane; k < L; k += G) {
+        const int u = ci[e0 + k];
+        r.nlow += u < y;
+        int code;
+        if (u == y) continue;
+        if (!init_code(rp, ci, y, u, code)) r.bad = true;
+        else if (u < y) continue;
+        else if (weight_bits(v[e0 + k]) == 0) r.zero = true;
+        else ++r.nh;
+    }
+#pragma unroll
+    for (int o = G / 2; o > 0; o >>= 1) {
+        r.nlow += __shfl_xor(r.nlow, o, G);
+        r.nh += __shfl_xor(r.nh, o, G);
+        r.zero |= __shfl_xor((int)r.zero, o, G) != 0;
+        r.bad |= __shfl_xor((int)r.bad, o, G) != 0;
+    }
+    unsigned long long pw = ~0ull;
+    int pk = -1;  // the entry taken last
+    for (int q = 0; q < R; ++q) {
+        unsigned long long bw = 0;
+        int bk = L;
+        for (int k = lane; k < L; k += G) {
+            if (ci[e0 + k] <= y) continue;
+            const unsigned long long w = weight_bits(v[e0 + k]);
+            if ((w < pw || (w == pw && k > pk)) && w > bw) {
+                bw = w;
+                bk = k;
+            }
+        }
+#pragma unroll
+        for (int o = G / 2; o > 0; o >>= 1) {
+            const unsigned long long ow = __shfl_xor(bw, o, G);
+            const int ok = __shfl_xor(bk, o, G);
+            if (ow > bw || (ow == bw && ok < bk)) {
+                bw = ow;
+                bk = ok;
+            }
+        }
+        int code = 0;
+        if (bw != 0) (void)init_code(rp, ci, y, ci[e0 + bk], code);
+        if (lane == 0) out[q] = code;
+        pw = bw;
+        pk = bk;
+    }
+    return r;
+}
+
+constexpr int kInitBlocks = 4096;   // two rounds of the chip
+constexpr int kInitThread = 32768;  // levels of few entries a row above this take a thread a row (7 us here, 13 against 7 at 65,536)
+}  // namespace
+
+template <int R, int G>
+__global__ __launch_bounds__(BS) void k_hem_init_group(int n, const int* __restrict__ rp, const int* __restrict__ ci,
+                                                       const double* __restrict__ v, int* __restrict__ rec,
+                                                       int2* __restrict__ deg, unsigned* __restrict__ gw,
+                                                       unsigned* __restrict__ xw, int* __restrict__ mate, int* cnt,
+                                                       int* err) {
+    __shared__ __align__(16) unsigned long long skey[2 * BS];
+    const int g = threadIdx.x / G, lane = threadIdx.x & (G - 1);
+    unsigned long long* key = skey + g * 2 * G;
+    for (int y = blockIdx.x * (BS / G) + g; y < n; y += gridDim.x * (BS / G)) {
+        const int e0 = rp[y], L = rp[y + 1] - e0;
+        int* out = rec + (size_t)y * R;
+        const InitRow r = L <= G       ? init_row<R, G, 1>(y, e0, L, rp, ci, v, key, out)
+                          : L <= 2 * G ? init_row<R, G, 2>(y, e0, L, rp, ci, v, key, out)
+                                       : init_long_row<R, G>(y, e0, L, rp, ci, v, out);
+        if (lane == 0) {
+            mate[y] = -1;
+            gw[y] = 0u;
+            int low = r.nlow;
+            if (r.nlow > kWordEdges) {  // extension: the number of lower entries, then their bits
+                const int words = (r.nlow + 31) / 32;
+                const int at = atomicAdd(&cnt[1], 1 + words);
+                xw[at] = (unsigned)r.nlow;
+                for (int k = 0; k < words; ++k)
+                    xw[at + 1 + k] = r.nlow - 32 * k >= 32 ? 0u : ~low_bits(r.nlow - 32 * k);
+                low = at | kWideFlag;
+            }
+            deg[y] = make_int2(low, r.nh | (r.zero ? kZeroFlag : 0));
+            if (r.bad) atomicOr(err, ERR_NONSYM);
+        }
     }
 }
 
@@ -931,13 +1101,12 @@ static int hem_record(int n, int64_t nnz, size_t room) {
 
 void launch_hem_init(int n, int64_t nnz, const int* rp, const int* ci, const double* v, HemWork& w, hipStream_t s) {
     w.side = hem_record(n, nnz, w.rec_ints);
-    const dim3 g(blocks_for(n));
-#define CALL(R)                                                                                                   \
-    hipLaunchKernelGGL(k_hem_init<R>, g, dim3(BS), 0, s, n, rp, ci, v, w.rec, w.deg, w.gw, w.xw, w.mate, w.cnt,   \
-                       w.err)
-    if (w.side == 4) CALL(4);
-    else if (w.side == 16) CALL(16);
-    else CALL(32);
+#define CALL(K, grid)                                                                                            \
+    hipLaunchKernelGGL(K, dim3(grid), dim3(BS), 0, s, n, rp, ci, v, w.rec, w.deg, w.gw, w.xw, w.mate, w.cnt, w.err)
+    if (w.side == 32) CALL((k_hem_init_group<32, 32>), blocks_for(n, BS / 32, kInitBlocks));
+    else if (w.side == 16) CALL((k_hem_init_group<16, 16>), blocks_for(n, BS / 16, kInitBlocks));
+    else if (n <= kInitThread) CALL((k_hem_init_group<4, 16>), blocks_for(n, BS / 16, kInitBlocks));
+    else CALL(k_hem_init, blocks_for(n));
 #undef CALL
 }
 
