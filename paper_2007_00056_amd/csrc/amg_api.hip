@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <atomic>
 #include <chrono>
+#include <climits>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -239,6 +240,23 @@ int2 read_int2(const int* d, hipStream_t s) {
     return make_int2(h[0], h[1]);
 }
 
+// Waits until the device has stored `value` to the mapped word: the host
+// watches it instead of blocking on the stream (some 15 us sooner).  After one
+// second it blocks, which also reports a failed kernel.
+void wait_word(const int* word, int value, hipStream_t s) {
+    const volatile int* w = word;
+    const auto t0 = std::chrono::steady_clock::now();
+    for (unsigned k = 1; *w != value; ++k) {
+        if ((k & 4095) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::seconds(1)) {
+            HIPCHK(hipStreamSynchronize(s));
+            if (*w != value) raise(AMG_EHIP, "amg_setup: a pass's sizes did not arrive");
+            break;
+        }
+        __builtin_ia32_pause();
+    }
+    std::atomic_thread_fence(std::memory_order_acquire);
+}
+
 void raise_err_word(int e, const char* where) {
     if (e & ERR_NONFINITE) raise(AMG_ENOTFINITE, "%s: matrix has a NaN or Inf value", where);
     if (e & ERR_STRUCT) raise(AMG_EINVAL, "%s: invalid CSR structure (row_ptr, column range or order)", where);
@@ -289,8 +307,7 @@ struct SetupWork {
     int* mate[2]{};
     int* agg[2]{};
     int* lead[2]{};
-    int* flag = nullptr;
-    int* ids = nullptr;
+    int* nc = nullptr;  // coarse rows
     int* stmp = nullptr;
     int* rowcnt = nullptr;
     int* ovf = nullptr;
@@ -304,7 +321,7 @@ struct SetupWork {
     int* mci = nullptr;
     double* mv = nullptr;
 
-    void init(int n, int64_t nnz, DevPool& P, int* err, bool edge_based, bool alternate) {
+    void init(int n, int64_t nnz, DevPool& P, int* err, bool edge_based, bool alternate, hipStream_t s) {
         edge = edge_based;
         if (edge) {
             hw.wsym = P.get<double>((size_t)nnz);
@@ -326,14 +343,14 @@ struct SetupWork {
             mv = P.get<double>((size_t)nnz);
         }
         hw.cnt = P.get<int>(8);
+        HIPCHK(hipMemsetAsync(hw.cnt, 0, 8 * sizeof(int), s));  // each pass leaves them cleared
         hw.err = err;
         for (int t = 0; t < 2; ++t) {
             mate[t] = P.get<int>(n);
             agg[t] = P.get<int>(n);
             lead[t] = P.get<int>(n);
         }
-        flag = P.get<int>(n);
-        ids = P.get<int>((size_t)n + 1);
+        nc = P.get<int>(1);
         stmp = P.get<int>(scan_tmp_ints(n));
         rowcnt = P.get<int>(n);
         ovf = P.get<int>(n);
@@ -413,7 +430,6 @@ Pass hem_pass(const Csr& Bin, SetupWork& W, int t, hipStream_t s, bool from_last
         B.v = W.mv;
         w.mate = W.agg[t];  // free until numbering writes the aggregate map
     }
-    HIPCHK(hipMemsetAsync(w.cnt, 0, 8 * sizeof(int), s));
     if (W.edge) {
         launch_ehem_init(n, B.rp, B.ci, B.v, w, s);
         run_rounds(W, w, n, s, [&](int r) { launch_ehem_round(r, n, B.rp, B.ci, w, s); });
@@ -434,9 +450,7 @@ Pass hem_pass(const Csr& Bin, SetupWork& W, int t, hipStream_t s, bool from_last
     P.cnt = w.cnt;
     // coarse ids: rank of each aggregate's smaller vertex; the count stays on
     // the device until the Galerkin product reads it back with its own sizes
-    launch_leader_flags(n, w.mate, W.flag, s);
-    launch_scan(W.flag, n, W.ids, W.stmp, s);
-    launch_assign_ids(n, w.mate, W.ids, P.agg, P.lead, s);
+    launch_numbering(n, w.mate, P.agg, P.lead, W.nc, W.novf, W.stmp, s);
     HIPCHK(hipGetLastError());
     return P;
 }
@@ -448,20 +462,18 @@ Pass hem_pass(const Csr& Bin, SetupWork& W, int t, hipStream_t s, bool from_last
 // `late`: the matching ran past its time limit (nothing is formed then).
 Csr galerkin(const Csr& B, Pass& P, SetupWork& W, DevPool& out, hipStream_t s, const int* err, int*& crp, bool& late) {
     const int nmax = P.n;  // coarse rows <= fine rows
-    const int* ncp = W.ids + P.n;
-    HIPCHK(hipMemsetAsync(W.novf, 0, sizeof(int), s));
-    launch_rap_count(nmax, B.nnz, ncp, P.lead, P.mate, B.rp, B.ci, P.agg, W.rowcnt, W.ovf, W.novf, s);
+    launch_rap_count(nmax, B.nnz, W.nc, P.lead, P.mate, B.rp, B.ci, P.agg, W.rowcnt, W.ovf, W.novf, s);
     launch_rap_count_slow(nmax, W.ovf, W.novf, P.lead, P.mate, B.rp, B.ci, P.agg, W.rowcnt, s);
     Csr C;
     if (!crp) crp = out.get<int>((size_t)nmax + 1);
     C.rp = crp;
-    launch_scan(W.rowcnt, nmax, C.rp, W.stmp, s);
-    HIPCHK(hipGetLastError());
     int* dw = nullptr;
     int* hw = pinned_words(&dw);
-    launch_pass_words(dw, P.cnt, ncp, C.rp + nmax, err, W.novf, s);  // one launch in place of four copies
+    thread_local int seq = 0;  // the words belong to the thread
+    seq = seq == INT_MAX ? 1 : seq + 1;
+    launch_offsets(nmax, W.rowcnt, C.rp, PassWords{dw, P.cnt, W.nc, err, W.novf, seq}, W.stmp, s);
     HIPCHK(hipGetLastError());
-    HIPCHK(hipStreamSynchronize(s));
+    wait_word(hw + kPassSeq, seq, s);
     raise_err_word(hw[10], "amg_setup");
     if (hw[5] != 0) raise(AMG_EINVAL, "matching: sparsity pattern is not structurally symmetric");
     late = hw[7] != 0;
@@ -1211,7 +1223,7 @@ void setup_impl(const amg_csr* Ain, const amg_params* pin, const amg_allocator* 
     } wg{wpool};
     SetupWork SW;
     if (A.n > p.max_coarse_rows && p.max_levels > 1)
-        SW.init(A.n, A.nnz, wpool, h->err, p.hem == 1, p.alternate == 1);
+        SW.init(A.n, A.nnz, wpool, h->err, p.hem == 1, p.alternate == 1, s);
     // timing events around every matching pass (start/end pairs), read once
     // the setup has synchronised
     std::vector<hipEvent_t> pev;
@@ -1597,7 +1609,7 @@ void batch_coarsen(const amg_csr* A, int count, const amg_params& p, hipStream_t
         ~WpoolGuard() { t.release(); }
     } wg{wpool};
     SetupWork SW;
-    SW.init((int)N, E, wpool, gerr, p.hem == 1, p.alternate == 1);
+    SW.init((int)N, E, wpool, gerr, p.hem == 1, p.alternate == 1, s);
     int* starts = P.get<int>(2 * (size_t)count);
     int* offs_d = P.get<int>((size_t)count);
     std::vector<int> hs(2 * (size_t)count + 2), ho((size_t)count);

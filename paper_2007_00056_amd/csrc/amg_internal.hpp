@@ -66,17 +66,22 @@ void launch_hem_tile(int n, const int* rp, const int* ci, const double* v, HemWo
 void launch_ehem_init(int n, const int* rp, const int* ci, const double* v, HemWork& w, hipStream_t s);
 void launch_ehem_round(int r, int n, const int* rp, const int* ci, HemWork& w, hipStream_t s);
 
-// Exclusive prefix sum: out[i] = sum in[0..i), out[n] = total.  tmp: scan_tmp_ints(n).
-size_t scan_tmp_ints(int n);
-// out[0..7] = cnt[0..7], out[8] = *ncp, out[9] = *nnzc, out[10] = *err (out: a
-// device address of mapped host memory).
-void launch_pass_words(int* out, const int* cnt, const int* ncp, const int* nnzc, const int* err, const int* novf,
-                       hipStream_t s);
-void launch_scan(const int* in, int n, int* out, int* tmp, hipStream_t s);
-void launch_leader_flags(int n, const int* mate, int* flag, hipStream_t s);
-// agg[v] = id of v's aggregate; lead[id] = smaller vertex of the aggregate.
-void launch_assign_ids(int n, const int* mate, const int* ids, int* agg, int* lead, hipStream_t s);
-
+size_t scan_tmp_ints(int n);  // scratch of the two prefix sums below
+// What a pass hands to the host.
+constexpr int kPassSeq = 12;  // place of the sequence word in `out`
+struct PassWords {
+    int* out;        // mapped host memory: cnt[0 .. 7], *nc, the entry count, *err, *novf, seq
+    int* cnt;        // cleared after
+    const int* nc;
+    const int* err;
+    const int* novf;
+    int seq;
+};
+// From the mates: agg[v] = id of v's aggregate, lead[id] = smaller vertex of
+// the aggregate, the coarse row count; *novf = 0.
+void launch_numbering(int n, const int* mate, int* agg, int* lead, int* nc, int* novf, int* tmp, hipStream_t s);
+// crp[0 .. n] = exclusive sums of the counts, and the pass's words.
+void launch_offsets(int n, const int* rowcnt, int* crp, const PassWords& w, int* tmp, hipStream_t s);
 // Galerkin product of one matching pass (aggregates of size <= 2).
 // n, nnz: rows and entries of the fine operator
 void launch_rap_count(int nmax, int64_t nnz, const int* ncp, const int* lead, const int* mate, const int* rp,

@@ -139,11 +139,23 @@ void launch_dinv(int n, const int* rp, const int* ci, const double* v, double* d
 }
 
 // ---------------------------------------------------------------------------
-// Exclusive prefix sum (three phases: tile sums, scan of tile sums, apply).
+// The two exclusive prefix sums of a pass, with what precedes and follows them
+// in the same kernels:
+//   numbering   over the leader flags; hands out the coarse ids.  Algorithm 2
+//               does so when the smaller vertex of a pair (or a singleton) is
+//               visited: ids are ranks of the aggregates' minimum vertex.
+//   row offsets over the coarse rows' entry counts; hands the host its words.
+// Up to ONE_MAX items one workgroup does all of it in one launch (9 us at
+// 14,000 rows, 4 up to 4096, where flags, three scan phases and assignment took
+// five kernels of 3-5 us each); above, three phases: tile sums, scan of the
+// tile sums, apply.
 // ---------------------------------------------------------------------------
 namespace {
 constexpr int SCAN_ITEMS = 8;
 constexpr int SCAN_TILE = BS * SCAN_ITEMS;
+constexpr int ONE_BS = 1024;
+constexpr int ONE_TILES = 4;
+constexpr int ONE_MAX = ONE_TILES * 4 * ONE_BS;
 
 __device__ __forceinline__ int block_excl_scan(int x, int& total) {
     __shared__ int sh[BS / kWave];
@@ -167,14 +179,121 @@ __device__ __forceinline__ int block_excl_scan(int x, int& total) {
     __syncthreads();
     return pre + inc - x;
 }
+
+// Numbering: item v is 1 where v leads its aggregate.
+struct Numbering {
+    const int* __restrict__ mate;
+    int* __restrict__ agg;
+    int* __restrict__ lead;
+    int* __restrict__ total;  // coarse rows
+    int* novf;                // cleared for the Galerkin product
+    __device__ __forceinline__ int load(int v) const { return mate[v]; }
+    __device__ __forceinline__ int value(int v, int m) const { return m < 0 || v < m; }
+    __device__ __forceinline__ void put(int v, int m, int id) const {
+        if (m >= 0 && m < v) return;
+        agg[v] = id;
+        if (m >= 0) agg[m] = id;
+        lead[id] = v;
+    }
+    // by one wave of one block, once the total is known
+    __device__ __forceinline__ void finish(int n, int sum) const {
+        if (threadIdx.x != 0) return;
+        *total = sum;
+        *novf = 0;
+    }
+};
+
+// Row offsets, and the words a pass hands to the host (mapped memory): the
+// matching's 8 counters, cleared for the next pass, the coarse row count, the
+// coarse entry count, the error word and the Galerkin product's overflow rows;
+// then seq (system scope).
+struct Offsets {
+    const int* __restrict__ cnt;
+    int* __restrict__ crp;
+    PassWords w;
+    __device__ __forceinline__ int load(int i) const { return cnt[i]; }
+    __device__ __forceinline__ int value(int, int c) const { return c; }
+    __device__ __forceinline__ void put(int i, int, int at) const { crp[i] = at; }
+    __device__ __forceinline__ void finish(int n, int sum) const {
+        const int t = threadIdx.x;
+        if (t >= kWave) return;
+        if (t < 8) {
+            w.out[t] = w.cnt[t];
+            w.cnt[t] = 0;
+        } else if (t == 8) {
+            w.out[8] = *w.nc;
+        } else if (t == 9) {
+            w.out[9] = sum;
+            crp[n] = sum;
+        } else if (t == 10) {
+            w.out[10] = *w.err;
+        } else if (t == 11) {
+            w.out[11] = *w.novf;
+        }
+        __threadfence_system();  // the wave's words before the sequence word
+        if (t == 0) __hip_atomic_store(&w.out[kPassSeq], w.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+};
 }  // namespace
 
-__global__ __launch_bounds__(BS) void k_scan_tiles(const int* __restrict__ in, int n, int* __restrict__ tsum) {
+// One workgroup: a thread holds 4 neighbouring items of each of T tiles.
+template <int T, class Op>
+__global__ __launch_bounds__(ONE_BS) void k_scan_one(int n, Op op) {
+    constexpr int NW = ONE_BS / kWave;
+    __shared__ int sums[T * NW];
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    int raw[T][4], pre[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) raw[t][j] = op.load(min((t * ONE_BS + (int)threadIdx.x) * 4 + j, n - 1));
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const int i = (t * ONE_BS + threadIdx.x) * 4;
+        int x = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x += i + j < n ? op.value(i + j, raw[t][j]) : 0;
+        int inc = x;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int y = __shfl_up(inc, off, kWave);
+            if (lane >= off) inc += y;
+        }
+        if (lane == kWave - 1) sums[t * NW + wid] = inc;
+        pre[t] = inc - x;
+    }
+    __syncthreads();
+    static_assert(T * NW <= kWave, "a sum a lane");
+    // every wave scans the waves' sums for itself
+    const int own = lane < T * NW ? sums[lane] : 0;
+    int inc = own;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const int y = __shfl_up(inc, off, kWave);
+        if (lane >= off) inc += y;
+    }
+    const int total = __shfl(inc, kWave - 1, kWave);
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        int ex = pre[t] + __shfl(inc - own, t * NW + wid, kWave);
+        const int i = (t * ONE_BS + threadIdx.x) * 4;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (i + j >= n) continue;
+            op.put(i + j, raw[t][j], ex);
+            ex += op.value(i + j, raw[t][j]);
+        }
+    }
+    op.finish(n, total);
+}
+
+template <class Op>
+__global__ __launch_bounds__(BS) void k_scan_tiles(int n, Op op, int* __restrict__ tsum) {
     const int base = blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_ITEMS;
     int s = 0;
 #pragma unroll
     for (int t = 0; t < SCAN_ITEMS; ++t)
-        if (base + t < n) s += in[base + t];
+        if (base + t < n) s += op.value(base + t, op.load(base + t));
     int total;
     block_excl_scan(s, total);
     if (threadIdx.x == 0) tsum[blockIdx.x] = total;
@@ -193,81 +312,49 @@ __global__ __launch_bounds__(BS) void k_scan_top(int* tsum, int nt) {
     if (threadIdx.x == 0) tsum[nt] = carry;
 }
 
-__global__ __launch_bounds__(BS) void k_scan_apply(const int* __restrict__ in, int n, const int* __restrict__ tsum,
-                                                   int nt, int* __restrict__ out) {
+template <class Op>
+__global__ __launch_bounds__(BS) void k_scan_apply(int n, Op op, const int* __restrict__ tsum, int nt) {
     const int base = blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_ITEMS;
-    int loc[SCAN_ITEMS];
+    int raw[SCAN_ITEMS];
     int s = 0;
 #pragma unroll
     for (int t = 0; t < SCAN_ITEMS; ++t) {
-        loc[t] = base + t < n ? in[base + t] : 0;
-        s += loc[t];
+        raw[t] = op.load(min(base + t, n - 1));
+        s += base + t < n ? op.value(base + t, raw[t]) : 0;
     }
     int total;
     int ex = block_excl_scan(s, total) + tsum[blockIdx.x];
 #pragma unroll
     for (int t = 0; t < SCAN_ITEMS; ++t) {
-        if (base + t < n) out[base + t] = ex;
-        ex += loc[t];
+        if (base + t >= n) continue;
+        op.put(base + t, raw[t], ex);
+        ex += op.value(base + t, raw[t]);
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = tsum[nt];
-}
-
-// The words a pass hands to the host, gathered by one small launch: the
-// matching's 8 counters, the coarse row count, the coarse entry count, the
-// error word and the Galerkin product's overflow rows.
-__global__ void k_pass_words(int* __restrict__ out, const int* __restrict__ cnt, const int* __restrict__ ncp,
-                             const int* __restrict__ nnzc, const int* __restrict__ err,
-                             const int* __restrict__ novf) {
-    const int t = threadIdx.x;
-    if (t < 8) out[t] = cnt[t];
-    else if (t == 8) out[8] = *ncp;
-    else if (t == 9) out[9] = *nnzc;
-    else if (t == 10) out[10] = *err;
-    else if (t == 11) out[11] = *novf;
-}
-
-void launch_pass_words(int* out, const int* cnt, const int* ncp, const int* nnzc, const int* err, const int* novf,
-                       hipStream_t s) {
-    hipLaunchKernelGGL(k_pass_words, dim3(1), dim3(kWave), 0, s, out, cnt, ncp, nnzc, err, novf);
+    if (blockIdx.x == 0) op.finish(n, tsum[nt]);
 }
 
 size_t scan_tmp_ints(int n) { return (size_t)(n + SCAN_TILE - 1) / SCAN_TILE + 1; }
 
-void launch_scan(const int* in, int n, int* out, int* tmp, hipStream_t s) {
-    const int nt = (n + SCAN_TILE - 1) / SCAN_TILE;
-    if (nt > 0) hipLaunchKernelGGL(k_scan_tiles, dim3(nt), dim3(BS), 0, s, in, n, tmp);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(BS), 0, s, tmp, nt);
-    hipLaunchKernelGGL(k_scan_apply, dim3(nt > 0 ? nt : 1), dim3(BS), 0, s, in, n, tmp, nt, out);
+template <class Op>
+static void scan_launch(int n, const Op& op, int* tmp, hipStream_t s) {
+    if (n <= 4 * ONE_BS) {
+        hipLaunchKernelGGL((k_scan_one<1, Op>), dim3(1), dim3(ONE_BS), 0, s, n, op);
+    } else if (n <= ONE_MAX) {
+        hipLaunchKernelGGL((k_scan_one<ONE_TILES, Op>), dim3(1), dim3(ONE_BS), 0, s, n, op);
+    } else {
+        const int nt = (n + SCAN_TILE - 1) / SCAN_TILE;
+        hipLaunchKernelGGL(k_scan_tiles<Op>, dim3(nt), dim3(BS), 0, s, n, op, tmp);
+        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(BS), 0, s, tmp, nt);
+        hipLaunchKernelGGL(k_scan_apply<Op>, dim3(nt), dim3(BS), 0, s, n, op, tmp, nt);
+    }
 }
 
-// Algorithm 2 hands out coarse ids when the smaller vertex of a pair (or a
-// singleton) is visited: ids are ranks of the aggregates' minimum vertex.
-__global__ __launch_bounds__(BS) void k_leader_flags(int n, const int* __restrict__ mate, int* __restrict__ flag) {
-    const int v = blockIdx.x * BS + threadIdx.x;
-    if (v >= n) return;
-    const int m = mate[v];
-    flag[v] = (m < 0 || v < m) ? 1 : 0;
+void launch_numbering(int n, const int* mate, int* agg, int* lead, int* nc, int* novf, int* tmp, hipStream_t s) {
+    scan_launch(n, Numbering{mate, agg, lead, nc, novf}, tmp, s);
 }
 
-__global__ __launch_bounds__(BS) void k_assign_ids(int n, const int* __restrict__ mate, const int* __restrict__ ids,
-                                                   int* __restrict__ agg, int* __restrict__ lead) {
-    const int v = blockIdx.x * BS + threadIdx.x;
-    if (v >= n) return;
-    const int m = mate[v];
-    if (m >= 0 && m < v) return;
-    const int id = ids[v];
-    agg[v] = id;
-    if (m >= 0) agg[m] = id;
-    lead[id] = v;
-}
-
-void launch_leader_flags(int n, const int* mate, int* flag, hipStream_t s) {
-    hipLaunchKernelGGL(k_leader_flags, dim3(blocks_for(n)), dim3(BS), 0, s, n, mate, flag);
-}
-
-void launch_assign_ids(int n, const int* mate, const int* ids, int* agg, int* lead, hipStream_t s) {
-    hipLaunchKernelGGL(k_assign_ids, dim3(blocks_for(n)), dim3(BS), 0, s, n, mate, ids, agg, lead);
+void launch_offsets(int n, const int* rowcnt, int* crp, const PassWords& w, int* tmp, hipStream_t s) {
+    scan_launch(n, Offsets{rowcnt, crp, w}, tmp, s);
 }
 
 // ---------------------------------------------------------------------------
