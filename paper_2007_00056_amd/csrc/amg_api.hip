@@ -647,10 +647,11 @@ void build_tail(amg_hier* h, hipStream_t s) {
     }
     if (k >= L || !tail_prepare()) return;
     h->tail = k;
+    K.nl = L - k;
     K.blob = h->pool.get<char>(16 * (size_t)A.words);
     for (int l = k; l < L; ++l) {
         const VLevel<T> V = vlevel<T>(h, h->lev[l]);
-        K.src[l - k] = TailSrc<T>{V.rp, V.ci, V.v, V.dinv, V.mem, (int)nnz[l]};
+        K.src[l - k] = TailSrc<T>{V.rp, V.ci, V.v, V.dinv, V.mem, (int)nnz[l], 0, 0, 0, nullptr, nullptr};
     }
     launch_tail_pack<T>(K, L - k, s);
     HIPCHK(hipGetLastError());

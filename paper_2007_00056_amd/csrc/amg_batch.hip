@@ -22,6 +22,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <memory>
+#include <type_traits>
 #include <vector>
 
 #include "amg_host.hpp"
@@ -54,12 +55,14 @@ struct BLev {
 
 struct BSeg {
     amg_status status = AMG_OK;  // a system whose setup failed takes no rows
-    int nlev = 0;
+    int nlev = 0;    // levels of the system
+    int lay = 0;     // levels of it in the batch: the last one goes to the coarsest or the tail solve
     int n0 = 0;     // level-0 rows
     int off0 = 0;   // first level-0 row
     int m = 0;      // coarsest rows
-    int cl = 0;     // coarsest level
-    int crow0 = 0;  // first coarsest row in the level-cl vectors
+    int cl = 0;     // last level in the batch (lay - 1)
+    int crow0 = 0;  // first row of it in the level-cl vectors
+    bool tail = false;  // levels cl and below run in one workgroup
 };
 
 template <class F>
@@ -99,6 +102,9 @@ struct amg_batch {
     int* act = nullptr;   // systems still iterating
     int* mark = nullptr;  // systems whose residual is recomputed
     int* all = nullptr;   // every system
+    int nlev = 0;         // levels of the deepest system
+    void* tjobs = nullptr;  // TailJob<T>[ntail]
+    int ntail = 0, tail_lds = 0;
     void* dd = nullptr;   // BDense<T>[nseg]
     int2* dtab = nullptr;
     double* ainv = nullptr;
@@ -184,7 +190,8 @@ void batch_vcycle(const amg_batch* B, const double* r, double* z, hipStream_t s)
         else vc_stream_resid<T, T>(view(k), vec(L.f), gk(k), w, vec(L.t), s);
         vc_restrict<T>(C.V, L.mem, vec(L.t), dinvs<T>(C), vec(C.f), vec(C.g), s);
     }
-    launch_bdense<T>(B->ndblk, static_cast<const BDense<T>*>(B->dd), B->dtab, s);
+    if (B->ndblk) launch_bdense<T>(B->ndblk, static_cast<const BDense<T>*>(B->dd), B->dtab, s);
+    if (B->ntail) vc_tails<T>(static_cast<const TailJob<T>*>(B->tjobs), B->ntail, B->tail_lds, s);
     for (int k = K - 2; k >= 1; --k) {
         const BLev& L = B->lev[k];
         const ScatterT<T> sc{B->lev[k - 1].mem, gk(k - 1), vec(B->lev[k - 1].xp), w};
@@ -643,7 +650,7 @@ void build_dense(amg_batch* B, std::vector<char>& host, size_t at_dd, size_t at_
     int nb = 0;
     for (int i = 0; i < B->nseg; ++i) {
         const BSeg& g = B->seg[i];
-        if (g.status != AMG_OK) {
+        if (g.status != AMG_OK || g.tail) {
             dd[i] = BDense<T>{};
             continue;
         }
@@ -658,6 +665,104 @@ void build_dense(amg_batch* B, std::vector<char>& host, size_t at_dd, size_t at_
                           ScatterT<T>{F.mem, gf, static_cast<T*>(F.xp), w}};
         for (int c = 0; c * 64 < g.m; ++c) dtab[nb++] = make_int2(i, c);
     }
+}
+
+// The systems whose small levels run in one workgroup (each in its own), their
+// packed operators and jobs.  Whether a system's do depends on it alone, and
+// its rows add in the order of the level kernels, so its results are the same
+// in every batch.
+template <class T>
+struct TailPlan {
+    std::vector<int> sys, words;
+    std::vector<TailPack<T>> pack;
+    std::vector<TailJob<T>> job;
+    int lds = 0, nl = 0;
+    size_t blob = 0;  // bytes
+};
+
+constexpr int kTailSystems = 1024;  // larger batches fill the device with the level kernels
+
+template <class T>
+void plan_tails(amg_batch* B, const std::vector<SegSrc>& src, TailPlan<T>& P) {
+    const char* e = getenv("HEMAMG_TAIL");
+    const int most = e ? atoi(e) : 1 << 30;
+    if (B->nseg > kTailSystems || !tail_prepare()) return;
+    for (int i = 0; i < B->nseg; ++i) {
+        BSeg& g = B->seg[i];
+        if (g.status != AMG_OK) continue;
+        const int L = g.nlev - 1;
+        std::vector<int> n;
+        std::vector<int64_t> nnz;
+        for (const SegLevelSrc& l : src[i].lev) {
+            n.push_back(l.n);
+            nnz.push_back(l.nnz);
+        }
+        TailPack<T> K{};
+        TailJob<T> J{};
+        for (int k = 1; k < L; ++k) {
+            const int lds = tail_layout<T>(&n[k], &nnz[k], nullptr, L - k, J.a, K.lev);
+            if (lds == 0 || lds > most) continue;
+            g.tail = true;
+            g.cl = k;
+            g.lay = k + 1;
+            K.nl = L - k;
+            for (int l = k; l < L; ++l) {
+                const SegLevelSrc& H = src[i].lev[l];
+                TailSrc<T>& S = K.src[l - k];
+                S = TailSrc<T>{H.rp, H.ci, nullptr, nullptr, H.mem, (int)H.nnz, H.rp_add, H.ci_add, H.mem_add, H.v, H.dinv};
+                if constexpr (std::is_same<T, float>::value) {
+                    S.v = H.v32;
+                    S.dinv = H.dinv32;
+                } else {
+                    S.v = H.v;
+                    S.dinv = H.dinv;
+                }
+            }
+            P.lds = std::max(P.lds, lds);
+            P.nl = std::max(P.nl, K.nl);
+            P.sys.push_back(i);
+            P.words.push_back(J.a.words);
+            P.blob += 16 * (size_t)J.a.words;
+            P.pack.push_back(K);
+            P.job.push_back(J);
+            break;
+        }
+    }
+}
+
+// Fills in the addresses, uploads the tables and packs the operators.
+template <class T>
+void build_tails(amg_batch* B, TailPlan<T>& P, const std::vector<size_t>& aoff, std::vector<char>& host,
+                 hipStream_t s) {
+    const size_t count = P.sys.size();
+    if (count == 0) return;
+    char* blob = B->pool.get<char>(P.blob);
+    for (size_t t = 0; t < count; ++t) {
+        const BSeg& g = B->seg[P.sys[t]];
+        const BLev& C = B->lev[g.cl];
+        const BLev& F = B->lev[g.cl - 1];
+        TailJob<T>& J = P.job[t];
+        P.pack[t].blob = blob;
+        J.a.blob = reinterpret_cast<const uint4*>(blob);
+        blob += 16 * (size_t)P.words[t];
+        J.a.ainv = B->ainv + aoff[P.sys[t]];
+        J.a.f = static_cast<const T*>(C.f) + g.crow0;
+        J.a.g = static_cast<const T*>(C.g) + g.crow0;
+        J.a.w = T(B->omega);
+        const T* gf = g.cl - 1 == 0 ? static_cast<const T*>(B->g0) : static_cast<const T*>(F.g);
+        J.sc = ScatterT<T>{F.mem + g.crow0, gf, static_cast<T*>(F.xp), T(B->omega)};
+    }
+    const size_t jb = sizeof(TailJob<T>) * count, pb = sizeof(TailPack<T>) * count;
+    host.resize(jb + pb);
+    std::memcpy(host.data(), P.job.data(), jb);
+    std::memcpy(host.data() + jb, P.pack.data(), pb);
+    char* dev = B->pool.get<char>(jb + pb);
+    HIPCHK(hipMemcpyAsync(dev, host.data(), jb + pb, hipMemcpyHostToDevice, s));
+    launch_tail_packs<T>(reinterpret_cast<const TailPack<T>*>(dev + jb), (int)count, P.nl, s);
+    HIPCHK(hipGetLastError());
+    B->tjobs = dev;
+    B->ntail = (int)count;
+    B->tail_lds = P.lds;
 }
 
 // Lays out a batch from the systems' levels wherever they are stored (see
@@ -679,18 +784,34 @@ void create_impl(const std::vector<SegSrc>& src, bool prec32, double omega, int 
     B->pool.s = s;
     B->pool.al = al;
     const int ns = count;
-    int K = 0;
-    for (int i = 0; i < ns; ++i) K = std::max(K, (int)src[i].lev.size());
-    if (K < 2) raise(AMG_EINVAL, "amg_batch: no system with two or more levels");
-    B->lev.resize(K);
     B->seg.resize(ns);
+    for (int i = 0; i < ns; ++i) {
+        BSeg& g = B->seg[i];
+        const int nl = (int)src[i].lev.size();
+        B->nlev = std::max(B->nlev, nl);
+        g.status = nl >= 2 ? src[i].status : (src[i].status != AMG_OK ? src[i].status : AMG_EINVAL);
+        if (g.status != AMG_OK) continue;  // no rows, no levels
+        g.nlev = g.lay = nl;
+        g.cl = nl - 1;
+        g.n0 = src[i].lev[0].n;
+        g.m = src[i].lev[nl - 1].n;
+    }
+    if (B->nlev < 2) raise(AMG_EINVAL, "amg_batch: no system with two or more levels");
+    TailPlan<float> tp32;
+    TailPlan<double> tp64;
+    if (prec32) plan_tails<float>(B.get(), src, tp32);
+    else plan_tails<double>(B.get(), src, tp64);
+    int K = 0;
+    for (const BSeg& g : B->seg) K = std::max(K, g.lay);
+    if (K < 2) K = 2;  // every system failed
+    B->lev.resize(K);
     // layouts: pos[k][i] = first row of system i in the level-k vectors
     std::vector<std::vector<int>> pos(K, std::vector<int>(ns, -1));
     std::vector<std::vector<int64_t>> epos(K, std::vector<int64_t>(ns, 0));
     for (int k = 0; k < K; ++k) {
         BLev& L = B->lev[k];
         for (int i = 0; i < ns; ++i) {
-            const int nl = (int)src[i].lev.size();
+            const int nl = B->seg[i].lay;
             if (k == 0) pos[k][i] = L.n;  // a failed system sits empty at its place
             if (k <= nl - 2) {
                 pos[k][i] = L.n;
@@ -701,7 +822,7 @@ void create_impl(const std::vector<SegSrc>& src, bool prec32, double omega, int 
         }
         L.V = L.n;
         for (int i = 0; i < ns; ++i) {
-            if ((int)src[i].lev.size() - 1 == k) {
+            if (B->seg[i].lay - 1 == k) {
                 pos[k][i] = L.V;
                 L.V += src[i].lev[k].n;
             }
@@ -711,14 +832,8 @@ void create_impl(const std::vector<SegSrc>& src, bool prec32, double omega, int 
     }
     for (int i = 0; i < ns; ++i) {
         BSeg& g = B->seg[i];
-        g.status = src[i].lev.size() >= 2 ? src[i].status : (src[i].status != AMG_OK ? src[i].status : AMG_EINVAL);
         g.off0 = pos[0][i];
-        if (g.status != AMG_OK) continue;  // no rows, no levels
-        g.nlev = (int)src[i].lev.size();
-        g.n0 = src[i].lev[0].n;
-        g.cl = g.nlev - 1;
-        g.m = src[i].lev[g.cl].n;
-        g.crow0 = pos[g.cl][i];
+        if (g.status == AMG_OK) g.crow0 = pos[g.cl][i];
     }
     B->n0 = B->lev[0].n;
     const size_t esz = B->prec32 ? 4 : 8;
@@ -768,7 +883,8 @@ void create_impl(const std::vector<SegSrc>& src, bool prec32, double omega, int 
     for (int i = 0; i < ns; ++i) segblk[i + 1] = segblk[i] + (B->seg[i].n0 + 255) / 256;
     B->nblk = segblk[ns];
     int ndb = 0;
-    for (int i = 0; i < ns; ++i) ndb += (B->seg[i].m + 63) / 64;
+    for (int i = 0; i < ns; ++i)
+        if (!B->seg[i].tail) ndb += (B->seg[i].m + 63) / 64;
     B->ndblk = ndb;
     B->part = P.get<double>(2 * (size_t)B->nblk);
     B->S = P.get<double>((size_t)ns * kBatchSlots);
@@ -781,12 +897,12 @@ void create_impl(const std::vector<SegSrc>& src, bool prec32, double omega, int 
         BLev& L = B->lev[k];
         int last = -1;
         for (int i = 0; i < ns; ++i)
-            if (k <= B->seg[i].nlev - 2) last = i;
+            if (k <= B->seg[i].lay - 2) last = i;
         for (int i = 0; i < ns; ++i) {
             const BSeg& g = B->seg[i];
-            if (k >= g.nlev) continue;
+            if (k >= g.lay) continue;
             const SegLevelSrc& H = src[i].lev[k];
-            if (k <= g.nlev - 2) {
+            if (k <= g.lay - 2) {
                 const int o = pos[k][i];
                 piece(H.rp, L.rp + o, (int64_t)H.n + (i == last ? 1 : 0), (int)epos[k][i] + H.rp_add, 0);
                 piece(H.ci, L.ci + epos[k][i], H.nnz, o + H.ci_add, 0);
@@ -862,6 +978,9 @@ void create_impl(const std::vector<SegSrc>& src, bool prec32, double omega, int 
     launch_gather((int)gtab.size(), reinterpret_cast<const GatherPiece*>(dev + at_pcs),
                   reinterpret_cast<const int2*>(dev + at_gtab), s);
     HIPCHK(hipGetLastError());
+    std::vector<char> thost;
+    if (B->prec32) build_tails<float>(B.get(), tp32, aoff, thost, s);
+    else build_tails<double>(B.get(), tp64, aoff, thost, s);
     // pinned host memory for the scalars and masks: a block of the pinned
     // pool when it fits (pinned allocation costs about a millisecond)
     const size_t pin = sizeof(double) * kBatchSlots * ns + sizeof(int) * ns;
@@ -931,6 +1050,7 @@ void batch_autotune(amg_batch* B, hipStream_t caller, int32_t* out) {
         L.rb = pick;
         if (out) out[k] = pick;
     }
+    for (int k = K - 1; out && k < B->nlev; ++k) out[k] = k + 1 < B->nlev ? 256 : 0;  // in one workgroup: no choice
     for (hipGraphExec_t* gs : {B->graph, B->bgraph})  // re-captured with the new launch shapes
         for (int k = 0; k < 2; ++k)
             if (gs[k]) {
@@ -1136,7 +1256,7 @@ amg_status amg_batch_set_graphs(amg_batch* b, int32_t on) {
 amg_status amg_batch_levels(const amg_batch* b, int32_t* levels) {
     return guarded([&] {
         if (!b || !levels) raise(AMG_EINVAL, "amg_batch_levels: NULL argument");
-        *levels = (int32_t)b->lev.size();
+        *levels = (int32_t)b->nlev;
     });
 }
 

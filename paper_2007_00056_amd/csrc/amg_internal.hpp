@@ -237,8 +237,15 @@ struct TailArgs {
     int words;           // 16-byte words of the block
     int nl, n0, m;       // smoothing levels; finest and coarsest rows
     int g0, a0, gm, am;  // their vectors
-    int dense_log, part; // log2 of the threads per column of the coarsest solve; its partial sums
+    int part;            // partial sums of the coarsest solve
 };
+template <class T>
+struct TailJob {
+    TailArgs<T> a;
+    ScatterT<T> sc;
+};
+// A level's arrays; the `add`s give the system's own numbering.  v or dinv
+// null: rounded from the double ones.
 template <class T>
 struct TailSrc {
     const int* rp;
@@ -247,21 +254,32 @@ struct TailSrc {
     const T* dinv;
     const int4* mem;
     int nnz;
+    int rp_add, ci_add, mem_add;
+    const double* v64;
+    const double* dinv64;
 };
 template <class T>
 struct TailPack {
     char* blob;
+    int nl;
     TailSrc<T> src[kTailLevels];
     TailLevel lev[kTailLevels];
 };
 // n[0 .. nl], nnz and lanes per row [0 .. nl - 1]: the LDS bytes of the cycle on these levels, or
-// 0 when it does not fit; fills lev[0 .. nl - 1] and A (not its pointers).
+// 0 when it does not fit; fills lev[0 .. nl - 1] and A (not its pointers).  lpr
+// null: for the CSR-stream kernels' order.
 template <class T>
 int tail_layout(const int* n, const int64_t* nnz, const int* lpr, int nl, TailArgs<T>& A, TailLevel* lev);
 template <class T>
 void launch_tail_pack(const TailPack<T>& K, int nl, hipStream_t s);
 template <class T>
 void vc_tail(const TailArgs<T>& A, int lds, const ScatterT<T>& sc, hipStream_t s);
+// Many systems at once: jobs and packs in device memory, nl the most levels of
+// a system.
+template <class T>
+void launch_tail_packs(const TailPack<T>* K, int count, int nl, hipStream_t s);
+template <class T>
+void vc_tails(const TailJob<T>* jobs, int count, int lds, hipStream_t s);
 bool tail_prepare();  // whether the device takes the tail kernels
 
 // S[slot0] (and S[slot1] when nv = 2) = fixed-order sums of the partials.

@@ -28,7 +28,8 @@ namespace {
 
 constexpr int BS = 1024;
 constexpr int kStage = 9;        // 16-byte words of the block a thread may load (as 8 or fewer the compiler spills them)
-constexpr int kAinvHeld = 16;    // entries of the inverse a thread holds: all up to 128 coarsest rows
+constexpr int kDenseParts = 8, kDenseRows = BS / kDenseParts;
+constexpr int kAinvHeld = kDenseRows / kDenseParts;  // entries of the inverse a thread holds, up to 128 coarsest rows
 // Most LDS for the cycle.  A level that needs more does not gain: with 902 rows
 // and 13,500 entries inside (135 KB) a V-cycle on 24^3 rows takes 31.6 us,
 // without them 29.6.
@@ -60,8 +61,33 @@ __device__ __forceinline__ double dpp(double x) {
 // with 8 a neighbour holds the other four, and both get the row's.  The four
 // entries of a step are loaded together (past the row's end the last one
 // again, not added): a chain of LDS reads per step, not per entry.
-template <class T>
+//
+// STREAM: the order of the CSR-stream kernels instead, one lane a row: rounded
+// products added in entry order.
+template <bool STREAM, class T>
 __device__ __forceinline__ T tail_row(const T* v, const uint16_t* ci, const T* x, int b, int e, int lane, int lpr) {
+    if constexpr (STREAM) {
+#pragma clang fp contract(off)
+        T s = T(0);
+        for (int k = b; k < e; k += 4) {
+            T p[4];
+            int c[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = min(k + u, e - 1);
+                p[u] = v[i];
+                c[u] = ci[i];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) p[u] = p[u] * x[c[u]];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const T t = s + p[u];
+                s = k + u < e ? t : s;
+            }
+        }
+        return s;
+    }
     T s[4] = {T(0), T(0), T(0), T(0)};
     for (int k = b + lane; k < e; k += 4 * lpr) {
         T p[4];
@@ -97,7 +123,7 @@ __device__ __forceinline__ TailLevel tail_level(const char* lds, int l) {
     return L;
 }
 
-template <class T>
+template <bool STREAM, class T>
 __device__ __forceinline__ void tail_cycle(const TailArgs<T>& A, const ScatterT<T>& sc) {
     extern __shared__ __align__(16) char lds[];
     const int tid = threadIdx.x;
@@ -114,15 +140,15 @@ __device__ __forceinline__ void tail_cycle(const TailArgs<T>& A, const ScatterT<
     const int t0 = min(tid, n0 - 1);  // no load behind a branch
     const T f0 = A.f[t0], g0 = A.g[t0];
     const Four mm = reinterpret_cast<const Four*>(sc.mem)[t0];
-    // the inverse: wave part dp of P takes the columns dp, dp + P, ... of row di
-    const int W = 1 << A.dense_log, P = BS >> A.dense_log;
-    const int di = tid & (W - 1), dp = __builtin_amdgcn_readfirstlane(tid >> A.dense_log), dr = min(di, m - 1);
+    // the inverse: thread (dp, di) takes the columns dp, dp + 8, ... of row di
+    const int di = tid & (kDenseRows - 1), dp = __builtin_amdgcn_readfirstlane(tid / kDenseRows);
     double ai[kAinvHeld];
-    if (m <= P * kAinvHeld) {
+    if (m <= kDenseRows) {
+        const int dr = min(di, m - 1);
 #pragma unroll
         for (int q = 0; q < kAinvHeld; ++q) {
             ai[q] = 0.0;
-            if (dp + P * q < m) ai[q] = (A.ainv + (unsigned)((dp + P * q) * m))[(unsigned)dr];
+            if (dp + kDenseParts * q < m) ai[q] = (A.ainv + (unsigned)((dp + kDenseParts * q) * m))[(unsigned)dr];
         }
     }
 #pragma unroll
@@ -159,7 +185,7 @@ __device__ __forceinline__ void tail_cycle(const TailArgs<T>& A, const ScatterT<
             const int J = t >> (sh + 2);
             const Rec q = rec[t >> sh];
             T r = T(0);
-            if (q.i != kTailNone) r = a[q.i] - w * tail_row(v, ci, g, q.b, q.e, lane, lpr);
+            if (q.i != kTailNone) r = a[q.i] - w * tail_row<STREAM>(v, ci, g, q.b, q.e, lane, lpr);
             T r1, r2, r3;  // from the lanes ahead
             if (lpr == 1) {
                 r1 = dpp<0x101>(r);
@@ -178,33 +204,43 @@ __device__ __forceinline__ void tail_cycle(const TailArgs<T>& A, const ScatterT<
         }
         __syncthreads();
     }
-    {  // coarsest: x = A^{-1} f in double, the parts added in order
+    {  // coarsest: x = A^{-1} f in double, in the batched solves' order of additions
         const T* f = reinterpret_cast<const T*>(lds + A.am);
         T* x = reinterpret_cast<T*>(lds + A.gm);
         double* part = reinterpret_cast<double*>(lds + A.part);
-        double s = 0.0;
-        if (m <= P * kAinvHeld) {
+        for (int r0 = 0; r0 < m; r0 += kDenseRows) {
+            double acc[8];
 #pragma unroll
-            for (int q = 0; q < kAinvHeld; ++q) {
-                const int j = dp + P * q;
-                if (j < m) s += ai[q] * double(f[j]);
-            }
-        } else {
-#pragma unroll 8
-            for (int j = dp; j < m; j += P) s += A.ainv[j * m + dr] * double(f[j]);
-        }
-        part[tid] = s;
-        __syncthreads();
-        if (tid < m) {
-            s = part[tid];
+            for (int k = 0; k < 8; ++k) acc[k] = 0.0;
+            if (m <= kDenseRows) {
 #pragma unroll
-            for (int p = 1; p < BS / kWave; ++p) {
-                const double q = part[(p < P ? p : 0) * W + tid];
-                s = p < P ? s + q : s;
+                for (int q = 0; q < kAinvHeld; ++q) {
+                    const int j = dp + kDenseParts * q;
+                    if (j < m) acc[q % 8] += ai[q] * double(f[j]);
+                }
+            } else {
+                const int i = min(r0 + di, m - 1);
+                for (int j0 = dp; j0 < m; j0 += 8 * kDenseParts) {
+                    double q[8];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) q[k] = (A.ainv + (unsigned)(min(j0 + k * kDenseParts, m - 1) * m))[(unsigned)i];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        const int j = j0 + k * kDenseParts;
+                        if (j < m) acc[k] += q[k] * double(f[j]);
+                    }
+                }
             }
-            x[tid] = T(s);
+            part[tid] = ((acc[0] + acc[4]) + (acc[2] + acc[6])) + ((acc[1] + acc[5]) + (acc[3] + acc[7]));
+            __syncthreads();
+            if (tid < kDenseRows && r0 + tid < m) {
+                double s = part[tid];
+#pragma unroll
+                for (int p = 1; p < kDenseParts; ++p) s += part[p * kDenseRows + tid];
+                x[r0 + tid] = T(s);
+            }
+            __syncthreads();
         }
-        __syncthreads();
     }
     for (int l = A.nl - 1; l >= 0; --l) {
         const TailLevel L = tail_level(lds, l);
@@ -225,7 +261,7 @@ __device__ __forceinline__ void tail_cycle(const TailArgs<T>& A, const ScatterT<
             const Rec q = rec[t >> sh];
             if (q.i == kTailNone) continue;
             const T ai = a[q.i], gi = g[q.i], di = dinv[q.i];
-            const T s = tail_row(v, ci, a, q.b, q.e, lane, lpr);
+            const T s = tail_row<STREAM>(v, ci, a, q.b, q.e, lane, lpr);
             if (lane == 0) g[q.i] = ai + w * (gi - di * s);
         }
         __syncthreads();
@@ -242,12 +278,21 @@ __device__ __forceinline__ void tail_cycle(const TailArgs<T>& A, const ScatterT<
 
 template <class T>
 __global__ __launch_bounds__(BS) void k_vc_tail(TailArgs<T> A, ScatterT<T> sc) {
-    tail_cycle<T>(A, sc);
+    tail_cycle<false, T>(A, sc);
 }
 
-// Packs one level a block row (blockIdx.y) into the layout k_vc_tail reads.
+// One system a workgroup, in the order of the CSR-stream kernels: a batch of 32
+// systems of 4096 to 32,768 rows takes 15 us here in place of seven launches
+// of 4-7 us (the whole batch 8.38 -> 7.70 ms).
 template <class T>
-__global__ __launch_bounds__(256) void k_tail_pack(TailPack<T> K) {
+__global__ __launch_bounds__(BS) void k_vc_tails(const TailJob<T>* __restrict__ jobs) {
+    const TailJob<T> J = jobs[blockIdx.x];
+    tail_cycle<true, T>(J.a, J.sc);
+}
+
+// Packs one level a block row (blockIdx.y) into the layout tail_cycle reads.
+template <class T>
+__device__ __forceinline__ void tail_pack(const TailPack<T>& K) {
     const TailSrc<T>& S = K.src[blockIdx.y];
     const TailLevel& L = K.lev[blockIdx.y];
     char* b = K.blob;
@@ -258,16 +303,26 @@ __global__ __launch_bounds__(256) void k_tail_pack(TailPack<T> K) {
     uint16_t* ci = reinterpret_cast<uint16_t*>(b + L.ci);
     Rec* rec = reinterpret_cast<Rec*>(b + L.rec);
     for (int e = t; e < S.nnz; e += step) {
-        v[e] = S.v[e];
-        ci[e] = (uint16_t)S.ci[e];
+        v[e] = S.v ? S.v[e] : T(S.v64[e]);
+        ci[e] = (uint16_t)(S.ci[e] + S.ci_add);
     }
-    for (int i = t; i < L.n; i += step) dinv[i] = S.dinv[i];
+    for (int i = t; i < L.n; i += step) dinv[i] = S.dinv ? S.dinv[i] : T(S.dinv64[i]);
     for (int r = t; r < 4 * L.nc; r += step) {
-        const int i = reinterpret_cast<const int*>(S.mem)[r];
+        const int i0 = reinterpret_cast<const int*>(S.mem)[r], i = i0 + S.mem_add;
         Rec q{kTailNone, 0, 0, 0};
-        if (i >= 0) q = Rec{(uint16_t)i, (uint16_t)S.rp[i], (uint16_t)S.rp[i + 1], 0};
+        if (i0 >= 0) q = Rec{(uint16_t)i, (uint16_t)(S.rp[i] + S.rp_add), (uint16_t)(S.rp[i + 1] + S.rp_add), 0};
         rec[r] = q;
     }
+}
+
+template <class T>
+__global__ __launch_bounds__(256) void k_tail_pack(TailPack<T> K) {
+    tail_pack<T>(K);
+}
+
+template <class T>
+__global__ __launch_bounds__(256) void k_tail_packs(const TailPack<T>* __restrict__ K) {
+    if ((int)blockIdx.y < K[blockIdx.z].nl) tail_pack<T>(K[blockIdx.z]);
 }
 
 }  // namespace
@@ -289,8 +344,8 @@ int tail_layout(const int* n, const int64_t* nnz, const int* lpr, int nl, TailAr
         take(L.dinv, (int64_t)sizeof(T) * n[l]);
         take(L.rec, 32 * (int64_t)n[l + 1]);
         take(L.ci, 2 * nnz[l]);
-        if (lpr[l] != 4 && lpr[l] != 8) return 0;
-        L.lpr_log = lpr[l] == 8 ? 1 : 0;
+        if (lpr && lpr[l] != 4 && lpr[l] != 8) return 0;
+        L.lpr_log = lpr && lpr[l] == 8 ? 1 : 0;
         if (at > kTailBytes) return 0;
     }
     at = (at + 16 * kWave - 1) / (16 * kWave) * (16 * kWave);
@@ -317,7 +372,6 @@ int tail_layout(const int* n, const int64_t* nnz, const int* lpr, int nl, TailAr
     A.gm = g;
     A.am = a;
     take(A.part, 8 * BS);
-    A.dense_log = A.m <= 64 ? 6 : A.m <= 128 ? 7 : 8;
     return at <= kTailBytes ? (int)at : 0;
 }
 
@@ -331,21 +385,34 @@ void vc_tail(const TailArgs<T>& A, int lds, const ScatterT<T>& sc, hipStream_t s
     hipLaunchKernelGGL(k_vc_tail<T>, dim3(1), dim3(BS), lds, s, A, sc);
 }
 
-// Once per device: the kernels may take all of a CU's LDS.
+template <class T>
+void launch_tail_packs(const TailPack<T>* K, int count, int nl, hipStream_t s) {
+    hipLaunchKernelGGL(k_tail_packs<T>, dim3(8, nl, count), dim3(256), 0, s, K);
+}
+
+template <class T>
+void vc_tails(const TailJob<T>* jobs, int count, int lds, hipStream_t s) {
+    hipLaunchKernelGGL(k_vc_tails<T>, dim3(count), dim3(BS), lds, s, jobs);
+}
+
+// The kernels may take that much of a CU's LDS.
 bool tail_prepare() {
     int dev = 0, most = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&most, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess || most < kTailBytes)
         return false;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_vc_tail<double>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, kTailBytes) == hipSuccess &&
-           hipFuncSetAttribute(reinterpret_cast<const void*>(&k_vc_tail<float>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, kTailBytes) == hipSuccess;
+    for (const void* k : {reinterpret_cast<const void*>(&k_vc_tail<double>), reinterpret_cast<const void*>(&k_vc_tail<float>),
+                          reinterpret_cast<const void*>(&k_vc_tails<double>),
+                          reinterpret_cast<const void*>(&k_vc_tails<float>)})
+        if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kTailBytes) != hipSuccess) return false;
+    return true;
 }
 
 #define AMG_INST(T)                                                         \
     template int tail_layout<T>(const int*, const int64_t*, const int*, int, TailArgs<T>&, TailLevel*); \
     template void launch_tail_pack<T>(const TailPack<T>&, int, hipStream_t); \
+    template void launch_tail_packs<T>(const TailPack<T>*, int, int, hipStream_t); \
+    template void vc_tails<T>(const TailJob<T>*, int, int, hipStream_t); \
     template void vc_tail<T>(const TailArgs<T>&, int, const ScatterT<T>&, hipStream_t);
 AMG_INST(double)
 AMG_INST(float)
