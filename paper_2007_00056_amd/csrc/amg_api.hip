@@ -1383,7 +1383,8 @@ void setup_impl(const amg_csr* Ain, const amg_params* pin, const amg_allocator* 
 // hierarchy (both steps of the level, several repetitions after a warm-up):
 // CSR-stream kernels with 128, 256 or 512 rows per block, or lane-group
 // kernels with 2, 4 or 8 lanes per row.  The schedules differ only in the
-// order of a row's additions.
+// order of a row's additions.  (The levels that run in one workgroup keep to it;
+// theirs applies only without that.)
 // ---------------------------------------------------------------------------
 template <class T>
 void tune_level_steps(amg_hier* h, int k, hipStream_t s) {
