@@ -205,6 +205,13 @@ void vc_resid_restrict(const VLevel<T>& L, int nc, const TIN* f, const T* g, T w
 template <class T, class TOUT>
 void vc_prolong_post(const VLevel<T>& L, const T* xp, const T* g, T w, TOUT* z, const ScatterT<T>* sc,
                      hipStream_t s);
+// The same two on level 0 for a right-hand side whose g = D^{-1} f does not
+// exist yet: formed where it is read (in double, rounded to T), stored in g.
+template <class T>
+void vc_stream_resid_first(const VLevel<T>& L, const double* f, const double* dinv, T w, T* r, T* g, hipStream_t s);
+template <class T>
+void vc_resid_restrict_first(const VLevel<T>& L, int nc, const double* f, const double* dinv, T w, const T* dinv_c,
+                             T* fc, T* gc, T* g, hipStream_t s);
 // g = D^{-1} f (computed in double, stored as T)
 template <class T>
 void vc_scale_dinv(int n, const double* dinv, const double* f, T* g, hipStream_t s);

@@ -17,7 +17,16 @@ struct EntAx {  // the entries of A and the x they are applied to
     const T* __restrict__ v;
     const int* __restrict__ ci;
     const T* __restrict__ x;
-    __device__ __forceinline__ T operator()(int e) const { return v[e] * x[ci[e]]; }
+    __device__ __forceinline__ T at(int i) const { return x[i]; }
+};
+
+template <class T>
+struct EntDf {  // the same for x = D^{-1} f, formed where it is read
+    const T* __restrict__ v;
+    const int* __restrict__ ci;
+    const double* __restrict__ dinv;
+    const double* __restrict__ f;
+    __device__ __forceinline__ T at(int i) const { return T(dinv[i] * f[i]); }
 };
 
 // ---------------------------------------------------------------------------
@@ -35,8 +44,8 @@ struct EntAx {  // the entries of A and the x they are applied to
 // precision: residual 30.6 us for 106 MB; 33.6 when blocks of 256 rows shared
 // the staging with barriers), by the chain of loads on smaller ones.
 // ---------------------------------------------------------------------------
-template <int K, int ORDER, class T>
-__device__ __forceinline__ void stage_chunk(const EntAx<T>& ent, int c0, int last, T* lds) {
+template <int K, int ORDER, class T, class Ent>
+__device__ __forceinline__ void stage_chunk(const Ent& ent, int c0, int last, T* lds) {
     const int lane = threadIdx.x & (kWave - 1);
     T a[K], x[K];
     int c[K];
@@ -47,7 +56,7 @@ __device__ __forceinline__ void stage_chunk(const EntAx<T>& ent, int c0, int las
         c[k] = ent.ci[e];
     }
 #pragma unroll
-    for (int k = 0; k < K; ++k) x[k] = ent.x[c[k]];
+    for (int k = 0; k < K; ++k) x[k] = ent.at(c[k]);
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         if (ORDER == 0) {
@@ -64,8 +73,8 @@ template <class T, int ORDER>
 constexpr int kWaveLds = ORDER == 0 ? kWaveChunk<T> : 2 * kWaveChunk<T>;
 
 // Sums of rows row0 .. row0 + 63 below n (a lane each); lds is this wave's.
-template <int ORDER = 0, class T>
-__device__ __forceinline__ T wave_rows(int row0, int n, const int* __restrict__ rp, const EntAx<T>& ent, T* lds) {
+template <int ORDER = 0, class T, class Ent>
+__device__ __forceinline__ T wave_rows(int row0, int n, const int* __restrict__ rp, const Ent& ent, T* lds) {
     static_assert(ORDER == 0 || ORDER == 4 || ORDER == 8, "");
     if (row0 >= n) return T(0);
     const int row = row0 + (int)(threadIdx.x & (kWave - 1));
@@ -122,8 +131,8 @@ __device__ __forceinline__ T wave_rows(int row0, int n, const int* __restrict__ 
 
 // Sums of RB consecutive rows from r0 on by a block of RB threads;
 // lds: RB / 64 * kWaveLds<T, ORDER> values.
-template <class T, int RB = kStreamBS, int ORDER = 0>
-__device__ __forceinline__ T stream_rows(int r0, int n, const int* __restrict__ rp, const EntAx<T>& ent, T* lds) {
+template <class T, int RB = kStreamBS, int ORDER = 0, class Ent>
+__device__ __forceinline__ T stream_rows(int r0, int n, const int* __restrict__ rp, const Ent& ent, T* lds) {
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     return wave_rows<ORDER>(r0 + w * kWave, n, rp, ent, lds + w * kWaveLds<T, ORDER>);
 }
@@ -167,8 +176,8 @@ static_assert(sizeof(SliceCode) == 128, "one cache line");
 // The sums of a coded slice with at most K distances.  Every load is made
 // (an absent entry's, from the row itself), so none waits for a branch.
 // lds: kCodeSlots * kWave values owned by this wave.
-template <int K, class T>
-__device__ __forceinline__ T coded_sum(const SliceCode& c, int row, int n, const EntAx<T>& ent, T* lds) {
+template <int K, class T, class Ent>
+__device__ __forceinline__ T coded_sum(const SliceCode& c, int row, int n, const Ent& ent, T* lds) {
 #pragma clang fp contract(off)
     const int lane = threadIdx.x & (kWave - 1);
     const int r = min(row, n - 1);
@@ -177,7 +186,7 @@ __device__ __forceinline__ T coded_sum(const SliceCode& c, int row, int n, const
 #pragma unroll
     for (int k = 0; k < K; ++k) a[k] = va[min(k * kWave + lane, c.last)];
 #pragma unroll
-    for (int k = 0; k < K; ++k) x[k] = ent.x[r + (__builtin_amdgcn_inverse_ballot_w64(c.mask[k]) ? c.off[k] : 0)];
+    for (int k = 0; k < K; ++k) x[k] = ent.at(r + (__builtin_amdgcn_inverse_ballot_w64(c.mask[k]) ? c.off[k] : 0));
     int pos = 0;  // entries of the slice before this lane's row
 #pragma unroll
     for (int k = 0; k < K; ++k)
@@ -224,9 +233,9 @@ __device__ __forceinline__ void hold_code(SliceCode& c) {
     asm volatile("" : "+s"(c.first), "+s"(c.total), "+s"(c.last), "+s"(c.cnt));
 }
 
-template <class T>
-__device__ __forceinline__ T coded_row(const SliceCode& c, int row, int n, const int* __restrict__ rp,
-                                       const EntAx<T>& ent, T* lds) {
+template <class T, class Ent>
+__device__ __forceinline__ T coded_row(const SliceCode& c, int row, int n, const int* __restrict__ rp, const Ent& ent,
+                                       T* lds) {
 #pragma clang fp contract(off)
     if (c.cnt >= 0) {
         if (c.cnt <= 5) return coded_sum<5>(c, row, n, ent, lds);
@@ -237,7 +246,7 @@ __device__ __forceinline__ T coded_row(const SliceCode& c, int row, int n, const
     if (row < n) {
         const int e1 = rp[row + 1];
         for (int e = rp[row]; e < e1; ++e) {
-            const T p = ent(e);
+            const T p = ent.v[e] * ent.at(ent.ci[e]);
             acc += p;
         }
     }
@@ -248,14 +257,14 @@ __device__ __forceinline__ T coded_row(const SliceCode& c, int row, int n, const
 // applied to, and the codes of its rows when KIND is kCoded; else KIND is the
 // order of additions.
 constexpr int kCoded = 1;
-template <class T, int KIND>
+template <class T, int KIND, class Ent = EntAx<T>>
 struct RowSrc {
     // LDS values of a block of RB threads
     template <int RB>
     static constexpr int lds = RB / kWave * (KIND == kCoded ? kCodeSlots * kWave : kWaveLds<T, KIND == kCoded ? 0 : KIND>);
     const SliceCode* code;
     const int* __restrict__ rp;
-    EntAx<T> ent;
+    Ent ent;
     // For every row of this block of RB threads, RB rows at a time:
     // in = pre(row), what the row's thread reads besides the matrix, loaded
     // ahead of the sum; then body(row, sum, in).  Each XCD takes one contiguous
