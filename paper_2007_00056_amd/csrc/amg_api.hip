@@ -233,11 +233,12 @@ int read_int(const int* d, hipStream_t s) {
     return h[0];
 }
 
-int2 read_int2(const int* d, hipStream_t s) {
+// n words (at most 32), in this thread's pinned words until the next read-back
+const int* read_ints(const int* d, int n, hipStream_t s) {
     int* h = pinned_words();
-    HIPCHK(hipMemcpyAsync(h, d, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipMemcpyAsync(h, d, n * sizeof(int), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    return make_int2(h[0], h[1]);
+    return h;
 }
 
 // Waits until the device has stored `value` to the mapped word: the host
@@ -574,7 +575,7 @@ void timed_end(amg_hier* h, int cls, hipStream_t s, bool recorded = false) {
 }
 
 // The order of additions of the CSR-stream kernels on level L, or -1 where the
-// lane-group kernels run.  A double level 0 with column codes reads those, in
+// lane-group kernels run.  A double level with column codes reads those, in
 // entry order.
 inline int stream_order(const amg_hier* h, const Level& L) {
     if (L.sched >= 0) return L.sched == 0 ? 0 : -1;
@@ -1198,8 +1199,9 @@ void setup_impl(const amg_csr* Ain, const amg_params* pin, const amg_allocator* 
     h->pool.al = al;
     DevPool& P = h->pool;
     P.hint(6 * (size_t)A.nnz + 96 * (size_t)A.n + (size_t(1) << 20));  // most of the hierarchy in one chunk
-    h->err = P.get<int>(2);  // error bits, slices of level 0 without a column code
-    HIPCHK(hipMemsetAsync(h->err, 0, 2 * sizeof(int), s));
+    // error bits, then per level the slices without a column code
+    h->err = P.get<int>(1 + kCodeLevels);
+    HIPCHK(hipMemsetAsync(h->err, 0, (1 + kCodeLevels) * sizeof(int), s));
 
     Level L0;
     L0.n = A.n;
@@ -1212,12 +1214,17 @@ void setup_impl(const amg_csr* Ain, const amg_params* pin, const amg_allocator* 
     launch_validate(A.n, A.nnz, A.row_ptr, A.col_idx, A.val, L0.dinv, h->err, s);
     HIPCHK(hipGetLastError());
     check_err_word(h->err, s, "amg_setup");
+    if (const char* e = getenv("HEMAMG_STREAM_MIN")) h->stream_min = atoi(e);  // tuning sweeps and tests
+    if (const char* e = getenv("HEMAMG_MID_MIN")) h->mid_min = atoi(e);
     if (const char* e = getenv("HEMAMG_CODE_MIN")) h->code_min = atoi(e);
-    if (A.n >= h->code_min && A.nnz <= (int64_t)kCodeSlots * A.n) {
-        L0.code = static_cast<SliceCode*>(static_cast<void*>(P.get<char>(slice_code_bytes(A.n))));
-        launch_code_slices(A.n, A.row_ptr, A.col_idx, L0.code, h->err + 1, s);
+    auto code_rows = [&](Level& L, int k) {
+        const int least = k == 0 ? h->code_min : p.precond_fp32 ? h->stream_min : h->mid_min;
+        if (k >= kCodeLevels || L.n < std::max(least, h->code_min) || L.nnz > (int64_t)kCodeSlots * L.n) return;
+        L.code = static_cast<SliceCode*>(static_cast<void*>(P.get<char>(slice_code_bytes(L.n))));
+        launch_code_slices(L.n, L.rp, L.ci, L.code, h->err + 1 + k, s);
         HIPCHK(hipGetLastError());
-    }
+    };
+    code_rows(L0, 0);
     h->lev.push_back(L0);
 
     DevPool wpool;
@@ -1307,6 +1314,7 @@ void setup_impl(const amg_csr* Ain, const amg_params* pin, const amg_allocator* 
         C.lpr = pick_lanes_per_row((double)C.nnz / C.n);
         launch_dinv(C.n, C.rp, C.ci, C.v, C.dinv, h->err, s);
         HIPCHK(hipGetLastError());  // its error bit is read back with the next level's sizes
+        code_rows(C, k + 1);
         h->lev.push_back(C);
     }
     // coarsest level: dense inverse
@@ -1328,19 +1336,18 @@ void setup_impl(const amg_csr* Ain, const amg_params* pin, const amg_allocator* 
         h->ainv_t = P.get<double>((size_t)m * m);
         launch_dense_inverse(DenseJob{m, 0, Lc.rp, Lc.ci, Lc.v, h->ainv_t, h->err}, work, s);
         HIPCHK(hipGetLastError());
-        const int2 e = read_int2(h->err, s);
-        raise_err_word(e.x, "coarsest level");
+        const int* e = read_ints(h->err, 1 + kCodeLevels, s);
+        raise_err_word(e[0], "coarsest level");
         // A few slices outside the pattern are read from the CSR arrays, lane
         // by lane: with 1 of 70 slices so, a V-cycle on 128^3 rows takes 175.8 us
         // (172.7 without any, 208.3 with no codes).
-        if ((int64_t)e.y * kCodeSpare > (A.n + kWave - 1) / kWave) h->lev[0].code = nullptr;
+        for (size_t k = 0; k < h->lev.size() && k < (size_t)kCodeLevels; ++k)
+            if ((int64_t)e[1 + k] * kCodeSpare > (h->lev[k].n + kWave - 1) / kWave) h->lev[k].code = nullptr;
     }
     // per-level work vectors, float copies of the values for a float V-cycle
     const bool fused = p.pre == 1 && p.post == 1;
     h->prec32 = p.precond_fp32 != 0;
     const size_t esz = h->prec32 ? sizeof(float) : sizeof(double);
-    if (const char* e = getenv("HEMAMG_STREAM_MIN")) h->stream_min = atoi(e);  // tuning sweeps and tests
-    if (const char* e = getenv("HEMAMG_MID_MIN")) h->mid_min = atoi(e);
     if (const char* e = getenv("HEMAMG_RB"))
         for (Level& L : h->lev) L.rb = atoi(e);
     if (const char* e = getenv("HEMAMG_GRAPHS")) h->use_graphs = atoi(e) != 0;

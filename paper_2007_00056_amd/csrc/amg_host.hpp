@@ -222,7 +222,7 @@ struct Level {
     // row; rb = rows per block of the CSR-stream kernels.
     int sched = -1;
     int rb = 256;
-    SliceCode* code = nullptr;  // level 0: column codes of its rows, when they fit
+    SliceCode* code = nullptr;  // column codes of its rows, when they fit
 
     LevelView view() const {
         LevelView w;
@@ -372,7 +372,9 @@ struct amg_hier {
     // level 0 72.2 (82.0).  Levels of 54,000 to 64,000 rows gain nothing (73.2
     // against 72.2), smaller ones lose the fused restriction.
     int mid_min = 65536;
-    // Level 0 from this many rows on is given column codes.  Writing them takes
+    // Levels that run the CSR-stream kernels are given column codes, in double
+    // from mid_min rows on, and level 0 from this many on (the Krylov methods'
+    // products always read it).  Writing them takes
     // 5-10 us at 4096-175,000 rows (47 us at 2.1M); a PCG solve to 1e-8 is
     // 1.30 ms with and 1.33 ms without them at 4096 rows, 3.88 and 4.00 ms at
     // 110,592.

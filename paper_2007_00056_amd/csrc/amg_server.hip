@@ -68,7 +68,7 @@ uint64_t footprint(int32_t n, int64_t nnz, const amg_params& p) {
     // level), D^{-1}, maps and member lists over <= N rows and <= Z entries;
     // V-cycle vectors; float copies; Krylov vectors; reduction partials
     uint64_t b = 8 * N + (8 * N + 12 * Z + 8 * N + 8 * N + 16 * N) + dense;
-    b += 5 * e * 2 * N + e * N + 2 * N + 256;  // vectors, level-0 column codes
+    b += 5 * e * 2 * N + e * N + 3 * N + 4096;  // vectors, column codes
     if (p.precond_fp32) b += 4 * 2 * Z + 4 * 2 * N;
     b += 10 * 8 * N + (1u << 20);
     // setup scratch at its peak: matching records and state, numbering,

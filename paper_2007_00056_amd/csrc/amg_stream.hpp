@@ -154,13 +154,15 @@ __device__ __forceinline__ T stream_rows(int r0, int n, const int* __restrict__ 
 // (p, q) takes 63 us where the CSR rows took 93 (295 MB, 4.7 TB/s; a copy of
 // this size reaches 5.0); on 128^3 rows the residual 25 us (40), the
 // postsmoothing 34 (51); with float values on 160^3 the residual 31 us (73)
-// and the postsmoothing 45 (79).
+// and the postsmoothing 45 (79).  Coarse levels that keep the pattern (128^3:
+// 524,288 and 131,072 rows) bring a V-cycle there from 174 to 161 us.
 //
 // The products are added in entry order and not fused with the additions, so
 // a row's sum is bit for bit that of stream_rows.  A slice that needs more
 // distances is marked (cnt < 0) and read from the CSR arrays, lane by lane.
 // ---------------------------------------------------------------------------
 constexpr int kCodeSlots = 8;
+constexpr int kCodeLevels = 16;  // levels that may have codes
 constexpr int kCodeSpare = 64;  // codes are used where at most one slice in so many lacks one
 
 struct alignas(128) SliceCode {
