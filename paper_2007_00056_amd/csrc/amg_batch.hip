@@ -94,6 +94,7 @@ struct amg_batch {
     std::vector<BSeg> seg;
     int n0 = 0;    // rows of the level-0 vectors
     int nblk = 0;  // reduction blocks over level 0
+    bool fuse = false;  // no system has more than kFuseBlocks of them
     int ndblk = 0; // blocks of the coarsest solves
     // device tables
     int2* btab = nullptr;
@@ -238,14 +239,18 @@ void iteration(const amg_batch* B, int pc, hipStream_t s) {
     const BLev& L0 = B->lev[0];
     const BatchTab T = B->tab(B->act);
     double* p = B->pv[pc];
-    launch_bspmv_dot(B->nblk, T, L0.rp, L0.ci, L0.v, p, B->q, p, B->part, s);
-    finish(B, B->act, B_PQ, s);
-    launch_bcg_update(B->nblk, T, B->x, B->r, p, B->q, L0.dinv, B->g0, B->prec32, B->part, B->S, cur, B_PQ, s);
-    finish(B, B->act, B_RR, s);
+    // the consumers add the partials of a system's blocks themselves
+    double *pa = B->part, *pb = B->part + B->nblk;
+    launch_bspmv_dot(B->nblk, T, L0.rp, L0.ci, L0.v, p, B->q, p, pa, s);
+    if (!B->fuse) finish(B, B->act, B_PQ, s);
+    launch_bcg_update(B->nblk, T, B->x, B->r, p, B->q, L0.dinv, B->g0, B->prec32, B->fuse ? pb : pa, B->S, cur, B_PQ,
+                      B->seg_blk, B->fuse ? pa : nullptr, s);
+    if (!B->fuse) finish(B, B->act, B_RR, s);
     vcycle(B, B->r, B->z, s);
-    launch_bdot(B->nblk, T, B->r, B->z, B->part, s);
-    finish(B, B->act, nxt, s);
-    launch_bcg_dir(B->nblk, T, B->z, p, B->pv[1 - pc], B->S, nxt, cur, s);
+    launch_bdot(B->nblk, T, B->r, B->z, pa, s);
+    if (!B->fuse) finish(B, B->act, nxt, s);
+    launch_bcg_dir(B->nblk, T, B->z, p, B->pv[1 - pc], B->S, nxt, cur, s, B->seg_blk, B->fuse ? pa : nullptr, pb,
+                   B_RR);
 }
 
 void read_slots(amg_batch* B, hipStream_t s) {
@@ -680,6 +685,9 @@ struct TailPlan {
     size_t blob = 0;  // bytes
 };
 
+// A system's blocks each read all its partials where they add them: at most
+// 4 KB each, so that the reads stay below the vectors'.
+constexpr int kFuseBlocks = 512;
 constexpr int kTailSystems = 1024;  // larger batches fill the device with the level kernels
 
 template <class T>
@@ -882,6 +890,8 @@ void create_impl(const std::vector<SegSrc>& src, bool prec32, double omega, int 
     std::vector<int> segblk(ns + 1, 0);
     for (int i = 0; i < ns; ++i) segblk[i + 1] = segblk[i] + (B->seg[i].n0 + 255) / 256;
     B->nblk = segblk[ns];
+    B->fuse = true;
+    for (int i = 0; i < ns; ++i) B->fuse &= segblk[i + 1] - segblk[i] <= kFuseBlocks;
     int ndb = 0;
     for (int i = 0; i < ns; ++i)
         if (!B->seg[i].tail) ndb += (B->seg[i].m + 63) / 64;

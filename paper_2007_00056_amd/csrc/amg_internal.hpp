@@ -403,11 +403,16 @@ void launch_bresidual(int nblk, const BatchTab& T, const int* rp, const int* ci,
 void launch_bdot(int nblk, const BatchTab& T, const double* a, const double* c, double* part, hipStream_t s);
 void launch_bfinish(int nseg, const int* seg_blk, const int* mask, const double* part, double* S, int slot_k,
                     hipStream_t s);
+// seg_blk and pq_part (or null: the slot holds it): the kernel adds the
+// partials of (p, q) itself and stores the sum in slot_pq
 void launch_bcg_update(int nblk, const BatchTab& T, double* x, double* r, const double* p, const double* q,
-                       const double* dinv, void* g, bool g32, double* part, const double* S, int slot_rho,
-                       int slot_pq, hipStream_t s);
-void launch_bcg_dir(int nblk, const BatchTab& T, const double* z, const double* p, double* pn, const double* S,
-                    int slot_new, int slot_old, hipStream_t s);
+                       const double* dinv, void* g, bool g32, double* part, double* S, int slot_rho, int slot_pq,
+                       const int* seg_blk, const double* pq_part, hipStream_t s);
+// with rz_part: the kernel adds the partials of (r, z) into slot_new and those
+// of (r, r) into slot_rr
+void launch_bcg_dir(int nblk, const BatchTab& T, const double* z, const double* p, double* pn, double* S,
+                    int slot_new, int slot_old, hipStream_t s, const int* seg_blk = nullptr,
+                    const double* rz_part = nullptr, const double* rr_part = nullptr, int slot_rr = 0);
 void launch_bzero(int nblk, const BatchTab& T, double* x, hipStream_t s);
 // Algorithm 5 over a batch (two-sum kernels write their second partials at part + nblk).
 void launch_bbicg_s(int nblk, const BatchTab& T, const double* r, const double* v, double* sv, const double* S,
