@@ -6,10 +6,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-namespace amg {
+#include "amg_index.hpp"
 
-constexpr int kWave = 64;
-constexpr int kNumXcd = 8;  // MI355X: 8 accelerator complex dies, 32 CUs each
+namespace amg {
 
 // Workgroups are dispatched round-robin over the XCDs (block b runs on XCD
 // b % 8).  Remapping gives each XCD one contiguous range of logical blocks, so

@@ -175,20 +175,20 @@ struct alignas(128) SliceCode {
 };
 static_assert(sizeof(SliceCode) == 128, "one cache line");
 
-// The sums of a coded slice with at most K distances.  Every load is made
-// (an absent entry's, from the row itself), so none waits for a branch.
+// The sums of a coded slice with at most K distances, by a wave that has rows of
+// it.  Every load is made (an absent entry's, from the row itself), so none
+// waits for a branch.
 // lds: kCodeSlots * kWave values owned by this wave.
 template <int K, class T, class Ent>
 __device__ __forceinline__ T coded_sum(const SliceCode& c, int row, int n, const Ent& ent, T* lds) {
 #pragma clang fp contract(off)
     const int lane = threadIdx.x & (kWave - 1);
-    const int r = min(row, n - 1);
     const T* va = ent.v + c.first;
     T a[K], x[K];
 #pragma unroll
-    for (int k = 0; k < K; ++k) a[k] = va[min(k * kWave + lane, c.last)];
+    for (int k = 0; k < K; ++k) a[k] = va[coded_val(k * kWave + lane, c.last)];
 #pragma unroll
-    for (int k = 0; k < K; ++k) x[k] = ent.at(r + (__builtin_amdgcn_inverse_ballot_w64(c.mask[k]) ? c.off[k] : 0));
+    for (int k = 0; k < K; ++k) x[k] = ent.at(coded_col(row, n, __builtin_amdgcn_inverse_ballot_w64(c.mask[k]), c.off[k]));
     int pos = 0;  // entries of the slice before this lane's row
 #pragma unroll
     for (int k = 0; k < K; ++k)
@@ -274,22 +274,18 @@ struct RowSrc {
     // neighbouring rows share are read into one L2.
     template <int RB, class Pre, class Body>
     __device__ __forceinline__ void rows(int n, T* lds, Pre pre, Body body) const {
-        const int nb = (n + RB - 1) / RB;
-        const int xcd = blockIdx.x % kNumXcd, per = nb / kNumXcd, rem = nb % kNumXcd;
-        const int end = (xcd + 1) * per + min(xcd + 1, rem);
-        const int step = gridDim.x / kNumXcd + (xcd < (int)gridDim.x % kNumXcd);  // blocks on this XCD
-        int b = xcd * per + min(xcd, rem) + blockIdx.x / kNumXcd;
+        const BlockRange mine = xcd_range((n + RB - 1) / RB, blockIdx.x, gridDim.x);
         if constexpr (KIND == kCoded) {
             const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-            const int last = (n - 1) / kWave;
-            SliceCode c = load_code(code, min(b * (RB / kWave) + w, last));
+            SliceCode c = load_code(code, slice_at(wave_slice(mine.first, RB, w), n));
             hold_code(c);
-            for (; b < end; b += step) {
+            for (int b = mine.first; b < mine.end; b += mine.step) {
                 const int row = b * RB + threadIdx.x;
                 const auto in = pre(min(row, n - 1));
                 // the next slice's record arrives during this slice's loads
-                SliceCode next = load_code(code, min((b + step) * (RB / kWave) + w, last));
-                const T s = coded_row<T>(c, row, n, rp, ent, lds + w * kCodeSlots * kWave);
+                SliceCode next = load_code(code, slice_at(wave_slice(b + mine.step, RB, w), n));
+                T s = T(0);
+                if (wave_has_rows(wave_slice(b, RB, w), n)) s = coded_row<T>(c, row, n, rp, ent, lds + w * kCodeSlots * kWave);
                 // every load has been used: said here, the loop has no wait for
                 // the last slice's store at its head
                 __builtin_amdgcn_s_waitcnt(0x0f70);
@@ -298,7 +294,7 @@ struct RowSrc {
                 c = next;
             }
         } else {
-            for (; b < end; b += step) {
+            for (int b = mine.first; b < mine.end; b += mine.step) {
                 const int row = b * RB + threadIdx.x;
                 const auto in = pre(min(row, n - 1));
                 const T s = stream_rows<T, RB, KIND>(b * RB, n, rp, ent, lds);
