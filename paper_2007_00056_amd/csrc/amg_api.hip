@@ -219,8 +219,9 @@ int* pinned_words(int** dev) {
     thread_local int* p = nullptr;
     thread_local int* d = nullptr;
     if (!p) {
-        HIPCHK(hipHostMalloc((void**)&p, 64 * sizeof(int), hipHostMallocMapped | hipHostMallocCoherent));
+        HIPCHK(hipHostMalloc((void**)&p, kPinnedWords * sizeof(int), hipHostMallocMapped | hipHostMallocCoherent));
         HIPCHK(hipHostGetDevicePointer(reinterpret_cast<void**>(&d), p, 0));
+        std::memset(p, 0, kPinnedWords * sizeof(int));  // no sequence word has arrived yet
     }
     if (dev) *dev = d;
     return p;
@@ -233,10 +234,12 @@ int read_int(const int* d, hipStream_t s) {
     return h[0];
 }
 
-// n words (at most 32), in this thread's pinned words until the next read-back
-const int* read_ints(const int* d, int n, hipStream_t s) {
+// N words, in this thread's pinned words until the next read-back
+template <int N>
+const int* read_ints(const int* d, hipStream_t s) {
+    static_assert(N <= kReadWords, "the read-back area");
     int* h = pinned_words();
-    HIPCHK(hipMemcpyAsync(h, d, n * sizeof(int), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipMemcpyAsync(h, d, N * sizeof(int), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     return h;
 }
@@ -356,7 +359,7 @@ struct SetupWork {
         rowcnt = P.get<int>(n);
         ovf = P.get<int>(n);
         novf = P.get<int>(1);
-        hc = pinned_words() + 32;  // this thread's pinned words, past the read-back area
+        hc = pinned_words() + kRoundWords;
         ev[0] = event_get(false);
         ev[1] = event_get(false);
         if (const char* e = getenv("HEMAMG_HEM_GRID")) hw.round_grid = atoi(e) > 0 ? atoi(e) : 96;
@@ -469,7 +472,8 @@ Csr galerkin(const Csr& B, Pass& P, SetupWork& W, DevPool& out, hipStream_t s, c
     if (!crp) crp = out.get<int>((size_t)nmax + 1);
     C.rp = crp;
     int* dw = nullptr;
-    int* hw = pinned_words(&dw);
+    int* hw = pinned_words(&dw) + kPassWords;
+    dw += kPassWords;
     thread_local int seq = 0;  // the words belong to the thread
     seq = seq == INT_MAX ? 1 : seq + 1;
     launch_offsets(nmax, W.rowcnt, C.rp, PassWords{dw, P.cnt, W.nc, err, W.novf, seq}, W.stmp, s);
@@ -1336,7 +1340,7 @@ void setup_impl(const amg_csr* Ain, const amg_params* pin, const amg_allocator* 
         h->ainv_t = P.get<double>((size_t)m * m);
         launch_dense_inverse(DenseJob{m, 0, Lc.rp, Lc.ci, Lc.v, h->ainv_t, h->err}, work, s);
         HIPCHK(hipGetLastError());
-        const int* e = read_ints(h->err, 1 + kCodeLevels, s);
+        const int* e = read_ints<1 + kCodeLevels>(h->err, s);
         raise_err_word(e[0], "coarsest level");
         // A few slices outside the pattern are read from the CSR arrays, lane
         // by lane: with 1 of 70 slices so, a V-cycle on 128^3 rows takes 175.8 us

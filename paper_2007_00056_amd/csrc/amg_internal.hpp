@@ -67,8 +67,15 @@ void launch_ehem_init(int n, const int* rp, const int* ci, const double* v, HemW
 void launch_ehem_round(int r, int n, const int* rp, const int* ci, HemWork& w, hipStream_t s);
 
 size_t scan_tmp_ints(int n);  // scratch of the two prefix sums below
-// What a pass hands to the host.
-constexpr int kPassSeq = 12;  // place of the sequence word in `out`
+// A thread's pinned words.  What a pass hands to the host has a place of its own:
+// the host takes it to have arrived when the sequence word has its value, which
+// no read-back may store there meanwhile.
+constexpr int kPinnedWords = 64;
+constexpr int kReadWords = 32;                 // read-backs: the first words
+constexpr int kRoundWords = kReadWords, kRounds = 2;  // worklist sizes of the edge-based rounds
+constexpr int kPassWords = 40;                 // a pass's words
+constexpr int kPassSeq = 12;                   // the sequence word among them, the last one
+static_assert(kRoundWords + kRounds <= kPassWords && kPassWords + kPassSeq < kPinnedWords, "places of their own");
 struct PassWords {
     int* out;        // mapped host memory: cnt[0 .. 7], *nc, the entry count, *err, *novf, seq
     int* cnt;        // cleared after
