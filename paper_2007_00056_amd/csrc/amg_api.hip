@@ -479,6 +479,9 @@ Csr galerkin(const Csr& B, Pass& P, SetupWork& W, DevPool& out, hipStream_t s, c
     launch_offsets(nmax, W.rowcnt, C.rp, PassWords{dw, P.cnt, W.nc, err, W.novf, seq}, W.stmp, s);
     HIPCHK(hipGetLastError());
     wait_word(hw + kPassSeq, seq, s);
+    // the words may arrive before the last blocks have ended: an error is
+    // reported with the stream finished, as every return of a setup
+    if (hw[5] != 0 || hw[7] != 0 || hw[10] != 0) HIPCHK(hipStreamSynchronize(s));
     raise_err_word(hw[10], "amg_setup");
     if (hw[5] != 0) raise(AMG_EINVAL, "matching: sparsity pattern is not structurally symmetric");
     late = hw[7] != 0;

@@ -74,3 +74,24 @@ def test_read_backs_leave_the_sequence_word(monkeypatch):
     t.join()
     if failures:
         raise failures[0]
+
+
+def test_refused_setup_returns_with_the_stream_finished():
+    """A pattern that is not symmetric, found in the first pass of 343,000 rows: its sizes come from the first of
+    many blocks, and the setup returns once they all have ended."""
+    import torch
+
+    a = P.poisson3d(70)
+    keep = np.ones(len(a.col), bool)
+    keep[a.row_ptr[1234] + 1] = a.col[a.row_ptr[1234] + 1] == 1234  # one entry of row 1234, not its mirror image
+    assert keep.sum() == len(a.col) - 1
+    rows = np.repeat(np.arange(a.n), np.diff(a.row_ptr))[keep]
+    rp = np.concatenate(([0], np.cumsum(np.bincount(rows, minlength=a.n)))).astype(np.int32)
+    A = hemamg.DeviceCSR.from_host(P.CSR(a.n, rp, a.col[keep], a.val[keep]), device="cuda:0")
+    torch.cuda.synchronize()
+    s = torch.cuda.Stream()
+    for _ in range(20):
+        with pytest.raises(hemamg.AmgError) as e:
+            hemamg.Hierarchy(A, stream=s)
+        assert s.query()
+        assert e.value.status == hemamg.AMG_EINVAL
