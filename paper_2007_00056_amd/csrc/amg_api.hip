@@ -319,6 +319,7 @@ struct SetupWork {
     int* hc = nullptr;  // pinned: worklist sizes read back between batches
     hipEvent_t ev[2]{};
     bool tile_strict = false;  // a pass past its time limit is an error (tests), not repeated
+    double first_limit_us = -1.0;  // time limit of a pass's first attempt (tests; below 0: the rule)
 
     bool edge = false;  // edge-based matching (Algorithm 3)
     int* mrp = nullptr;  // mirrored matrix of a pass from the last index
@@ -364,6 +365,7 @@ struct SetupWork {
         ev[1] = event_get(false);
         if (const char* e = getenv("HEMAMG_HEM_GRID")) hw.round_grid = atoi(e) > 0 ? atoi(e) : 96;
         if (const char* e = getenv("HEMAMG_TILE_STRICT")) tile_strict = atoi(e) != 0;
+        if (const char* e = getenv("HEMAMG_HEM_LIMIT")) first_limit_us = atof(e);
         if (const char* e = getenv("HEMAMG_HEM_TILE")) hw.tile_rows = atoi(e) > 0 ? atoi(e) : 0;  // rows per tile
     }
     ~SetupWork() {
@@ -404,21 +406,28 @@ void run_rounds(SetupWork& W, HemWork& w, int n, hipStream_t s, Launch&& launch_
     }
 }
 
-// Time limit of a node-based pass in wall-clock ticks (250 ms; a pass of a few
-// million rows takes well under one).
-long long tile_timeout_ticks() {
+// Wall-clock ticks of the current device in a microsecond.
+double wall_ticks_per_us() {
     thread_local int dev = -1;
-    thread_local long long ticks = 0;
+    thread_local double ticks = 0.0;
     int d = 0;
     HIPCHK(hipGetDevice(&d));
     if (d != dev) {
         int khz = 0;
         HIPCHK(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, d));
-        ticks = (long long)(khz > 0 ? khz : 100000) * 250;
+        ticks = (khz > 0 ? khz : 100000) / 1000.0;
         dev = d;
     }
     return ticks;
 }
+
+// Time limit of a node-based pass in microseconds.  A pass always ends by itself;
+// the limit is for a device that other work holds up, so it lies above the
+// longest pass that a matrix can ask for: a chain of one decision a row, 4 us
+// where it leads from tile to tile, and 16 us for every 64 entries of a row that
+// is read again (a pass of 2 million rows of 7 entries takes 2 ms, one on a
+// chain of a million rows 0.53 s).
+double pass_limit_us(int n, int64_t nnz) { return 250e3 + 4.0 * n + 0.25 * (double)nnz; }
 
 // from_last: the pass starts from the last index (run on the mirrored matrix,
 // its pairs mapped back before numbering).
@@ -500,8 +509,7 @@ Csr galerkin(const Csr& B, Pass& P, SetupWork& W, DevPool& out, hipStream_t s, c
 }
 
 // One matching pass on B and its Galerkin product.  A pass past its time limit
-// (a device shared with work that holds it up) is repeated with 16 times the
-// limit, twice.
+// is repeated once, with four times the limit.
 Csr coarsen_pass(const Csr& B, Pass& P, SetupWork& W, int t, DevPool& out, hipStream_t s, const int* err,
                  bool from_last, std::vector<hipEvent_t>* marks = nullptr) {
     auto mark = [&] {
@@ -509,16 +517,16 @@ Csr coarsen_pass(const Csr& B, Pass& P, SetupWork& W, int t, DevPool& out, hipSt
         marks->push_back(event_get(true));
         HIPCHK(hipEventRecord(marks->back(), s));
     };
-    long long tmo = tile_timeout_ticks();
+    const double limit = pass_limit_us(B.n, B.nnz), first = W.first_limit_us >= 0.0 ? W.first_limit_us : limit;
     int* crp = nullptr;
     mark();
-    for (int k = 0;; ++k, tmo *= 16) {
-        P = hem_pass(B, W, t, s, from_last, tmo);
+    for (int k = 0;; ++k) {
+        P = hem_pass(B, W, t, s, from_last, (long long)((k == 0 ? first : 4.0 * limit) * wall_ticks_per_us()));
         if (k == 0) mark();
         bool late = false;
         const Csr C = galerkin(B, P, W, out, s, err, crp, late);
         if (!late) return C;
-        if (k == 2 || W.tile_strict) raise(AMG_EHIP, "matching pass did not finish in time");
+        if (k == 1 || W.tile_strict) raise(AMG_EHIP, "matching pass did not finish in time");
     }
 }
 

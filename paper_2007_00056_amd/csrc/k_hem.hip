@@ -399,6 +399,12 @@ __device__ __forceinline__ void or_dev(unsigned* p, unsigned bits) {
 // at the head of the sweep makes every sweep wait for the wave's stores.
 __device__ __forceinline__ void settle() { __builtin_amdgcn_s_waitcnt(0x0f70); }  // vmcnt(0)
 
+// Whether the pass was given up (the same for the whole wave).
+__device__ __forceinline__ bool given_up(const int* cnt) {
+    const int g = __hip_atomic_load(&cnt[7], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __builtin_amdgcn_readfirstlane(g) != 0;
+}
+
 // LDS words that other waves of the workgroup read or write meanwhile
 template <class I>
 __device__ __forceinline__ I lds_load(const I* p) {
@@ -648,8 +654,10 @@ __device__ __forceinline__ void poll_choices(const HemState& S, const Tile& T, u
 // the passes of a setup at 160^3 with smooth coefficients took 85 ms and take
 // 20 ms, those at 128^3 (constant coefficients) 6.8 ms and 4.2 ms.
 //
-// Past tmo wall-clock ticks a wave stops and cnt[7] is set; the host repeats
-// the pass with a longer limit (every fact found is found again).
+// Past tmo wall-clock ticks a wave stops and sets cnt[7]; the other waves look at
+// it when they look at the clock, workgroups before they take a tile, so a pass
+// given up has ended within about one limit whatever its number of tiles.  The
+// host repeats it with a longer limit (every fact found is found again).
 template <int R, int NT>
 __global__ __launch_bounds__(NT) void k_hem_tile(HemState S, int rows, int* cnt, const int* err, long long tmo) {
     constexpr int TM = NT - 2 * kWave;  // vertices of a tile at most
@@ -665,12 +673,13 @@ __global__ __launch_bounds__(NT) void k_hem_tile(HemState S, int rows, int* cnt,
     // a pattern that is not symmetric: some bits would never be set
     if (cnt[5] != 0 || (*err & ERR_NONSYM)) return;
     if (threadIdx.x == 0) {
-        s_tile = atomicAdd(&cnt[0], 1);
+        s_tile = given_up(cnt) ? -1 : atomicAdd(&cnt[0], 1);
         s_left = TM / kWave;
         s_max = 0;
         s_w[TM] = 0u;
     }
     __syncthreads();
+    if (s_tile < 0) return;
     const int off = s_tile * rows;
     const int m = min(rows, S.n - off);
     const Tile T{off, m, s_w};
@@ -741,7 +750,7 @@ __global__ __launch_bounds__(NT) void k_hem_tile(HemState S, int rows, int* cnt,
         const unsigned own = T.load(to), tgt = T.load(ta);
         const bool fire = (~own & mo) == 0u || (~tgt & mt) == 0u || (int)own < 0 || (int)tgt < 0;
         unsigned long long todo = __ballot(fire);
-        if ((++sweeps & 1023) == 0 && wall_clock64() - t_start > tmo) {
+        if ((++sweeps & 1023) == 0 && (wall_clock64() - t_start > tmo || given_up(cnt))) {
             late = true;
             break;
         }
