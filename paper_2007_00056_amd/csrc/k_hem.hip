@@ -22,6 +22,15 @@
 // a stale word only delays: no rounds, no barriers and no order between
 // words are needed, and the result is Algorithm 2's, bit for bit, whatever
 // the timing.  The lowest undecided vertex can always decide, so the walk ends.
+//
+// That holds as long as no conclusion rests on a bit being absent from one word
+// when it was set before a bit seen in another.  "Unavailable" is such a
+// conclusion: a top bit without the lower ones.  Where these share a word, one
+// read has both.  In a vertex with more lower edges than a word holds they are
+// in different words: whoever takes it has first seen every bit below its own
+// position, so a lower neighbour that could still read too few of them has made
+// its own edge dead and does not ask, and for a higher one the taker's bit is
+// never set.
 #include <cstdint>
 
 #include "amg_device.hpp"
@@ -414,11 +423,18 @@ template <class I>
 __device__ __forceinline__ void lds_store(I* p, I x) {
     __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
-__device__ __forceinline__ void lds_or(unsigned* p, unsigned bits) {
+template <class I>
+__device__ __forceinline__ void lds_or(I* p, I bits) {
     (void)__hip_atomic_fetch_or(p, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 enum { kUnknown = 0, kAvail = 1, kGone = 2 };
+
+// What is known of a vertex's choices in higher tiles: low half, a bit per record
+// entry that its state is known; high half, that it is available.  One word, so
+// that no read has the first without the second (read apart, a known entry that
+// looks unavailable would be passed by).  The low half is also watched as a word.
+using Known = unsigned long long __attribute__((may_alias));
 
 // The tile of a workgroup: vertices off .. off + m - 1, their words in LDS.
 // The bits of lower edges from other tiles arrive in gw (set there by those
@@ -579,8 +595,8 @@ __device__ __forceinline__ void poll_words(const HemState& S, const Tile& T, con
 // of vertices that are free to take them each time, the others, which only
 // let later edges be marked earlier, every eighth time.
 template <int TM>
-__device__ __forceinline__ void poll_choices(const HemState& S, const Tile& T, unsigned* s_x, unsigned* s_y,
-                                             const int* s_r, const int* s_e, const int* s_left) {
+__device__ __forceinline__ void poll_choices(const HemState& S, const Tile& T, Known* s_k, const int* s_r,
+                                             const int* s_e, const int* s_left) {
     constexpr int B = TM / kWave < 8 ? TM / kWave : 8;
     const int lane = threadIdx.x % kWave;
     __builtin_amdgcn_s_setprio(3);
@@ -596,7 +612,7 @@ __device__ __forceinline__ void poll_choices(const HemState& S, const Tile& T, u
                 r[i] = 0;
                 if (l < T.m) {
                     r[i] = lds_load(&s_r[l]);
-                    if (r[i] > 0 && ((lds_load(&s_x[l]) >> (r[i] - 1)) & 1u)) r[i] = 0;
+                    if (r[i] > 0 && ((lds_load(&s_k[l]) >> (r[i] - 1)) & 1u)) r[i] = 0;
                     if ((it & 7) != 0 && T.load(l) != kAllDead) r[i] = 0;
                     q[i] = r[i] > 0 ? s_e[(r[i] - 1) * (TM + 1) + l] : 0;
                 }
@@ -612,10 +628,9 @@ __device__ __forceinline__ void poll_choices(const HemState& S, const Tile& T, u
                 const int l = l0 + i * kWave;
                 if (r[i] > 0) {
                     const bool full = (~t[i] & low_bits(q[i] & 31)) == 0u;
-                    const unsigned bit = 1u << (r[i] - 1);
-                    if (full) lds_or(&s_y[l], bit);
-                    if (full || (t[i] & kTaken))  // after s_y: LDS operations of a wave stay in order
-                        lds_or(&s_x[l], bit);
+                    const Known bit = 1ull << (r[i] - 1);
+                    if (full) lds_or(&s_k[l], bit | bit << 32);
+                    else if (t[i] & kTaken) lds_or(&s_k[l], bit);
                 }
             }
         }
@@ -646,9 +661,9 @@ __device__ __forceinline__ void poll_choices(const HemState& S, const Tile& T, u
 //    group step takes about 2000 for up to 4 vertices, or 16 with short rows.
 //  * No wave that matches touches global memory but to store.  The last two
 //    poll what other tiles set: bits of this tile's words are merged into LDS,
-//    and for each choice in a higher tile that is waited for, s_x tells, per
-//    record entry, that it is known, and s_y that it is available.  Facts about
-//    an entry stay true, so nothing is taken back when a vertex moves on.
+//    and for each choice in a higher tile that is waited for, s_k tells, per
+//    record entry, that it is known and whether it is available.  Facts about an
+//    entry stay true, so nothing is taken back when a vertex moves on.
 //
 // Against rounds of ready vertices between barriers (the same matching):
 // the passes of a setup at 160^3 with smooth coefficients took 85 ms and take
@@ -663,8 +678,8 @@ __global__ __launch_bounds__(NT) void k_hem_tile(HemState S, int rows, int* cnt,
     constexpr int TM = NT - 2 * kWave;  // vertices of a tile at most
     constexpr int G = R < 16 ? R : 16, E = R / G, NG = kWave / G;
     constexpr int ES = TM + 1;      // entry t of vertex l at s_e[t * ES + l]: no bank conflicts either way
-    __shared__ unsigned s_w[2 * TM + 1];  // words, one that is never looked at, then known entries
-    __shared__ unsigned s_y[TM];          // available entries, of those known
+    constexpr int KW = TM + 2;  // s_w from here on: s_k
+    __shared__ __align__(8) unsigned s_w[KW + 2 * TM];  // words, one that is never looked at (and one more), s_k
     __shared__ unsigned s_m[TM];          // bits of lower edges from other tiles
     __shared__ int s_r[TM];               // 1 + the entry waited for in a higher tile
     __shared__ int s_e[R * ES];
@@ -685,7 +700,7 @@ __global__ __launch_bounds__(NT) void k_hem_tile(HemState S, int rows, int* cnt,
     const Tile T{off, m, s_w};
     const int lane = threadIdx.x % kWave, base = threadIdx.x - lane;
     const int l = threadIdx.x, u = off + l;
-    unsigned* const s_x = s_w + TM + 1;
+    Known* const s_k = reinterpret_cast<Known*>(s_w + KW);
     unsigned st = 0, mo = kNever, mt = kNever;
     int to = TM, ta = TM;
     bool zeros = false;
@@ -705,7 +720,7 @@ __global__ __launch_bounds__(NT) void k_hem_tile(HemState S, int rows, int* cnt,
             w0 = kAllDead & ~low_bits(d.x);
         }
         s_w[l] = w0;
-        s_x[l] = s_y[l] = 0u;
+        s_k[l] = 0u;
         s_m[l] = xm;
         s_r[l] = 0;
 #pragma unroll
@@ -731,7 +746,7 @@ __global__ __launch_bounds__(NT) void k_hem_tile(HemState S, int rows, int* cnt,
     }
     if (base >= TM) {
         if (gridDim.x > 1 && base == TM) poll_words<TM>(S, T, s_m, &s_left);
-        else if (gridDim.x > 1) poll_choices<TM>(S, T, s_x, s_y, s_r, s_e, &s_left);
+        else if (gridDim.x > 1) poll_choices<TM>(S, T, s_k, s_r, s_e, &s_left);
         return;
     }
     // the edge of record entry q of LDS vertex b is dead
@@ -844,7 +859,8 @@ __global__ __launch_bounds__(NT) void k_hem_tile(HemState S, int rows, int* cnt,
             const unsigned ow = live ? (unsigned)in.y : 0u, f = (unsigned)in.z;
             const int k0 = (int)(f & 0xffffu);
             const bool tk = (ow & kTaken) != 0u, conf = (f & vConf) != 0u;
-            const unsigned kn = lds_load(&s_x[lv]), av = lds_load(&s_y[lv]), xm = s_m[lv];
+            const Known known = lds_load(&s_k[lv]);
+            const unsigned kn = (unsigned)known, av = (unsigned)(known >> 32), xm = s_m[lv];
             int q[E], jl[E];
             unsigned cm = 0u, fm = 0u, rm = 0u;  // entries: candidates, available ones, ones that the row holds
 #pragma unroll
@@ -856,7 +872,7 @@ __global__ __launch_bounds__(NT) void k_hem_tile(HemState S, int rows, int* cnt,
             for (int i = 0; i < E; ++i) {
                 const int e = t + i * G;
                 const unsigned w = T.load(jl[i] < m ? jl[i] : TM);
-                const bool full = (~w & low_bits(q[i] & 31)) == 0u || ((kn & av) >> e) & 1u;
+                const bool full = (~w & low_bits(q[i] & 31)) == 0u || (av >> e) & 1u;
                 const bool gone = !full && (jl[i] < m ? (int)w < 0 : ((kn >> e) & 1u) != 0u);
                 cm |= group_mask<G>(q[i] != 0 && (conf ? e == k0 : e >= k0 && (q[i] == kRowEnt || !gone))) << (i * G);
                 fm |= group_mask<G>(full) << (i * G);
@@ -893,7 +909,7 @@ __global__ __launch_bounds__(NT) void k_hem_tile(HemState S, int rows, int* cnt,
                 int nta = TM;
                 unsigned nmt = row ? 0u : kNever;
                 if (!done && !conf && !nconf && !row) {
-                    nta = kl < m ? kl : TM + 1 + lv;
+                    nta = kl < m ? kl : KW + 2 * lv;
                     nmt = 1u << (k & 31);
 #pragma unroll
                     for (int i = 0; i < E; ++i)
