@@ -326,6 +326,13 @@ struct SetupWork {
     int* mci = nullptr;
     double* mv = nullptr;
 
+    // about what init draws, without the mirrored matrix
+    static size_t bytes(int n, int64_t nnz, bool edge_based) {
+        const size_t own = edge_based ? 8 * (size_t)nnz
+                                      : 4 * (hem_rec_ints(n, nnz) + hem_ent_ints(n, nnz) + hem_ext_words(nnz));
+        return own + 64 * (size_t)n + 4096;
+    }
+
     void init(int n, int64_t nnz, DevPool& P, int* err, bool edge_based, bool alternate, hipStream_t s) {
         edge = edge_based;
         if (edge) {
@@ -336,8 +343,10 @@ struct SetupWork {
             hw.wl[0] = P.get<int>(n);
             hw.wl[1] = P.get<int>(n);
         } else {
-            hw.rec_ints = 16 * (size_t)n;
+            hw.rec_ints = hem_rec_ints(n, nnz);
             hw.rec = P.get<int>(hw.rec_ints);
+            hw.ent_ints = hem_ent_ints(n, nnz);
+            hw.ent = P.get<int>(hw.ent_ints);
             hw.deg = P.get<int2>(n);
             hw.gw = P.get<unsigned>(n);
             hw.xw = P.get<unsigned>(hem_ext_words(nnz));
@@ -1245,7 +1254,7 @@ void setup_impl(const amg_csr* Ain, const amg_params* pin, const amg_allocator* 
     DevPool wpool;
     wpool.s = s;
     wpool.al = al;
-    wpool.hint((size_t)A.nnz * (p.hem == 1 ? 8 : 0) + 4 * hem_ext_words(A.nnz) + 128 * (size_t)A.n + 4096 +
+    wpool.hint(SetupWork::bytes(A.n, A.nnz, p.hem == 1) +
                (p.alternate ? 12 * (size_t)A.nnz + 4 * (size_t)A.n : 0));
     struct WpoolGuard {
         DevPool& t;
@@ -1633,7 +1642,7 @@ void batch_coarsen(const amg_csr* A, int count, const amg_params& p, hipStream_t
     DevPool wpool;
     wpool.s = s;
     wpool.al = P.al;
-    wpool.hint((size_t)E * (p.hem == 1 ? 8 : 0) + 4 * hem_ext_words(E) + 128 * (size_t)N + 4096 +
+    wpool.hint(SetupWork::bytes((int)N, E, p.hem == 1) +
                (p.alternate ? 12 * (size_t)E + 4 * (size_t)N : 0));
     struct WpoolGuard {
         DevPool& t;

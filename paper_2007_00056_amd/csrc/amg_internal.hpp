@@ -36,6 +36,10 @@ void launch_dinv(int n, const int* rp, const int* ci, const double* v, double* d
 struct HemWork {
     int* rec;         // records of 4, 16 or 32 entries a vertex
     size_t rec_ints;  // room for them
+    int* ent;         // mirror images of the entries of rows that their records do not hold
+    size_t ent_ints;  // room for them
+    bool mirrors = false;  // the current pass has them
+    bool long_rows = false;  // the current pass takes small tiles
     int2* deg;        // [n] lower entries (or extension offset) and higher edge-neighbours
     unsigned* gw;     // [n] a vertex's word as set by other tiles
     unsigned* xw;     // [hem_ext_words(nnz)] extension words of rows with many lower entries
@@ -55,6 +59,8 @@ struct HemWork {
 // Extension words of a pass: a row of more than 31 lower entries takes one word
 // and one per 32 of them (at most 3/32 of their number).
 inline size_t hem_ext_words(int64_t nnz) { return (size_t)(nnz / 10 + 64); }
+size_t hem_rec_ints(int n, int64_t nnz);
+size_t hem_ent_ints(int n, int64_t nnz);
 // Node-based pass (w.cnt must be zeroed before the initialisation): all tiles
 // in one launch.  cnt[7] != 0 afterwards: it did not finish within tmo
 // wall-clock ticks and must be repeated.

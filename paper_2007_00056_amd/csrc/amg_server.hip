@@ -71,10 +71,10 @@ uint64_t footprint(int32_t n, int64_t nnz, const amg_params& p) {
     b += 5 * e * 2 * N + e * N + 3 * N + 4096;  // vectors, column codes
     if (p.precond_fp32) b += 4 * 2 * Z + 4 * 2 * N;
     b += 10 * 8 * N + (1u << 20);
-    // setup scratch at its peak: matching records and state, numbering,
+    // setup scratch at its peak: matching records, codes and state, numbering,
     // Galerkin counts, the intermediate operator of a two-pass level, the
     // dense factorisation
-    b += 256 * N + Z + 60 * N + (4 * N + 12 * Z) + dense;
+    b += 256 * N + 5 * Z + 60 * N + (4 * N + 12 * Z) + dense;
     if (p.hem == 1) b += 8 * Z + 4 * N;            // symmetric weights, pointers
     if (p.alternate) b += 4 * N + 12 * Z + 4096;  // mirrored matrix of a pass from the last index
     return b;

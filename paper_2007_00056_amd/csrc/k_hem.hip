@@ -90,6 +90,9 @@ constexpr int kZeroFlag = 1 << 30;  // deg[].y: the row stores zeros above the d
 // of the list has to be read from the row (a wide neighbour, or one too far).
 constexpr int kMaxDelta = 1 << 26;
 constexpr int kRowEnt = 31;
+// Where a vertex is in the row of a higher edge-neighbour, per entry of its own
+// row: kHas | position, and kWideEnt if the neighbour is wide.  0: no such edge.
+constexpr int kWideEnt = 1 << 31, kHas = 1 << 30;
 __device__ __forceinline__ unsigned low_bits(int p) { return (1u << p) - 1u; }
 }  // namespace
 
@@ -218,6 +221,8 @@ __global__ __launch_bounds__(BS) void k_hem_init(int n, const int* __restrict__ 
 // the record is its rank among the row's, counted through LDS (weights compare
 // as their bit patterns: a strict order, with the column, whatever they are).
 // Rows of more than 2 G entries are ranked by taking the largest R times.
+// A row whose list the record does not hold leaves where its mirror images are in
+// ent, an int per entry, so that the matching need not look for them each time.
 // Every entry's mirror image is looked for, the lower ones' by lanes that would
 // wait, so no sum over the rows is needed: with one add a block to a single
 // word a pass of 65,536 rows took 53 us instead of 13.
@@ -232,14 +237,18 @@ struct InitRow {  // what a row's lanes find together
     bool zero, bad;
 };
 
-// code of y's record entry for its higher neighbour u; false: u's row has no y
-__device__ __forceinline__ bool init_code(const int* __restrict__ rp, const int* __restrict__ ci, int y, int u,
-                                          int& code) {
+// y in the row of its neighbour u: code of y's record entry for u, and where it
+// is (kHas | position, and kWideEnt if u is wide; 0: u's row has no y)
+struct InitEdge {
+    int code, at;
+};
+__device__ __forceinline__ InitEdge init_edge(const int* __restrict__ rp, const int* __restrict__ ci, int y, int u) {
     const int b = rp[u], e = rp[u + 1];
-    const int at = find_col_short(ci, b, e, y);
+    const int pos = find_col_short(ci, b, e, y) - b;
     const int delta = u - y;
-    code = wide_row(ci, b, e, u) || delta >= kMaxDelta ? kRowEnt : (delta << 5) | (at - b);
-    return at >= 0;
+    const bool wide = wide_row(ci, b, e, u);
+    return InitEdge{wide || delta >= kMaxDelta ? kRowEnt : (delta << 5) | pos,
+                    pos >= 0 ? kHas | pos | (wide ? kWideEnt : 0) : 0};
 }
 
 __device__ __forceinline__ unsigned long long weight_bits(double a) { return (unsigned long long)__double_as_longlong(fabs(a)); }
@@ -247,10 +256,11 @@ __device__ __forceinline__ unsigned long long weight_bits(double a) { return (un
 template <int R, int G, int E>
 __device__ __forceinline__ InitRow init_row(int y, int e0, int L, const int* __restrict__ rp,
                                             const int* __restrict__ ci, const double* __restrict__ v,
-                                            unsigned long long* key, int* __restrict__ out) {
+                                            unsigned long long* key, int* __restrict__ out, int* __restrict__ ent) {
     const int lane = threadIdx.x & (G - 1), base = threadIdx.x & (kWave - 1) & ~(G - 1);
     const unsigned group = unsigned((1ull << G) - 1);
-    int u[E], code[E];
+    int u[E];
+    InitEdge in[E];
     double a[E];
     unsigned long long w[E];
 #pragma unroll
@@ -260,11 +270,13 @@ __device__ __forceinline__ InitRow init_row(int y, int e0, int L, const int* __r
         a[t] = k < L ? v[e0 + k] : 0.0;
     }
     InitRow r{0, 0, false, false};
+    bool other = false;  // an entry that a record cannot hold
 #pragma unroll
     for (int t = 0; t < E; ++t) {
-        code[t] = 0;
+        in[t] = InitEdge{0, 0};
         const bool off = u[t] != y;
-        const bool ok = off && init_code(rp, ci, y, u[t], code[t]);
+        if (off) in[t] = init_edge(rp, ci, y, u[t]);
+        const bool ok = in[t].at != 0;
         const bool up = ok && u[t] > y;
         w[t] = up ? weight_bits(a[t]) : 0;
         key[lane + G * t] = w[t];
@@ -272,6 +284,12 @@ __device__ __forceinline__ InitRow init_row(int y, int e0, int L, const int* __r
         r.nh += __popc(unsigned(__ballot(w[t] != 0) >> base) & group);
         r.zero |= (unsigned(__ballot(up && w[t] == 0) >> base) & group) != 0;
         r.bad |= (unsigned(__ballot(off && !ok) >> base) & group) != 0;
+        other |= (unsigned(__ballot(w[t] != 0 && in[t].code == kRowEnt) >> base) & group) != 0;
+    }
+    if (ent && (r.nh > R || other)) {  // a row that the record does not hold
+#pragma unroll
+        for (int t = 0; t < E; ++t)
+            if (lane + G * t < L) ent[e0 + lane + G * t] = w[t] != 0 ? in[t].at : 0;
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     int rank[E] = {};
@@ -285,7 +303,7 @@ __device__ __forceinline__ InitRow init_row(int y, int e0, int L, const int* __r
     }
 #pragma unroll
     for (int t = 0; t < E; ++t)
-        if (w[t] != 0 && rank[t] < R) out[rank[t]] = code[t];
+        if (w[t] != 0 && rank[t] < R) out[rank[t]] = in[t].code;
     for (int q = lane; q < R; q += G)
         if (q >= r.nh) out[q] = 0;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -295,18 +313,24 @@ __device__ __forceinline__ InitRow init_row(int y, int e0, int L, const int* __r
 template <int R, int G>
 __device__ __forceinline__ InitRow init_long_row(int y, int e0, int L, const int* __restrict__ rp,
                                                  const int* __restrict__ ci, const double* __restrict__ v,
-                                                 int* __restrict__ out) {
+                                                 int* __restrict__ out, int* __restrict__ ent) {
     const int lane = threadIdx.x & (G - 1);
     InitRow r{0, 0, false, false};
     for (int k = lane; k < L; k += G) {
         const int u = ci[e0 + k];
         r.nlow += u < y;
-        int code;
-        if (u == y) continue;
-        if (!init_code(rp, ci, y, u, code)) r.bad = true;
-        else if (u < y) continue;
-        else if (weight_bits(v[e0 + k]) == 0) r.zero = true;
-        else ++r.nh;
+        int at = 0;
+        if (u != y) {
+            at = init_edge(rp, ci, y, u).at;
+            if (at == 0) r.bad = true;
+            if (u < y) at = 0;
+            else if (weight_bits(v[e0 + k]) == 0) {
+                r.zero |= at != 0;
+                at = 0;
+            }
+        }
+        r.nh += at != 0;
+        if (ent) ent[e0 + k] = at;
     }
 #pragma unroll
     for (int o = G / 2; o > 0; o >>= 1) {
@@ -338,7 +362,7 @@ __device__ __forceinline__ InitRow init_long_row(int y, int e0, int L, const int
             }
         }
         int code = 0;
-        if (bw != 0) (void)init_code(rp, ci, y, ci[e0 + bk], code);
+        if (bw != 0) code = init_edge(rp, ci, y, ci[e0 + bk]).code;
         if (lane == 0) out[q] = code;
         pw = bw;
         pk = bk;
@@ -355,16 +379,16 @@ __global__ __launch_bounds__(BS) void k_hem_init_group(int n, const int* __restr
                                                        const double* __restrict__ v, int* __restrict__ rec,
                                                        int2* __restrict__ deg, unsigned* __restrict__ gw,
                                                        unsigned* __restrict__ xw, int* __restrict__ mate, int* cnt,
-                                                       int* err) {
+                                                       int* err, int* __restrict__ ent) {
     __shared__ __align__(16) unsigned long long skey[2 * BS];
     const int g = threadIdx.x / G, lane = threadIdx.x & (G - 1);
     unsigned long long* key = skey + g * 2 * G;
     for (int y = blockIdx.x * (BS / G) + g; y < n; y += gridDim.x * (BS / G)) {
         const int e0 = rp[y], L = rp[y + 1] - e0;
         int* out = rec + (size_t)y * R;
-        const InitRow r = L <= G       ? init_row<R, G, 1>(y, e0, L, rp, ci, v, key, out)
-                          : L <= 2 * G ? init_row<R, G, 2>(y, e0, L, rp, ci, v, key, out)
-                                       : init_long_row<R, G>(y, e0, L, rp, ci, v, out);
+        const InitRow r = L <= G       ? init_row<R, G, 1>(y, e0, L, rp, ci, v, key, out, ent)
+                          : L <= 2 * G ? init_row<R, G, 2>(y, e0, L, rp, ci, v, key, out, ent)
+                                       : init_long_row<R, G>(y, e0, L, rp, ci, v, out, ent);
         if (lane == 0) {
             mate[y] = -1;
             gw[y] = 0u;
@@ -391,6 +415,7 @@ struct HemState {
     const double* __restrict__ v;
     const int* __restrict__ rec;
     const int2* __restrict__ deg;
+    const int* __restrict__ ent;  // per entry of rows that their records do not hold: its mirror image; or null
     unsigned* gw;  // words set by other tiles
     unsigned* xw;  // extension words of wide vertices
     int* mate;
@@ -463,28 +488,37 @@ struct Tile {
         if (!wide) set_word(S, j, 1u << pos);
         else or_dev(&S.xw[(S.deg[j].x & ~kWideFlag) + 1 + pos / 32], 1u << (pos % 32));
     }
-    // lower edge `pos` of j is taken
-    __device__ __forceinline__ void taken(const HemState& S, int j, int pos, bool wide) const {
-        if (!wide) {
+    // lower edge `pos` of j, with extension words xo, is taken
+    __device__ __forceinline__ void taken(const HemState& S, int j, int pos, int xo) const {
+        if (xo < 0) {
             set_word(S, j, ~(1u << pos));
             return;
         }
-        unsigned* x = S.xw + (S.deg[j].x & ~kWideFlag);
-        const int words = ((int)x[0] + 31) / 32;
-        for (int k = 0; k < words; ++k) or_dev(&x[1 + k], k == pos / 32 ? ~(1u << (pos % 32)) : ~0u);
         set_word(S, j, kTaken);
+        const int words = ((int)S.xw[xo - 1] + 31) / 32;
+        for (int k = 0; k < words; ++k) or_dev(&S.xw[xo + k], k == pos / 32 ? ~(1u << (pos % 32)) : ~0u);
     }
-    // j for its lower edge `pos`, from j's word wj
-    __device__ __forceinline__ int state(const HemState& S, int j, int pos, bool wide, unsigned wj) const {
+    // a wide vertex's extension words (-1: the vertex is not wide)
+    __device__ __forceinline__ int ext(const HemState& S, int j, bool wide) const {
+        return wide ? (S.deg[j].x & ~kWideFlag) + 1 : -1;
+    }
+    // a vertex for its lower edge `pos`, from its word wj and extension words xo
+    __device__ __forceinline__ int state(const HemState& S, int pos, int xo, unsigned wj) const {
         bool full;
-        if (!wide) {
+        if (xo < 0) {
             full = (~wj & low_bits(pos)) == 0u;
         } else {
-            const unsigned* x = S.xw + (S.deg[j].x & ~kWideFlag) + 1;
             full = true;
-            for (int k = 0; 32 * k < pos && full; ++k) {
-                const unsigned need = pos - 32 * k >= 32 ? ~0u : low_bits(pos - 32 * k);
-                full = (~load_dev(&x[k]) & need) == 0u;
+            for (int k0 = 0; 32 * k0 < pos && full; k0 += 4) {  // four loads in flight
+                unsigned x[4];
+                const int last = (pos - 1) / 32;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) x[k] = load_dev(&S.xw[xo + min(k0 + k, last)]);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int need = pos - 32 * min(k0 + k, last);
+                    full &= (~x[k] & (need >= 32 ? ~0u : low_bits(need))) == 0u;
+                }
             }
             settle();
         }
@@ -492,30 +526,40 @@ struct Tile {
     }
 };
 
-// By a whole wave, on one vertex u: its heaviest higher edge-neighbour not
-// known to be unavailable (lowest column on ties).  Returns the neighbour (-1:
-// none), its position and state.
-__device__ __forceinline__ int wave_choice(const HemState& S, const Tile& T, int u, int& pos, bool& wide, int& st) {
+// Entry e of u's row, as kHas | .. above; j: its column.
+__device__ __forceinline__ int row_edge(const HemState& S, int u, int e, int j) {
+    if (S.ent) return S.ent[e];
+    if (j <= u || S.v[e] == 0.0) return 0;
+    const int b = S.rp[j], e1 = S.rp[j + 1];
+    return kHas | (find_col(S.ci, b, e1, u) - b) | (wide_row(S.ci, b, e1, j) ? kWideEnt : 0);
+}
+__device__ __forceinline__ int edge_pos(int at) { return at & (kHas - 1); }
+
+// A vertex's choice from its row: the neighbour (-1: none), its position and
+// extension words, and its state.
+struct RowChoice {
+    int j, pos, xo, st;
+};
+
+// By a whole wave, on one vertex u with row entries b .. e1 - 1: its heaviest
+// higher edge-neighbour not known to be unavailable (lowest column on ties).
+__device__ __forceinline__ RowChoice wave_choice(const HemState& S, const Tile& T, int u, int b, int e1) {
     const int lane = threadIdx.x % kWave;
     unsigned long long bw = 0;
-    int bj = INT_MAX, bp = 0, bs = kUnknown;
-    bool bwide = false;
-    for (int e = S.rp[u] + lane; e < S.rp[u + 1]; e += kWave) {
-        const int j = S.ci[e];
-        const double a = fabs(S.v[e]);
-        if (j <= u || a == 0.0) continue;
-        const int b = S.rp[j], e1 = S.rp[j + 1];
-        const int p = find_col(S.ci, b, e1, u) - b;
-        const bool wd = wide_row(S.ci, b, e1, j);
-        const int s = T.state(S, j, p, wd, T.word(S, j));
+    int bj = INT_MAX, bp = 0, bs = kUnknown, bx = -1;
+    for (int e = b + lane; e < e1; e += kWave) {
+        const int j = S.ci[e], at = row_edge(S, u, e, j);
         // non-negative doubles order as their bits do; every weight is nonzero
-        const unsigned long long w = (unsigned long long)__double_as_longlong(a);
+        const unsigned long long w = weight_bits(S.v[e]);
+        if (at == 0) continue;
+        const int xo = T.ext(S, j, at < 0);
+        const int s = T.state(S, edge_pos(at), xo, T.word(S, j));
         if (s != kGone && (w > bw || (w == bw && j < bj))) {
             bw = w;
             bj = j;
-            bp = p;
+            bp = edge_pos(at);
             bs = s;
-            bwide = wd;
+            bx = xo;
         }
     }
     unsigned long long mw = bw;
@@ -528,21 +572,27 @@ __device__ __forceinline__ int wave_choice(const HemState& S, const Tile& T, int
             mj = oj;
         }
     }
-    if (mj == INT_MAX) return -1;
+    if (mj == INT_MAX) return RowChoice{-1, 0, -1, kGone};
     const int src = __ffsll((long long)__ballot(bj == mj)) - 1;  // each column is held by one lane
-    pos = __shfl(bp, src);
-    wide = __shfl((int)bwide, src) != 0;
-    st = __shfl(bs, src);
-    return mj;
+    return RowChoice{mj, __builtin_amdgcn_readlane(bp, src), __builtin_amdgcn_readlane(bx, src),
+                     __builtin_amdgcn_readlane(bs, src)};
 }
 
-// By a whole wave: every higher edge of u but the one to `keep` is dead.
-__device__ __forceinline__ void wave_dead(const HemState& S, const Tile& T, int u, int keep) {
-    for (int e = S.rp[u] + (int)(threadIdx.x % kWave); e < S.rp[u + 1]; e += kWave) {
-        const int j = S.ci[e];
-        if (j <= u || j == keep || S.v[e] == 0.0) continue;
-        const int b = S.rp[j], e1 = S.rp[j + 1];
-        T.dead(S, j, find_col(S.ci, b, e1, u) - b, wide_row(S.ci, b, e1, j));
+// By a whole wave: every higher edge of u (row entries b .. e1 - 1) but the one
+// to `keep` is dead.
+__device__ __forceinline__ void wave_dead(const HemState& S, const Tile& T, int u, int b, int e1, int keep) {
+    constexpr int B = 4;  // entries of a lane in flight together
+    for (int e0 = b + (int)(threadIdx.x % kWave); e0 < e1; e0 += B * kWave) {
+        int j[B], at[B];
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            const int e = e0 + k * kWave;
+            j[k] = e < e1 ? S.ci[e] : keep;
+            at[k] = e < e1 ? row_edge(S, u, e, j[k]) : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < B; ++k)
+            if (at[k] != 0 && j[k] != keep) T.dead(S, j[k], edge_pos(at[k]), at[k] < 0);
     }
 }
 
@@ -704,9 +754,12 @@ __global__ __launch_bounds__(NT) void k_hem_tile(HemState S, int rows, int* cnt,
     unsigned st = 0, mo = kNever, mt = kNever;
     int to = TM, ta = TM;
     bool zeros = false;
+    int rb = 0, re = 0;  // the row
     if (l < m) {
         const int2 d = S.deg[u];
         const int b = S.rp[u];
+        rb = b;
+        re = S.rp[u + 1];
         const int c = d.y & ~kZeroFlag;
         zeros = (d.y & kZeroFlag) != 0;
         if (c > R) st |= vMore;
@@ -737,7 +790,7 @@ __global__ __launch_bounds__(NT) void k_hem_tile(HemState S, int rows, int* cnt,
     }
     __syncthreads();
     if (zeros) {  // stored zeros are no edges: dead from the start
-        for (int e = S.rp[u]; e < S.rp[u + 1]; ++e) {
+        for (int e = rb; e < re; ++e) {
             const int j = S.ci[e];
             if (j <= u || S.v[e] != 0.0) continue;
             const int b = S.rp[j], e1 = S.rp[j + 1];
@@ -755,8 +808,12 @@ __global__ __launch_bounds__(NT) void k_hem_tile(HemState S, int rows, int* cnt,
         if (jl < m) T.set(jl, 1u << (q & 31));
         else or_dev(&S.gw[off + jl], 1u << (q & 31));
     };
-    int cj = -1, cp = 0;  // choices from the row: vertex, position
-    bool cw = false;      // and whether it is wide
+    int xa = 0, xe = 0;  // a wide vertex's extension words, those known to be full left out
+    if (st & vWide) {
+        xa = (S.deg[u].x & ~kWideFlag) + 1;
+        xe = xa + ((int)S.xw[xa - 1] + 31) / 32;
+    }
+    int cj = -1, cp = 0, cx = -1;  // the choice from the row: vertex, position, extension words
     int4* const sel = s_sel + base / kWave * NG;
     const long long t_start = wall_clock64();
     int sweeps = 0;
@@ -774,14 +831,21 @@ __global__ __launch_bounds__(NT) void k_hem_tile(HemState S, int rows, int* cnt,
             if (__ballot((st & vRare) != 0) != 0) {
                 // wide vertices and choices from the row: their words in global memory
                 if ((st & vWide) && to != TM) {
-                    const unsigned* x = S.xw + (S.deg[u].x & ~kWideFlag);
-                    const int words = ((int)x[0] + 31) / 32;
-                    bool all = true;
-                    for (int i = 0; i < words && all; ++i) all = load_dev(&x[1 + i]) == ~0u;
-                    const unsigned g = load_dev(&S.gw[u]) | (all ? kAllDead : 0u);
+                    // the words from the first that was not full, four at a time
+                    const unsigned g0 = load_dev(&S.gw[u]);
+                    unsigned x[4];
+                    bool on;
+                    do {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) x[i] = load_dev(&S.xw[min(xa + i, xe - 1)]);
+                        on = (x[0] & x[1] & x[2] & x[3]) == ~0u;
+                        if (on) xa = min(xa + 4, xe);
+                    } while (on && xa < xe);
+                    const unsigned g = g0 | (xa == xe ? kAllDead : 0u);
                     if (g != 0u) T.set(l, g);
                 }
-                if ((st & vRow) && !(st & vConf) && to != TM && cj >= 0 && T.state(S, cj, cp, cw, T.word(S, cj)) != kUnknown) mt = 0u;
+                if ((st & vRow) && !(st & vConf) && to != TM && cj >= 0 && T.state(S, cp, cx, T.word(S, cj)) != kUnknown)
+                    mt = 0u;
                 settle();
             }
             __builtin_amdgcn_s_sleep(2);
@@ -797,42 +861,43 @@ __global__ __launch_bounds__(NT) void k_hem_tile(HemState S, int rows, int* cnt,
                 row &= row - 1;
                 const unsigned ow = __builtin_amdgcn_readlane(own, src);
                 unsigned f = __builtin_amdgcn_readlane(st, src);
-                int j = __builtin_amdgcn_readlane(cj, src), pos = __builtin_amdgcn_readlane(cp, src);
-                bool wide = __builtin_amdgcn_readlane((int)cw, src) != 0;
+                RowChoice c{__builtin_amdgcn_readlane(cj, src), __builtin_amdgcn_readlane(cp, src),
+                            __builtin_amdgcn_readlane(cx, src), kGone};
+                const int b = __builtin_amdgcn_readlane(rb, src), e1 = __builtin_amdgcn_readlane(re, src);
                 const int v = off + base + src;
                 bool done = false;
                 if (ow & kTaken) {
-                    wave_dead(S, T, v, -1);
+                    wave_dead(S, T, v, b, e1, -1);
                     done = true;
                 } else {
                     if (!(f & vConf)) {
-                        int s = j >= 0 ? T.state(S, j, pos, wide, T.word(S, j)) : kGone;
-                        if (s == kGone) j = wave_choice(S, T, v, pos, wide, s);
-                        if (j < 0) {
+                        if (c.j >= 0) c.st = T.state(S, c.pos, c.xo, T.word(S, c.j));
+                        if (c.st == kGone) c = wave_choice(S, T, v, b, e1);
+                        if (c.j < 0) {
                             f |= vConf;  // no neighbour left
-                        } else if (s == kAvail) {
+                        } else if (c.st == kAvail) {
                             f |= vConf;
-                            wave_dead(S, T, v, j);
+                            wave_dead(S, T, v, b, e1, c.j);
                         }
                     }
                     if (ow == kAllDead && (f & vConf)) {
-                        if (j >= 0 && lane == 0) {
-                            S.mate[v] = j;
-                            S.mate[j] = v;
-                            T.taken(S, j, pos, wide);
+                        if (c.j >= 0 && lane == 0) {
+                            S.mate[v] = c.j;
+                            S.mate[c.j] = v;
+                            T.taken(S, c.j, c.pos, c.xo);
                         }
-                        if (j >= 0 && !wide && j < off + m) {
-                            const int q = lane < R ? s_e[lane * ES + (j - off)] : 0;
-                            if (q > kRowEnt) mark(j - off, q);
+                        if (c.j >= 0 && c.xo < 0 && c.j < off + m) {
+                            const int q = lane < R ? s_e[lane * ES + (c.j - off)] : 0;
+                            if (q > kRowEnt) mark(c.j - off, q);
                         }
                         done = true;
                     }
                 }
                 if (lane == src) {
                     st = f | vRare;
-                    cj = j;
-                    cp = pos;
-                    cw = wide;
+                    cj = c.j;
+                    cp = c.pos;
+                    cx = c.xo;
                     ta = TM;
                     mt = kNever;
                     mo = f & vConf ? kAllDead : kNever;
@@ -841,8 +906,8 @@ __global__ __launch_bounds__(NT) void k_hem_tile(HemState S, int rows, int* cnt,
                         mo = kNever;
                     }
                 }
-                settle();
             }
+            settle();
         }
         // the others, NG at a time: a group of G lanes each, E record entries a lane
         const int rank = __builtin_amdgcn_mbcnt_hi((unsigned)(todo >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)todo, 0u));
@@ -936,7 +1001,8 @@ __global__ __launch_bounds__(NT) void k_hem_tile(HemState S, int rows, int* cnt,
             while (rest != 0) {
                 const int src = __ffsll((long long)rest) - 1;
                 rest &= rest - 1;
-                wave_dead(S, T, off + base + src, __builtin_amdgcn_readlane(more, src));
+                wave_dead(S, T, off + base + src, __builtin_amdgcn_readlane(rb, src),
+                          __builtin_amdgcn_readlane(re, src), __builtin_amdgcn_readlane(more, src));
             }
             settle();
         }
@@ -1124,13 +1190,27 @@ static int hem_record(int n, int64_t nnz, size_t room) {
     return r == 32 && (size_t)n * 32 > room ? 16 : r;
 }
 
+constexpr int kLongRows = 32;  // entries a row on average: above, passes take tiles of
+constexpr int kLongTile = 8;   // this many rows (see launch_hem_tile)
+
+// Room for the records of every pass of a setup (a later pass has fewer rows, but
+// may have longer ones), and for the mirror images of rows that records do not
+// hold: a first pass of short rows has next to none.
+size_t hem_rec_ints(int n, int64_t nnz) { return (nnz > 14 * (int64_t)n ? 32 : 16) * (size_t)n; }
+size_t hem_ent_ints(int n, int64_t nnz) { return (size_t)(2 * nnz <= 15 * (int64_t)n ? nnz / 2 : nnz); }
+
 void launch_hem_init(int n, int64_t nnz, const int* rp, const int* ci, const double* v, HemWork& w, hipStream_t s) {
     w.side = hem_record(n, nnz, w.rec_ints);
-#define CALL(K, grid)                                                                                            \
-    hipLaunchKernelGGL(K, dim3(grid), dim3(BS), 0, s, n, rp, ci, v, w.rec, w.deg, w.gw, w.xw, w.mate, w.cnt, w.err)
-    if (w.side == 32) CALL((k_hem_init_group<32, 32>), blocks_for(n, BS / 32, kInitBlocks));
-    else if (w.side == 16) CALL((k_hem_init_group<16, 16>), blocks_for(n, BS / 16, kInitBlocks));
-    else if (n <= kInitThread) CALL((k_hem_init_group<4, 16>), blocks_for(n, BS / 16, kInitBlocks));
+    const bool thread = w.side == 4 && n > kInitThread;
+    w.long_rows = nnz > kLongRows * (int64_t)n;
+    w.mirrors = !thread && (size_t)nnz <= w.ent_ints;
+    int* const ent = w.mirrors ? w.ent : nullptr;
+#define CALL(K, grid, ...)                                                                                       \
+    hipLaunchKernelGGL(K, dim3(grid), dim3(BS), 0, s, n, rp, ci, v, w.rec, w.deg, w.gw, w.xw, w.mate, w.cnt, w.err, \
+                       ##__VA_ARGS__)
+    if (w.side == 32) CALL((k_hem_init_group<32, 32>), blocks_for(n, BS / 32, kInitBlocks), ent);
+    else if (w.side == 16) CALL((k_hem_init_group<16, 16>), blocks_for(n, BS / 16, kInitBlocks), ent);
+    else if (!thread) CALL((k_hem_init_group<4, 16>), blocks_for(n, BS / 16, kInitBlocks), ent);
     else CALL(k_hem_init, blocks_for(n));
 #undef CALL
 }
@@ -1144,13 +1224,24 @@ void launch_hem_init(int n, int64_t nnz, const int* rp, const int* ci, const dou
 //   long rows, 16,533 rows of 18.6 entries       0.86 / 0.83 / 0.75 ms
 //   long rows, 4,440 rows of 18.8 entries        0.47 / 0.51 / 0.54 ms
 constexpr int kFewRows = 10000;  // long rows: up to here the large tiles win
+// Rows longer than that are mostly wide, or have neighbours that are, and are
+// then read again by a whole wave, one vertex after the other: a wave takes few
+// vertices.  Their words are in memory anyhow, so little is lost between tiles.
+// Pass times with tiles of 2 / 8 / 16 / 64 rows / as many as a workgroup takes:
+//   10,978 rows of 104 entries     1.65 / 2.00 / 2.43 / 4.14 / 4.40 ms
+//    2,748 rows of 81 entries      0.85 / 1.08 / 1.31 / 2.15 / 3.76 ms
+//    5,488 rows of 39 entries      0.32 / 0.26 / 0.27 / 0.33 / 0.34 ms
+//    2,744 rows of 23 entries      0.23 / 0.17 / 0.20 / 0.28 / 0.28 ms
+//       89 rows of 25 entries      0.08 / 0.08 / 0.09 / 0.10 / 0.10 ms
+//      686 rows of 21 entries      0.13 / 0.11 / 0.11 / 0.12 / 0.08 ms
 
 void launch_hem_tile(int n, const int* rp, const int* ci, const double* v, HemWork& w, long long tmo,
                      hipStream_t s) {
-    const HemState S{n, rp, ci, v, w.rec, w.deg, w.gw, w.xw, w.mate};
+    const HemState S{n, rp, ci, v, w.rec, w.deg, w.mirrors ? w.ent : nullptr, w.gw, w.xw, w.mate};
+    const bool long_rows = w.long_rows && w.side == 32;
 #define CALL(R, NT)                                                                                               \
     {                                                                                                             \
-        const int tm = NT - 2 * kWave;                                                                            \
+        const int tm = long_rows ? kLongTile : NT - 2 * kWave;                                                    \
         const int rows = w.tile_rows > 0 && w.tile_rows < tm ? w.tile_rows : tm;                                  \
         hipLaunchKernelGGL((k_hem_tile<R, NT>), dim3((unsigned)(((int64_t)n + rows - 1) / rows)), dim3(NT), 0, s, \
                            S, rows, w.cnt, w.err, tmo);                                                           \
@@ -1158,7 +1249,7 @@ void launch_hem_tile(int n, const int* rp, const int* ci, const double* v, HemWo
     if (w.side == 4) CALL(4, 512)
     else if (w.side == 16 && n > kFewRows) CALL(16, 256)
     else if (w.side == 16) CALL(16, 1024)
-    else if (n > kFewRows) CALL(32, 256)
+    else if (n > kFewRows || long_rows) CALL(32, 256)
     else CALL(32, 1024)
 #undef CALL
 }

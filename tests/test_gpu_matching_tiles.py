@@ -40,13 +40,14 @@ def band(n, width, reach, seed, zeros=0.0, hubs=()):
     return symmetric(n, i, j, w)
 
 
-def form(n, nnz, n0):
+def form(n, nnz, n0, nnz0):
     """Record entries and threads a workgroup of a pass over n rows, of a setup of n0 rows."""
     avg = nnz / n
     rec = 4 if avg <= 7.5 else 16 if avg <= 14.0 else 32
-    if rec == 32 and 32 * n > 16 * n0:
+    if rec == 32 and 32 * n > (32 if nnz0 > 14 * n0 else 16) * n0:
         rec = 16
-    return rec, 512 if rec == 4 else 256 if n > 10000 else 1024
+    long_rows = rec == 32 and avg > 32.0  # tiles of 8 rows by themselves
+    return rec, 512 if rec == 4 else 256 if n > 10000 or long_rows else 1024
 
 
 CASES = {  # the matrix, and the forms its passes take
@@ -54,14 +55,15 @@ CASES = {  # the matrix, and the forms its passes take
     "short rows, stored zeros": (lambda: band(1500, 3, 90, 2, zeros=0.15), {(4, 512)}),
     "mid rows": (lambda: band(1500, 5, 200, 3, zeros=0.1), {(16, 1024)}),
     "mid rows, many": (lambda: band(12007, 5, 300, 4), {(16, 256)}),
-    "long rows": (lambda: band(1500, 16, 300, 5, zeros=0.1), {(16, 1024), (32, 1024)}),
-    "long rows, many": (lambda: band(42011, 14, 500, 6, zeros=0.05), {(16, 256), (32, 256)}),
-    "hubs": (lambda: band(1500, 3, 60, 7, zeros=0.1, hubs=(0, 400, 1100, 1499)), {(16, 1024)}),
+    "long rows": (lambda: band(1500, 16, 300, 5, zeros=0.1), {(32, 1024)}),
+    "long rows, many": (lambda: band(42011, 14, 500, 6, zeros=0.05), {(32, 256)}),
+    "very long rows": (lambda: band(1300, 40, 400, 8, zeros=0.1, hubs=(700,)), {(32, 256)}),
+    "hubs": (lambda: band(1500, 3, 60, 7, zeros=0.1, hubs=(0, 400, 1100, 1499)), {(32, 1024)}),
 }
 
 
 @pytest.mark.parametrize("alternate", [0, 1])
-@pytest.mark.parametrize("tile", [1, 37, 64, 101])
+@pytest.mark.parametrize("tile", [0, 1, 37, 64, 101])
 @pytest.mark.parametrize("name", list(CASES))
 def test_small_tiles(name, tile, alternate, monkeypatch):
     print("case", name, "tile", tile, alternate, flush=True)
@@ -70,5 +72,5 @@ def test_small_tiles(name, tile, alternate, monkeypatch):
     a = make()
     with hemamg.Hierarchy(hemamg.DeviceCSR.from_host(a, device="cuda:0"), alternate=alternate) as g:
         s = g.stats()
-        assert forms <= {form(n, z, a.n) for n, z in zip(s["pass_n"], s["pass_nnz"])}
+        assert forms <= {form(n, z, a.n, a.nnz) for n, z in zip(s["pass_n"], s["pass_nnz"])}
         assert_same_hierarchy(g, oracle.Hierarchy(a, alternate=alternate))

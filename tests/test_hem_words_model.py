@@ -150,6 +150,9 @@ def words_model(a, T, rng, bits=31, packed=True):
                     j, pos = hs[at[u]]
                     mate[u], mate[j] = j, u
                     taken(j, pos)
+                    if rng.random() < 0.5:  # whoever takes a vertex may make its edges dead, before it knows itself
+                        for i, q in higher[j]:
+                            dead(i, q)
                 done[u] = True
         if done[u]:
             todo.remove(u)
