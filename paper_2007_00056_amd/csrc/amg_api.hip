@@ -606,7 +606,7 @@ inline int stream_order(const amg_hier* h, const Level& L) {
     if (L.n >= h->stream_min) return 0;
     if (L.n < h->mid_min) return -1;
     if (L.code && !h->prec32) return 0;
-    return L.lpr == 4 || L.lpr == 8 ? L.lpr : -1;
+    return (L.lpr == 4 || L.lpr == 8) && L.nnz <= (int64_t)kLongRow * L.n ? L.lpr : -1;
 }
 inline bool streamed(const amg_hier* h, const Level& L) { return stream_order(h, L) >= 0; }
 

@@ -370,7 +370,9 @@ struct amg_hier {
     // 218,265 rows of 11.3 entries (97 x 101 x 89, single precision) takes
     // 103.5 us (118.2 with lane groups there), one with 216,611 rows on a double
     // level 0 72.2 (82.0).  Levels of 54,000 to 64,000 rows gain nothing (73.2
-    // against 72.2), smaller ones lose the fused restriction.
+    // against 72.2), smaller ones lose the fused restriction.  Nor do long rows
+    // (kLongRow): on 65,536 rows of 65 entries the steps take 45 us, with lane
+    // groups 30; at 128,000 rows of 26 it is 33 and 36.
     int mid_min = 65536;
     // Levels that run the CSR-stream kernels are given column codes, in double
     // from mid_min rows on, and level 0 from this many on (the Krylov methods'
