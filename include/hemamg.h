@@ -231,7 +231,9 @@ amg_status amg_timing_read(amg_hier* h, int32_t kernel, int64_t* launches, doubl
  * the order of a row's additions.  schedule: [host] int32[levels] or NULL;
  * receives rows per block for CSR-stream levels, minus the lanes per row for
  * lane-group levels, 0 for the coarsest (all 0 when pre/post are not 1, whose
- * path has one schedule).  Overwrites the handle's work vectors; blocks the
+ * path has one schedule).  Levels without a choice keep theirs and report 256:
+ * the small ones that run in one workgroup, and CSR-stream kernels on rows whose
+ * columns are coded.  Overwrites the handle's work vectors; blocks the
  * host.  Errors: AMG_EINVAL, AMG_EHIP. */
 amg_status amg_autotune(amg_hier* h, void* stream, int32_t* schedule);
 
@@ -380,7 +382,7 @@ amg_status amg_batch_levels(const amg_batch* b, int32_t* levels);
  * CSR-stream kernels, chosen by timing the level's steps on this batch.
  * Results do not change (a row's sum is formed in entry order whatever the
  * block size).  schedule: [host] int32[levels] or NULL (0 for the last
- * level).  Blocks the host.  Errors: AMG_EINVAL, AMG_EHIP. */
+ * level; 256 where there is no choice, see amg_autotune).  Blocks the host.  Errors: AMG_EINVAL, AMG_EHIP. */
 amg_status amg_batch_autotune(amg_batch* b, void* stream, int32_t* schedule);
 
 /* Frees the batch.  NULL is accepted. */

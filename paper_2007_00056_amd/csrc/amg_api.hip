@@ -1421,8 +1421,10 @@ void setup_impl(const amg_csr* Ain, const amg_params* pin, const amg_allocator* 
 // hierarchy (both steps of the level, several repetitions after a warm-up):
 // CSR-stream kernels with 128, 256 or 512 rows per block, or lane-group
 // kernels with 2, 4 or 8 lanes per row.  The schedules differ only in the
-// order of a row's additions.  (The levels that run in one workgroup keep to it;
-// theirs applies only without that.)
+// order of a row's additions.  Where there is no choice none is timed: levels that
+// run in one workgroup keep to it, and rows read by column codes take 256 rows a
+// block whatever is asked.  A mid-size level's own schedule (CSR-stream in the
+// lane-group order) takes part.
 // ---------------------------------------------------------------------------
 template <class T>
 void tune_level_steps(amg_hier* h, int k, hipStream_t s) {
@@ -1485,13 +1487,20 @@ void autotune_impl(amg_hier* h, hipStream_t s, int32_t* out) {
     struct Cand {
         int sched, rb;
     };
-    const Cand cands[] = {{0, 128}, {0, 256}, {0, 512}, {2, 256}, {4, 256}, {8, 256}};
+    const Cand cands[] = {{0, 128}, {0, 256}, {0, 512}, {2, 256}, {4, 256}, {8, 256}, {-1, 256}};
     const int reps = 5;
     for (int k = 0; k + 1 < nl; ++k) {
         Level& Lk = h->lev[k];
+        if (h->tail && k >= h->tail) {
+            if (out) out[k] = 256;
+            continue;
+        }
         float best = 1e30f;
         Cand pick{-1, 256};
+        Lk.sched = -1;
+        const bool own = stream_order(h, Lk) > 0;
         for (const Cand& c : cands) {
+            if ((c.sched == 0 && c.rb != 256 && Lk.code) || (c.sched < 0 && !own)) continue;
             Lk.sched = c.sched;
             Lk.rb = c.rb;
             auto step = [&] {
@@ -1513,7 +1522,7 @@ void autotune_impl(amg_hier* h, hipStream_t s, int32_t* out) {
         }
         Lk.sched = pick.sched;
         Lk.rb = pick.rb;
-        if (out) out[k] = pick.sched == 0 ? pick.rb : -pick.sched;
+        if (out) out[k] = pick.sched <= 0 ? pick.rb : -pick.sched;
     }
     h->drop_graphs();
     HIPCHK(hipStreamSynchronize(s));

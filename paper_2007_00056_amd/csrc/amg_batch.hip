@@ -1056,6 +1056,7 @@ void batch_autotune(amg_batch* B, hipStream_t caller, int32_t* out) {
         float best = 1e30f;
         int pick = 256;
         for (int rb : cand) {
+            if (L.code && rb != 256) continue;  // coded rows: always 256 a block
             L.rb = rb;
             auto step = [&] {
                 if (B->prec32) batch_level_steps<float>(B, k, s);
