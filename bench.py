@@ -61,14 +61,36 @@ def level_sizes(h, hemamg):
     return [hemamg.amg_level_size(h, k) for k in range(L)]
 
 
-STREAM_MIN = 262144  # levels with at least this many rows use the CSR-stream kernels
+# The library's rules for the rows of a level: from STREAM_MIN rows on the CSR-stream
+# kernels run, below that and from MID_MIN on those too unless rows are long;
+# column codes are made from these many rows on (level 0: CODE_MIN), of at most 8
+# entries each, and used if at most one slice of 64 rows in 64 lacks one.
+STREAM_MIN, MID_MIN, CODE_MIN, LONG_ROW = 262144, 65536, 4096, 32
 
 
-CODE_MIN = 4096  # level 0 from this many rows on, of at most 8 entries each, is read through column codes
+def slices_fit(rp, ci):
+    """Whether nearly all slices of 64 rows have at most 8 distances from the diagonal and no longer row."""
+    n = len(rp) - 1
+    row = np.repeat(np.arange(n, dtype=np.int64), np.diff(rp))
+    d = np.unique((row // 64 << 33) + (ci - row + n))
+    over = np.bincount(d >> 33, minlength=(n + 63) // 64) > 8
+    over |= np.maximum.reduceat(np.diff(rp), np.arange(0, n, 64)) > 8
+    return int(over.sum()) * 64 <= len(over)
 
 
-def coded_rows(n, nnz):
-    return n >= CODE_MIN and nnz <= 8 * n
+def row_kinds(sizes, e, arrays):
+    """Per smoothing level: (its rows have codes, what its V-cycle kernels are: "coded", "stream" or "group").
+    arrays(k): level k's row pointers and columns.  (The smallest levels, which run in one workgroup on less than
+    112 KB, are priced as lane groups.)"""
+    kinds = []
+    for k, (n, nnz) in enumerate(sizes[:-1]):
+        least = CODE_MIN if k == 0 else MID_MIN if e == 8 else STREAM_MIN
+        codes = n >= least and nnz <= 8 * n and slices_fit(*arrays(k))
+        if n >= STREAM_MIN or (n >= MID_MIN and codes and e == 8):
+            kinds.append((codes, "coded" if codes else "stream"))
+        else:
+            kinds.append((codes, "stream" if n >= MID_MIN and 2 * n < nnz <= LONG_ROW * n else "group"))
+    return kinds
 
 
 def rows_bytes(n, nnz, e, coded):
@@ -77,10 +99,11 @@ def rows_bytes(n, nnz, e, coded):
     return e * nnz + 2 * n if coded else (e + 4) * nnz + 4 * (n + 1)
 
 
-def kernel_bytes(sizes, e, method, coded=False):
+def kernel_bytes(sizes, e, method, coded=False, spmv_coded=None):
     """Bytes each timed level-0 kernel moves as implemented: preconditioner
     values and vectors of e bytes (8 double, 4 float), int32 indices or column
-    codes, the level-0 right-hand side and result in double; every array
+    codes (coded: the V-cycle's kernels; spmv_coded: the outer product, default
+    the same), the level-0 right-hand side and result in double; every array
     counted once."""
     (n, nnz) = sizes[0]
     csr = rows_bytes(n, nnz, e, coded)
@@ -92,7 +115,7 @@ def kernel_bytes(sizes, e, method, coded=False):
         # presmoothing + residual: g gather, r read (8 n), residual write
         1: csr + 2 * e * n + 8 * n,
         # outer SpMV + dot, always double: p read + q write
-        2: rows_bytes(n, nnz, 8, coded) + 16 * n,
+        2: rows_bytes(n, nnz, 8, coded if spmv_coded is None else spmv_coded) + 16 * n,
     }
 
 
@@ -124,16 +147,16 @@ def host_cpu():
     return {"nproc": nproc, "model": model}
 
 
-def level_bytes(k, sizes, e):
-    """One V-cycle level k (down + up sweep) in the fused form, values and
+def level_bytes(k, sizes, e, kind):
+    """One V-cycle level k (down + up sweep) by kernels of that kind, values and
     vectors of e bytes; level 0 reads its right-hand side in double."""
     n, nnz = sizes[k]
     nc = sizes[k + 1][0]
     nf = sizes[k - 1][0] if k > 0 else 0
-    csr = rows_bytes(n, nnz, e, k == 0 and n >= STREAM_MIN and coded_rows(n, nnz))
+    csr = rows_bytes(n, nnz, e, kind == "coded")
     fin = 8 if k == 0 else e
     scatter = (16 * n + 2 * e * nf) if k > 0 else 0  # members + finer g read + finer xp write
-    if n >= STREAM_MIN:
+    if kind != "group":
         down = (csr + (fin + 2 * e) * n) + (e * n + (16 + 3 * e) * nc)  # residual, restriction (+ g_c)
     else:
         down = csr + (fin + e) * n + (16 + 3 * e) * nc  # fused residual + restriction
@@ -141,14 +164,14 @@ def level_bytes(k, sizes, e):
     return down + up
 
 
-def iteration_bytes(sizes, method, e):
-    """Algorithmic bytes of one Krylov iteration (V-cycle + outer kernels)."""
-    vc = sum(level_bytes(k, sizes, e) for k in range(len(sizes) - 1))
+def iteration_bytes(sizes, method, e, kinds):
+    """Algorithmic bytes of one Krylov iteration (V-cycle + outer kernels); kinds: see row_kinds."""
+    vc = sum(level_bytes(k, sizes, e, kinds[k][1]) for k in range(len(sizes) - 1))
     m = sizes[-1][0]
     vc += 8 * m * m + 2 * e * m + (16 * m + 2 * e * sizes[-2][0] if len(sizes) > 1 else 0)
     n, nnz = sizes[0]
     vc += (8 - e) * n  # level-0 result in double
-    spmv = rows_bytes(n, nnz, 8, coded_rows(n, nnz)) + 16 * n
+    spmv = rows_bytes(n, nnz, 8, bool(kinds) and kinds[0][0]) + 16 * n
     if method == "pcg":
         # spmv+dot, update (x,r,p,q,dinv read; x,r write; g write), (r,z) in the V-cycle, direction (z,p read; p write)
         return vc + spmv + 8 * n + 56 * n + e * n + 24 * n
@@ -394,9 +417,12 @@ def main():
     iters = recs[-1]["iters"]
     setup_ms = float(np.median([r["setup_ms"] for r in recs]))
     solve_ms = float(np.median([r["solve_ms"] for r in recs]))
-    it_bytes = iteration_bytes(sizes, method, esz)
-    coded = coded_rows(*sizes[0])
-    kb = kernel_bytes(sizes, esz, method, coded)
+    h = hemamg.amg_setup(A, params)  # once more, untimed: which levels' rows are read through codes
+    kinds = row_kinds(sizes, esz, lambda k: hemamg.amg_export_level(h, k)[:2])
+    hemamg.amg_destroy(h)
+    it_bytes = iteration_bytes(sizes, method, esz, kinds)
+    coded = bool(kinds) and kinds[0][1] == "coded"
+    kb = kernel_bytes(sizes, esz, method, coded, bool(kinds) and kinds[0][0])
     names = {0: "k_vc_post (level 0)", 1: "k_vc_resid (level 0)", 2: "k_stream_spmv_dot (outer SpMV)"}
     kernels = {}
     for k, (c, ms) in kern_tot.items():
