@@ -1,6 +1,5 @@
-// Device-side helpers shared by the gfx950 kernels: wavefront reductions,
-// XCD-aware block mapping, coherent loads and a register-resident sorted
-// accumulator.  Wavefronts are 64 lanes wide on CDNA4.
+// Device-side helpers shared by the gfx950 kernels: wavefront and block
+// reductions, XCD-aware block mapping.  Wavefronts are 64 lanes wide on CDNA4.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -85,52 +84,5 @@ __device__ __forceinline__ double block_sum_partials(const double* __restrict__ 
     __syncthreads();
     return tot;
 }
-
-// Sorted list of up to CAP (key, sum) pairs kept in registers (all indexing
-// resolves at compile time after unrolling).  The first value added for a key
-// initialises its sum; later values are added in call order.
-template <int CAP>
-struct SortedAcc {
-    int key[CAP];
-    double val[CAP];
-    int len;
-
-    __device__ __forceinline__ void clear() { len = 0; }
-
-    // Returns false (and leaves the list unchanged) when a new key does not fit.
-    template <bool WITH_VAL>
-    __device__ __forceinline__ bool add(int k, double x) {
-        int pos = 0;
-        bool found = false;
-#pragma unroll
-        for (int t = 0; t < CAP; ++t) {
-            if (t < len) {
-                if (key[t] < k) pos = t + 1;
-                if (key[t] == k) {
-                    found = true;
-                    if (WITH_VAL) val[t] += x;
-                }
-            }
-        }
-        if (found) return true;
-        if (len == CAP) return false;
-#pragma unroll
-        for (int t = CAP - 1; t > 0; --t) {
-            if (t > pos && t <= len) {
-                key[t] = key[t - 1];
-                if (WITH_VAL) val[t] = val[t - 1];
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < CAP; ++t) {
-            if (t == pos) {
-                key[t] = k;
-                if (WITH_VAL) val[t] = x;
-            }
-        }
-        ++len;
-        return true;
-    }
-};
 
 }  // namespace amg

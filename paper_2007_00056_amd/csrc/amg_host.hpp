@@ -59,7 +59,7 @@ void* pinned_get();
 void pinned_put(void* p);
 // Pinned host words for small read-backs (per thread, kept for the process).
 // (mapped into the device and coherent: a kernel may write them, through the
-// device address *dev, for the host to read once the stream has finished)
+// device address *dev, and the host read them meanwhile, see kPassWords)
 int* pinned_words(int** dev = nullptr);
 int read_int(const int* d, hipStream_t s);
 void raise_err_word(int e, const char* where);

@@ -13,7 +13,7 @@ enum : int {
     ERR_NONFINITE = 2,   // NaN or Inf value
     ERR_DIAG = 4,        // missing or zero diagonal
     ERR_NONSYM = 8,      // pattern not structurally symmetric
-    ERR_SINGULAR = 16,   // dense coarsest LU met a zero pivot
+    ERR_SINGULAR = 16,   // the coarsest matrix has a zero pivot
 };
 
 constexpr int kUndecided = 0x3fffffff;  // round stamp of an undecided vertex

@@ -463,7 +463,7 @@ using Known = unsigned long long __attribute__((may_alias));
 
 // The tile of a workgroup: vertices off .. off + m - 1, their words in LDS.
 // The bits of lower edges from other tiles arrive in gw (set there by those
-// tiles) and are merged into the LDS word by the vertex's own thread; a
+// tiles) and are merged into the LDS word by a polling wave; a
 // lower tile reads a vertex's state from gw alone, since all lower edges below
 // its own come from its own tile or lower ones.
 struct Tile {
@@ -717,7 +717,7 @@ __device__ __forceinline__ void poll_choices(const HemState& S, const Tile& T, K
 //
 // Against rounds of ready vertices between barriers (the same matching):
 // the passes of a setup at 160^3 with smooth coefficients took 85 ms and take
-// 20 ms, those at 128^3 (constant coefficients) 6.8 ms and 4.2 ms.
+// 15 ms, those at 128^3 (constant coefficients) 6.8 ms and 3.9 ms.
 //
 // Past tmo wall-clock ticks a wave stops and sets cnt[7]; the other waves look at
 // it when they look at the clock, workgroups before they take a tile, so a pass
