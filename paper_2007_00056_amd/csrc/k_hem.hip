@@ -871,7 +871,10 @@ __global__ __launch_bounds__(NT) void k_hem_tile(HemState S, int rows, int* cnt,
                     done = true;
                 } else {
                     if (!(f & vConf)) {
-                        if (c.j >= 0) c.st = T.state(S, c.pos, c.xo, T.word(S, c.j));
+                        // one lane's reading: words change meanwhile, and lanes that
+                        // read differently would take different branches
+                        if (c.j >= 0)
+                            c.st = __builtin_amdgcn_readfirstlane(T.state(S, c.pos, c.xo, T.word(S, c.j)));
                         if (c.st == kGone) c = wave_choice(S, T, v, b, e1);
                         if (c.j < 0) {
                             f |= vConf;  // no neighbour left
